@@ -325,7 +325,6 @@ size_t carve(const Plan &P, char *base, Dev &d)
     d.nrec = c.take<uint32_t>(1);
     d.src_tot = P.src_tot;
     d.ticket = c.take<uint32_t>(8);
-    d.tq = c.take<uint32_t>(16);
     d.err = c.take<int32_t>(1);
     c.take<double>(2 * kDiagGrid);  // diag scratch (last region)
     return c.off;

@@ -181,9 +181,22 @@ struct Dev {
     // scan scratch, tickets, errors
     uint32_t *scanpart;       // [<= 1 << 16]
     uint32_t *ticket;         // [8]
-    uint32_t *tq;             // [16]: the FP64 pass's eight tile queues and its exit ticket
     int32_t *err;             // [1]
 };
+
+// The segment whose slot range holds `slot`.
+__device__ __forceinline__ int seg_of_slot(const Dev &d, int64_t slot)
+{
+    int lo = 0, hi = d.nseg;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (d.seg[mid].base <= slot)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
 
 // ---------------------------------------------------------------------------------------
 // Philox4x32 (Salmon et al., SC'11) with kPhiloxRounds = 7 rounds (reading R17: the

@@ -9,8 +9,8 @@ namespace pic {
 // Launch shape of the particle kernels.
 struct Launch {
     int block;   // threads per block of the FP64 kernels (64, 128 or 256)
-    int ppt;     // particles per thread per tile (FP32 pass: 4 or 8)
-    int grid;    // persistent blocks of the FP64 kernels (multiple of 8 for the XCD-aware mapping)
+    int ppt;     // particles per thread per tile of the FP32 pass (4 or 8)
+    int grid;    // the FP64 sort scatter's blocks / 8 (a multiple of 8 for the XCD-aware mapping)
     int window;  // widest LDS window span, in cells, of the FP32 pass and of the sorts
     int sort_ppt;  // particles per thread of the FP32 sort scatter
     int nt;        // fused FP32 pass: non-temporal particle loads and stores
@@ -23,6 +23,7 @@ enum StageBits : int { SB_PUSH = 1, SB_COLLIDE = 2, SB_DEPOSIT = 4, SB_HIST = 8 
 // is false (the caller launched it).
 hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f64, int stages, int hist,
                             bool with_params = true);
+hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist);
 hipError_t launch_field_energy(const Dev &d, hipStream_t s);
 // After a pass with the COLLIDE stage: the FP32 form's candidate kernel (no-op for FP64,
 // whose pass scatters in place).

@@ -1,14 +1,8 @@
 // pic_kernels.hip -- gfx950 kernels of the electrostatic 1D3V PIC Monte Carlo step.
 //
 // This file holds the field solve, the birth ranking and placement, particle loading,
-// diagnostics, the scans of the sort, and the FP64 (plain x, v) particle pass and sort
-// scatter; the FP32 cell+offset pass, candidates and sort are in pic_pass32.hip.  The FP64
-// pass covers every particle stage with one template: gather + Boris push + walls,
-// null-collision MC, cloud-in-cell deposit and the sort histogram are compile-time stage
-// bits, so its separate-stage verbs and its fused step run the same per-particle code.  It
-// streams each segment's slots once, coalesced, with persistent blocks that take tiles from
-// per-XCD queues and steal from the others when theirs is empty (load balancing inside the
-// GPU), and deposits with FP64 atomics, each tile's shares merged first in an LDS window.
+// diagnostics, the scans of the sort, and the FP64 sort scatter; the FP32 cell+offset pass
+// and sort are in pic_pass32.hip, the FP64 (plain x, v) pass in pic_pass64.hip.
 #include <type_traits>
 
 #include "pic.h"
@@ -19,12 +13,11 @@
 namespace pic {
 
 // =======================================================================================
-// Tile scheduling of the persistent FP64 kernels: live tiles are enumerated over all
-// segments.  The particle pass takes them from queues (tq_grab); the sort scatter gives
-// block b a contiguous run of them.  Blocks are dispatched round-robin over the 8 XCDs, so block b is mapped
-// to run (b % 8) * (G / 8) + b / 8: each XCD gets one contiguous eighth of the particles
-// (and of the cells, once sorted), which keeps its L2 working set to its own part of the
-// grid.
+// Tile scheduling of the FP64 sort scatter: live tiles are enumerated over all segments and
+// block b takes a contiguous run of them.  Blocks are dispatched round-robin over the 8 XCDs,
+// so block b is mapped to run (b % 8) * (G / 8) + b / 8: each XCD gets one contiguous eighth
+// of the particles (and of the cells, once sorted), which keeps its L2 working set to its
+// own part of the grid.
 // =======================================================================================
 constexpr int kMaxSeg = 512;
 
@@ -68,24 +61,6 @@ __device__ __forceinline__ int seg_of_tile(const int64_t *s_tpre, int nseg, int6
     return lo;
 }
 
-// Single-GPU load balancing of the persistent FP64 pass (the analogue, inside one GPU, of
-// the paper's particle load balancing between ranks): the live tiles are split into eight
-// contiguous queues, one per XCD (queue x holds tiles [x T / 8, (x + 1) T / 8)), and a
-// block takes kGrabTiles tiles at a time from the queue of its own XCD (blocks are
-// dispatched round-robin over the XCDs), with the next grab in flight while it works; when
-// that queue is empty it takes from the others in turn.  Blocks that draw slow tiles (many
-// cell changes, births spread over the domain, atomics on shared nodes) simply take fewer,
-// so the launch ends when the work does, not when the slowest static share does.  A queue
-// counter is the number of tiles handed out; the last block to finish resets them.
-constexpr int kGrabTiles = 4;
-constexpr int kTileQueues = 8;
-
-// First tile of the next grab from queue x (a value >= the queue's end means empty).
-__device__ __forceinline__ int64_t tq_grab(const Dev &d, int x, int64_t T)
-{
-    return (int64_t)x * T / kTileQueues + (int64_t)atomicAdd(d.tq + x, (uint32_t)kGrabTiles);
-}
-
 __device__ __forceinline__ void block_run(int64_t T, int64_t &t0, int64_t &t1)
 {
     const int64_t G = gridDim.x;
@@ -93,263 +68,6 @@ __device__ __forceinline__ void block_run(int64_t T, int64_t &t0, int64_t &t1)
     if ((G & 7) == 0) vb = (int64_t)(blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
     t0 = vb * T / G;
     t1 = (vb + 1) * T / G;
-}
-
-// =======================================================================================
-// Block reductions of a few per-thread tallies, flushed to the striped counters.
-// =======================================================================================
-struct Tally {
-    uint32_t push, wl, wr, el, iz, cx;
-    double kel, ker, v2max;
-    __device__ void zero()
-    {
-        push = wl = wr = el = iz = cx = 0;
-        kel = ker = 0.0;
-        v2max = 0.0;
-    }
-};
-
-__device__ void flush_tally(const Dev &d, int seg, Tally &t, bool want_vmax)
-{
-    __shared__ double s_red[16][9];
-    const int lane = lane_id(), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    double v[9] = {(double)t.push, (double)t.wl, (double)t.wr, (double)t.el, (double)t.iz,
-                   (double)t.cx, t.kel, t.ker, t.v2max};
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = wave_sum_f64(v[k]);
-    v[8] = wave_max_f64(v[8]);
-    if (lane == 0)
-        for (int k = 0; k < 9; ++k) s_red[w][k] = v[k];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double a[9];
-        for (int k = 0; k < 9; ++k) a[k] = s_red[0][k];
-        for (int i = 1; i < nw; ++i) {
-            for (int k = 0; k < 8; ++k) a[k] += s_red[i][k];
-            a[8] = fmax(a[8], s_red[i][8]);
-        }
-        const int st = stripe_of_block();
-        unsigned long long *c = d.cnt + ((int64_t)st * d.nseg + seg) * C_NCNT;
-        if (a[0] != 0.0) atomicAdd(c + C_PUSH, (unsigned long long)a[0]);
-        if (a[1] != 0.0) atomicAdd(c + C_WALL_L, (unsigned long long)a[1]);
-        if (a[2] != 0.0) atomicAdd(c + C_WALL_R, (unsigned long long)a[2]);
-        if (a[3] != 0.0) atomicAdd(c + C_EL, (unsigned long long)a[3]);
-        if (a[4] != 0.0) atomicAdd(c + C_IZ, (unsigned long long)a[4]);
-        if (a[5] != 0.0) atomicAdd(c + C_CX, (unsigned long long)a[5]);
-        double *sm = d.sums + ((int64_t)st * d.nseg + seg) * S_NSUM;
-        if (a[6] != 0.0) unsafeAtomicAdd(sm + S_KE_L, a[6]);
-        if (a[7] != 0.0) unsafeAtomicAdd(sm + S_KE_R, a[7]);
-        if (want_vmax && a[8] > 0.0) {
-            const int half = 1 - *d.vcur;
-            atomicMax(d.vmax2 + ((int64_t)half * kCntStripes + st) * d.nseg + seg, dbits(a[8]));
-        }
-    }
-    __syncthreads();
-    t.zero();
-}
-
-// =======================================================================================
-// The FP64 particle pass (the FP32 form runs in k_pass32).  A persistent grid walks the
-// tiles of all segments; each stage is optional, so the same kernel serves the fused pass
-// and the separate stages.  The deposit adds each tile's shares into an LDS window of FP64
-// nodes, then each touched node into the FP64 node array with one atomic.
-// =======================================================================================
-enum Stage : int { ST_PUSH = 1, ST_COLLIDE = 2, ST_DEPOSIT = 4, ST_HIST = 8 };
-
-template <int STAGES, int PPT>
-__global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt)
-{
-    constexpr bool PUSH = STAGES & ST_PUSH;
-    constexpr bool COLL = STAGES & ST_COLLIDE;
-    constexpr bool DEPO = STAGES & ST_DEPOSIT;
-    constexpr bool HISTC = STAGES & ST_HIST;  // histogram-only pass
-    const bool hist = HISTC || (hist_rt != 0);
-    constexpr bool NEED_V = PUSH || COLL;
-    constexpr bool NEED_ID = COLL;
-
-    __shared__ int64_t s_tpre[kMaxSeg + 1];
-    __shared__ int64_t s_lim[2 * kMaxSeg];       // each segment's slots in use, from LDS
-    __shared__ double s_win[(DEPO || HISTC) ? kWin64 : 1];  // the tile's deposit (or count) window
-    __shared__ int s_mm[8];
-
-    const int BLOCK = blockDim.x;
-    const int64_t TILE = (int64_t)BLOCK * PPT;
-    sched_prefix(d, TILE, s_tpre, s_lim);
-    const int64_t T = s_tpre[d.nseg];
-    const int b = *d.cur;
-    const int64_t step = *d.step;
-    const uint32_t tag = (uint32_t)step;
-    const int st = stripe_of_block();
-
-    Tally tal;
-    tal.zero();
-    int tseg = -1;
-    // tile queues: own XCD's first, then the others in turn (see tq_grab)
-    __shared__ int64_t s_grab;
-    __shared__ bool s_last;
-    const int xq = (int)(blockIdx.x % kTileQueues);
-    int qi = 0;
-    if (threadIdx.x == 0) s_grab = tq_grab(d, xq, T);
-    __syncthreads();
-    int64_t g0 = s_grab;
-
-    for (;;) {
-        const int x = (xq + qi) % kTileQueues;
-        const int64_t qend = (int64_t)(x + 1) * T / kTileQueues;
-        if (g0 >= qend) {
-            // this queue is empty: try the next one, or stop after the last
-            if (++qi == kTileQueues) break;
-            __syncthreads();
-            if (threadIdx.x == 0) s_grab = tq_grab(d, (xq + qi) % kTileQueues, T);
-            __syncthreads();
-            g0 = s_grab;
-            continue;
-        }
-        // the next grab from the same queue, in flight while these tiles are processed
-        __syncthreads();
-        if (threadIdx.x == 0) s_grab = tq_grab(d, x, T);
-        const int64_t g1 = min(g0 + kGrabTiles, qend);
-    for (int64_t t = g0; t < g1; ++t) {
-        const int sg = __builtin_amdgcn_readfirstlane(seg_of_tile(s_tpre, d.nseg, t));
-        const SegC &S = d.seg[sg];
-        const EnsC &e = d.ens[S.ens];
-        const Seg64 G = seg64(S, e);  // gather, push and deposit constants in registers
-        const int s = S.species;
-        if (sg != tseg) {
-            if (tseg >= 0 && (PUSH || COLL)) flush_tally(d, tseg, tal, COLL);
-            tseg = sg;
-        }
-        // the tile's slots from LDS, so its loads wait on nothing in global memory
-        const int64_t lt = t - s_tpre[sg];
-        const int64_t first = s_lim[2 * sg] + lt * TILE;
-        const int64_t last = min(first + TILE, s_lim[2 * sg + 1]);
-
-        // every particle's loads are issued before any is tested, so the tile waits for
-        // memory once
-        PS<true> p[PPT];
-        bool live[PPT];
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int64_t i = first + (int64_t)k * BLOCK + threadIdx.x;
-            p[k].x = -1.0;
-            if (i < last) p_load<true>(d, b, i, p[k], NEED_V, NEED_ID);
-        }
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) live[k] = p_alive<true>(p[k]);
-        const double numax = COLL ? d.numax[sg] : 0.0;
-        const double pnull = COLL ? d.pnull[sg] : 0.0;
-        // The tile in phases, each over all its particles: push (every gather issued before
-        // any particle is pushed), collide, write back.  A particle still goes through push
-        // then collide, and the push constants are dead once the pushes are done.
-        if constexpr (PUSH) {
-            double Eg[PPT];
-            gather64<PPT>(d, G, p, Eg);
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                if (!live[k]) continue;
-                const int64_t i = first + (int64_t)k * BLOCK + threadIdx.x;
-                ++tal.push;
-                const int wall = p_push64(d, G, p[k], Eg[k]);
-                if (wall == 3) {
-                    p_kill<true>(p[k]);
-                    live[k] = false;
-                    d.x[b][i] = -1.0;
-                } else if (wall) {
-                    const double v2 = speed2_rn((double)p[k].vx, (double)p[k].vy, (double)p[k].vz);
-                    if (wall == 1) {
-                        ++tal.wl;
-                        tal.kel += S.halfmw * v2;
-                    } else {
-                        ++tal.wr;
-                        tal.ker += S.halfmw * v2;
-                    }
-                    p_kill<true>(p[k]);
-                    live[k] = false;
-                    d.x[b][i] = -1.0;
-                }
-            }
-        }
-        int ch[PPT];  // collision channel (-1: none)
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            ch[k] = -1;
-            if (COLL && live[k]) {
-                double ve[3], vi[3];
-                ch[k] = p_collide<true>(e, S, s, numax, pnull, tag, p[k], ve, vi);
-                if (ch[k] == 0)
-                    ++tal.el;
-                else if (ch[k] == 2)
-                    ++tal.cx;
-                else if (ch[k] == 1) {
-                    ++tal.iz;
-                    // birth record: slot in this block's stripe, or in the next ones when
-                    // it is full
-                    const BirthBuf bb = birth_buf(d, (int)(tag & 1u));
-                    int bst = st & (kStripes - 1);
-                    uint32_t slot = atomicAdd(bb.nbirth + bst, 1u);
-                    for (int a = 1; a < kStripes && (int64_t)slot >= d.birth_stripe_cap; ++a) {
-                        bst = (bst + 1) & (kStripes - 1);
-                        slot = atomicAdd(bb.nbirth + bst, 1u);
-                    }
-                    if ((int64_t)slot < d.birth_stripe_cap) {
-                        Birth &B = bb.births[(int64_t)bst * d.birth_stripe_cap + slot];
-                        B.pid = p[k].id;
-                        B.ens = S.ens;
-                        B.cell = 0;
-                        B.off = 0.f;
-                        B.x = p[k].x;
-                        for (int q = 0; q < 3; ++q) {
-                            B.ve[q] = ve[q];
-                            B.vi[q] = vi[q];
-                        }
-                        birth_mark(bb, e, p[k].id);
-                    } else {
-                        atomicOr(d.err, (int)E_CAP_BIRTH);
-                    }
-                    const double ve2 = speed2_rn(ve[0], ve[1], ve[2]);
-                    tal.v2max = fmax(tal.v2max, ve2);
-                    if (S.other >= 0) {
-                        const double vi2 = speed2_rn(vi[0], vi[1], vi[2]);
-                        const int half = 1 - *d.vcur;
-                        atomicMax(d.vmax2 + ((int64_t)half * kCntStripes + st) * d.nseg + S.other,
-                                  dbits(vi2));
-                    }
-                    if (DEPO) {
-                        // the new pair sits at the parent's position
-                        global_deposit64(d, S, s, p[k].x, hist);
-                        if (S.other >= 0) global_deposit64(d, d.seg[S.other], 1, p[k].x, hist);
-                    }
-                }
-                tal.v2max = fmax(tal.v2max, speed2_rn((double)p[k].vx, (double)p[k].vy, (double)p[k].vz));
-            }
-        }
-        // write back (the collide stage alone only the velocities it changed)
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            if (!(live[k] && (PUSH || ch[k] >= 0))) continue;
-            const int64_t i = first + (int64_t)k * BLOCK + threadIdx.x;
-            if (PUSH) d.x[b][i] = p[k].x;
-            d.dvx[b][i] = p[k].vx;
-            d.dvy[b][i] = p[k].vy;
-            d.dvz[b][i] = p[k].vz;
-        }
-        // deposit through the tile's LDS window (and sort histogram), by runs of equal cell
-        // across the wave's lanes
-        if constexpr (DEPO) {
-            tile_deposit64<PPT>(d, G, s, live, p, hist, s_win, s_mm);
-        } else if (HISTC) {
-            tile_deposit64<PPT, true>(d, G, s, live, p, true, s_win, s_mm);
-        }
-    }
-        __syncthreads();
-        g0 = s_grab;
-    }
-    if ((PUSH || COLL) && tseg >= 0) flush_tally(d, tseg, tal, COLL);
-    // the last block to finish resets the queues (every block has stopped taking tiles)
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(d.tq + kTileQueues, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (s_last && threadIdx.x <= kTileQueues) d.tq[threadIdx.x] = 0u;
 }
 
 // =======================================================================================
@@ -1719,31 +1437,6 @@ __global__ void k_diag(Dev d, int sg, double *out /* [grid][2] */)
         if (_e != hipSuccess) return _e;                        \
     } while (0)
 
-// The persistent FP64 pass: stages that push or collide run on half the grid, the deposit
-// and histogram on all of it (on the 4e7-particle slab, push and collide were fastest at two
-// blocks per CU and the deposit at three to four; more blocks slowed every stage).
-template <int STAGES>
-static hipError_t launch_particles_t(const Dev &d, const Launch &L, hipStream_t s, int hist)
-{
-    const int grid = (STAGES & (ST_PUSH | ST_COLLIDE)) ? std::max(8, L.grid / 16 * 8) : L.grid;
-    switch (L.ppt) {
-    case 1:
-        hipLaunchKernelGGL((k_particles<STAGES, 1>), dim3(grid), dim3(L.block), 0, s, d, hist);
-        break;
-    case 2:
-        hipLaunchKernelGGL((k_particles<STAGES, 2>), dim3(grid), dim3(L.block), 0, s, d, hist);
-        break;
-    case 8:
-        hipLaunchKernelGGL((k_particles<STAGES, 8>), dim3(grid), dim3(L.block), 0, s, d, hist);
-        break;
-    default:
-        hipLaunchKernelGGL((k_particles<STAGES, 4>), dim3(grid), dim3(L.block), 0, s, d, hist);
-        break;
-    }
-    LAUNCH_CHECK();
-    return hipSuccess;
-}
-
 hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f64, int stages, int hist,
                             bool with_params)
 {
@@ -1753,20 +1446,7 @@ hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f
         LAUNCH_CHECK();
     }
     if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt != 0);
-#define PIC_CASE(ST) \
-    case ST:         \
-        return launch_particles_t<ST>(d, L, s, hist);
-    switch (stages) {
-        PIC_CASE(ST_PUSH)
-        PIC_CASE(ST_COLLIDE)
-        PIC_CASE(ST_DEPOSIT)
-        PIC_CASE(ST_HIST)
-        PIC_CASE(ST_PUSH | ST_COLLIDE | ST_DEPOSIT)
-        PIC_CASE(ST_PUSH | ST_DEPOSIT)
-    default:
-        return hipErrorInvalidValue;
-    }
-#undef PIC_CASE
+    return launch_pass64(d, L.block, s, stages, hist);
 }
 
 hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist)

@@ -26,32 +26,6 @@ struct PS<true> {
 };
 
 template <bool F64>
-__device__ __forceinline__ void p_load(const Dev &d, int b, int64_t i, PS<F64> &p, bool need_v,
-                                       bool need_id)
-{
-    if constexpr (!F64) {
-        p.cell = d.cell[b][i];
-        if (p.cell == kDead) return;
-        p.off = d.off[b][i];
-        if (need_v) {
-            p.vx = d.fvx[b][i];
-            p.vy = d.fvy[b][i];
-            p.vz = d.fvz[b][i];
-        }
-    } else {
-        // every load is issued at once (a dead slot's velocity is read and not used), so a
-        // tile waits for memory once
-        p.x = d.x[b][i];
-        if (need_v) {
-            p.vx = d.dvx[b][i];
-            p.vy = d.dvy[b][i];
-            p.vz = d.dvz[b][i];
-        }
-    }
-    if (need_id) p.id = d.id[b][i];
-}
-
-template <bool F64>
 __device__ __forceinline__ bool p_alive(const PS<F64> &p)
 {
     if constexpr (!F64)
@@ -184,54 +158,6 @@ __device__ __forceinline__ int p_push64(const Dev &d, const Seg64 &G, PS<true> &
     // step reports PIC_ENONFINITE
     if (!(fabs(x) <= 1.0e300)) atomicOr(d.err, (int)E_NONFINITE);
     return (x < 0.0) ? 1 : 2;
-}
-
-// Gather (linear weighting of node E), Boris push, position update, walls.
-// Returns 0 alive, 1 absorbed at the left wall, 2 at the right wall.
-template <bool F64>
-__device__ __forceinline__ int p_push(const Dev &d, const SegC &S, const EnsC &e, PS<F64> &p)
-{
-    if constexpr (!F64) {
-        const float2 ec = d.Ecell[S.gbase + p.cell];
-        const float Ep = fmaf(p.off, ec.y, ec.x) + (float)e.E_ext;
-        const float h = (float)S.h;
-        const float t[3] = {(float)S.t[0], (float)S.t[1], (float)S.t[2]};
-        const float s[3] = {(float)S.s[0], (float)S.s[1], (float)S.s[2]};
-        boris<float>(h, t, s, Ep, p.vx, p.vy, p.vz);
-        float o = p.off + p.vx * (float)S.dtdx;
-        const float fl = floorf(o);
-        int c = p.cell + (int)fl;
-        o -= fl;
-        if (o >= 1.0f) {
-            o -= 1.0f;
-            c += 1;
-        }
-        p.off = o;
-        if (S.periodic) {
-            if (c < 0)
-                c += S.ncells;
-            else if (c >= S.ncells)
-                c -= S.ncells;
-            p.cell = c;
-            if (c < 0 || c >= S.ncells) {  // moved more than a period: not a valid state
-                atomicOr(d.err, (int)E_NONFINITE);
-                return 3;
-            }
-            return 0;
-        }
-        p.cell = c;
-        if (c < 0) return 1;
-        if (c >= S.ncells) return 2;
-        return 0;
-    } else {
-        const Seg64 G = seg64(S, e);
-        PS<true> q[1] = {p};
-        double Ep[1];
-        gather64<1>(d, G, q, Ep);
-        const int w = p_push64(d, G, q[0], Ep[0]);
-        p = q[0];
-        return w;
-    }
 }
 
 __device__ __forceinline__ void sc(float a, float *s, float *c) { sincosf(a, s, c); }
@@ -385,129 +311,6 @@ __device__ __forceinline__ void global_deposit64(const Dev &d, const SegC &S, in
     unsafeAtomicAdd(Q + j, 1.0 - f);
     unsafeAtomicAdd(Q + j1, f);
     if (hist) atomicAdd(d.cellcnt + S.cbase + j, 1u);
-}
-
-// The FP64 deposit window of one tile: nodes [base, base + n) accumulate in LDS (FP64 LDS
-// atomics) and are added to the node array once per tile; n = 0 sends every share to HBM.
-struct Win64 {
-    double *w;
-    int base, n;
-};
-
-// Cloud-in-cell deposit of one particle per lane (FP64 form), called by every lane of the
-// wave with the lane's cell (key < 0: none) and in-cell fraction: lanes hold consecutive
-// slots, which after a sort mostly share a cell, so the wave first sums the shares of each
-// run of consecutive lanes with the same cell (a segmented scan over the lanes) and the
-// last lane of each run adds the run's two shares, into the tile's LDS window when both
-// nodes lie in it and with one FP64 atomic per node otherwise, and its count to the sort
-// histogram.  `cnt_only` skips the shares.
-__device__ __forceinline__ void wave_deposit64(const Dev &d, const Seg64 &S, int s, int key, double f,
-                                               bool hist, bool cnt_only, const Win64 &W = Win64{nullptr, 0, 0})
-{
-    const int lane = lane_id();
-    const bool live = key >= 0;
-    double a = live ? 1.0 - f : 0.0, c = f;
-    uint32_t n = live ? 1u : 0u;
-    const int prev = __shfl_up(key, 1);
-    const bool head = lane == 0 || prev != key;
-    const unsigned long long heads = __ballot(head);
-    // first lane of this lane's run: the highest head at or below it
-    const unsigned long long below = heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull));
-    const int start = 63 - __clzll((long long)below);
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const double ta = __shfl_up(a, o), tc = __shfl_up(c, o);
-        const uint32_t tn = __shfl_up(n, o);
-        if (lane - o >= start) {
-            a += ta;
-            c += tc;
-            n += tn;
-        }
-    }
-    const bool tail = lane == kWave - 1 || ((heads >> (lane + 1)) & 1ull);
-    if (!tail || key < 0) return;
-    if (!cnt_only) {
-        const int r = key - W.base;
-        if (r >= 0 && r + 1 < W.n) {
-            // node wbase + r + 1 may be N of a periodic grid: the flush wraps it to node 0
-            unsafeAtomicAdd(W.w + r, a);
-            unsafeAtomicAdd(W.w + r + 1, c);
-        } else {
-            int j1 = key + 1;
-            if (S.periodic && j1 == S.ncells) j1 = 0;
-            double *Q = d.Qd + (int64_t)s * d.nodes_tot + S.gbase;
-            unsafeAtomicAdd(Q + key, a);
-            unsafeAtomicAdd(Q + j1, c);
-        }
-    }
-    if (hist) {
-        const int r = key - W.base;
-        if (cnt_only && r >= 0 && r < W.n)
-            unsafeAtomicAdd(W.w + r, (double)n);  // a count window: small exact integers
-        else
-            atomicAdd(d.cellcnt + S.cbase + key, n);
-    }
-}
-
-// Deposit of one FP64 tile through an LDS window over the nodes of its cells (at most
-// kWin64 nodes from the lowest cell of the tile; shares beyond it go to HBM atomics): the
-// window is cleared, the waves add their merged runs into it, and each nonzero node is
-// added to the node array with one FP64 atomic.  With COUNT the window holds the sort
-// histogram's counts per cell instead (the histogram-only pass), each touched cell added
-// with one atomic.  Called by every thread of the block; `s_mm` holds 8 ints.  The next
-// call's barriers order its clearing after this flush.
-constexpr int kWin64 = 1024;
-
-template <int PPT, bool COUNT = false>
-__device__ __forceinline__ void tile_deposit64(const Dev &d, const Seg64 &S, int s, const bool (&live)[PPT],
-                                               const PS<true> (&p)[PPT], bool hist, double *s_win, int *s_mm)
-{
-    int mn = INT32_MAX, mx = -1;
-    int key[PPT];
-    double f[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        f[k] = 0.0;
-        key[k] = live[k] ? (int)cell_of_x64(S, p[k].x, f[k]) : -1;
-        if (live[k]) {
-            mn = min(mn, key[k]);
-            mx = max(mx, key[k]);
-        }
-    }
-    mn = wave_min_i32(mn);
-    mx = wave_max_i32(mx);
-    const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    if (lane_id() == 0) {
-        s_mm[w] = mn;
-        s_mm[4 + w] = mx;
-    }
-    __syncthreads();
-    mn = s_mm[0];
-    mx = s_mm[4];
-    for (int i = 1; i < nw; ++i) {
-        mn = min(mn, s_mm[i]);
-        mx = max(mx, s_mm[4 + i]);
-    }
-    // nodes mn .. mx + 1 (cells mn .. mx for the counts)
-    const int n = mx >= 0 ? min(mx - mn + (COUNT ? 1 : 2), kWin64) : 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) s_win[i] = 0.0;
-    __syncthreads();
-    const Win64 W{s_win, mn, n};
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) wave_deposit64(d, S, s, key[k], f[k], COUNT || hist, COUNT, W);
-    __syncthreads();
-    double *Q = d.Qd + (int64_t)s * d.nodes_tot + S.gbase;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const double v = s_win[i];
-        if (v == 0.0) continue;
-        if constexpr (COUNT) {
-            atomicAdd(d.cellcnt + S.cbase + mn + i, (uint32_t)v);
-        } else {
-            int node = mn + i;
-            if (S.periodic && node >= S.ncells) node -= S.ncells;
-            unsafeAtomicAdd(Q + node, v);
-        }
-    }
 }
 
 }  // namespace pic

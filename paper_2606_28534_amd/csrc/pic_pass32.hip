@@ -22,19 +22,6 @@ enum : int { PS_PUSH = 1, PS_COLLIDE = 2, PS_DEPOSIT = 4, PS_HIST = 8 };
 // collision-candidate records staged in LDS per tile (more go straight to HBM)
 constexpr uint32_t kRecLds = 256;
 
-__device__ __forceinline__ int seg_of_slot(const Dev &d, int64_t slot)
-{
-    int lo = 0, hi = d.nseg;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (d.seg[mid].base <= slot)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
 // Block b takes tile b.  Workgroups go to the XCDs round-robin, so the tiles in use are
 // spread evenly over the eight XCDs however much of the slot capacity is filled.  (Giving
 // each XCD a contiguous eighth of the capacity instead, for L2 locality, left the XCDs that
