@@ -82,11 +82,7 @@ __global__ void __launch_bounds__(256) k_adj_b(const int32_t *xc, const double *
 __device__ double adj_block_scan(double v, double *s_w)
 {
     const int lane = lane_id(), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const double t = __shfl_up(v, o);
-        if (lane >= o) v += t;
-    }
+    v = wave_incl_scan(v);
     if (lane == kWave - 1) s_w[w] = v;
     __syncthreads();
     double add = 0.0;

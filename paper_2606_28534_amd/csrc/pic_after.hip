@@ -56,7 +56,7 @@ constexpr int kCandSegs = 12;  // segments a block stages (more: read from globa
 
 // Block `bid` (a kernel of its own, or the first blocks of the kernel that follows the pass).
 template <bool CXREL>
-__device__ void cand_body(const Dev &d, int tile, int64_t T, int hist, int bid, int ct)
+__device__ void cand_body(const Dev &d, int tile, int64_t T, int hist, int bid, int ct, bool depo = true)
 {
     __shared__ uint32_t s_pre[kCandTilesMax + 1];
     __shared__ int s_tj[kCandTilesMax];  // staged entry of each tile's segment (-1: not staged)
@@ -92,24 +92,14 @@ __device__ void cand_body(const Dev &d, int tile, int64_t T, int hist, int bid, 
             d.ctile[t] = 0u;
         }
         const uint32_t c = w & kCandCountMask;
-        uint32_t inc = c;
-#pragma unroll
-        for (int o = 1; o < kCandTilesMax; o <<= 1) {
-            const uint32_t n = __shfl_up(inc, o);
-            if (k >= o) inc += n;
-        }
+        static_assert(kCandTilesMax == kWave, "one lane per tile");
+        const uint32_t inc = wave_incl_scan(c);
         // a tile opens a new entry when it holds candidates and its segment differs from
         // that of the last earlier tile with candidates (segments grow with the slot, so
         // the keys of such tiles never decrease: the previous one is the running maximum
         // over the lanes below)
         const int key = c ? (int)((w >> 12) & 0x3FFu) : -1;
-        int pm = key;
-#pragma unroll
-        for (int o = 1; o < kCandTilesMax; o <<= 1) {
-            const int n = __shfl_up(pm, o);
-            if (k >= o) pm = max(pm, n);
-        }
-        int before = __shfl_up(pm, 1);
+        int before = lane_up<1>(wave_scan<kWave>(key, [](int x, int y) { return max(x, y); }));
         if (k == 0) before = -1;
         const bool head = key >= 0 && key != before;
         const unsigned long long hm = __ballot(head);
@@ -253,9 +243,9 @@ __device__ void cand_body(const Dev &d, int tile, int64_t T, int hist, int bid, 
         if (ch == 1) lb = atomicAdd(&s_nb, 1u);
         __syncthreads();
         if (threadIdx.x == 0 && s_nb) s_bbase = atomicAdd(bb.nbirth + bst, s_nb);
-        // the deposit of the new pair (the fused step's; the separate stages deposit all
+        // the deposit of the new pair (not in a step of separate stages, which deposits all
         // particles afresh), while the reservation is in flight
-        if (ch == 1) {
+        if (ch == 1 && depo) {
             const SegC Se = j >= 0 ? s_seg[j] : d.seg[sg];
             global_deposit32(d, Se, Se.species, p.cell, p.off, hist != 0);
             if (oth >= 0) {
@@ -306,9 +296,9 @@ __device__ void cand_body(const Dev &d, int tile, int64_t T, int hist, int bid, 
 }
 
 template <bool CXREL>
-__global__ void __launch_bounds__(256) k_cand32(Dev d, int tile, int64_t T, int hist, int ct)
+__global__ void __launch_bounds__(256) k_cand32(Dev d, int tile, int64_t T, int hist, int ct, int depo)
 {
-    cand_body<CXREL>(d, tile, T, hist, (int)blockIdx.x, ct);
+    cand_body<CXREL>(d, tile, T, hist, (int)blockIdx.x, ct, depo != 0);
 }
 
 
@@ -503,7 +493,7 @@ __global__ void __launch_bounds__(256) k_neutrals(Dev d)
 // null-collision bound.  The last block advances the slot and id counters.
 // Block `bid` of `nblk` (a kernel of its own, or a range of blocks of the kernel that
 // follows the pass).
-__device__ void source_body(const Dev &d, int hist, int bid, int nblk)
+__device__ void source_body(const Dev &d, int hist, int bid, int nblk, bool depo = true)
 {
     __shared__ bool s_last;
     const int64_t g = (int64_t)bid * blockDim.x + threadIdx.x;
@@ -553,7 +543,7 @@ __device__ void source_body(const Dev &d, int hist, int bid, int nblk)
             d.fvy[b][i] = vy;
             d.fvz[b][i] = vz;
             d.id[b][i] = d.next_id[sg] + (uint32_t)k;
-            global_deposit32(d, S, s, c, o, hist != 0);
+            if (depo) global_deposit32(d, S, s, c, o, hist != 0);
             const double v2 = speed2_rn((double)vx, (double)vy, (double)vz);
             if (s == 0)
                 v2e = v2;
@@ -626,7 +616,10 @@ __device__ void source_body(const Dev &d, int hist, int bid, int nblk)
     if (threadIdx.x == 0) d.ticket[4] = 0u;
 }
 
-__global__ void __launch_bounds__(256) k_source(Dev d, int hist) { source_body(d, hist, (int)blockIdx.x, (int)gridDim.x); }
+__global__ void __launch_bounds__(256) k_source(Dev d, int hist, int depo)
+{
+    source_body(d, hist, (int)blockIdx.x, (int)gridDim.x, depo != 0);
+}
 
 hipError_t launch_neutrals(const Dev &d, hipStream_t s)
 {
@@ -636,25 +629,25 @@ hipError_t launch_neutrals(const Dev &d, hipStream_t s)
     return hipSuccess;
 }
 
-hipError_t launch_source(const Dev &d, int hist, hipStream_t s)
+hipError_t launch_source(const Dev &d, int hist, hipStream_t s, bool depo)
 {
     if (d.src_tot == 0) return hipSuccess;
     const int64_t blocks = (d.src_tot + 255) / 256;
-    hipLaunchKernelGGL(k_source, dim3((unsigned)blocks), dim3(256), 0, s, d, hist);
+    hipLaunchKernelGGL(k_source, dim3((unsigned)blocks), dim3(256), 0, s, d, hist, depo ? 1 : 0);
     LAUNCH_CHECK();
     return hipSuccess;
 }
 
-hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot)
+hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool depo)
 {
     const int tile = 256 * ppt;
     const int64_t T = cap_tot / tile;
     const int ct = cand_tiles(T);
     const dim3 g((unsigned)((T + ct - 1) / ct));
     if (d.any_cx_rel)
-        hipLaunchKernelGGL(k_cand32<true>, g, dim3(256), 0, s, d, tile, T, hist, ct);
+        hipLaunchKernelGGL(k_cand32<true>, g, dim3(256), 0, s, d, tile, T, hist, ct, depo ? 1 : 0);
     else
-        hipLaunchKernelGGL(k_cand32<false>, g, dim3(256), 0, s, d, tile, T, hist, ct);
+        hipLaunchKernelGGL(k_cand32<false>, g, dim3(256), 0, s, d, tile, T, hist, ct, depo ? 1 : 0);
     return hipGetLastError();
 }
 

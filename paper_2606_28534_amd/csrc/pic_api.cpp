@@ -304,6 +304,10 @@ size_t carve(const Plan &P, char *base, Dev &d)
     d.g_tot = P.g_tot;
     d.ngt = P.g_tot / kGroupTile <= kMaxGroupTiles ? (int32_t)(P.g_tot / kGroupTile) : 0;
     d.gtile = c.take<uint32_t>(std::max<int64_t>(d.ngt, 1));
+    d.nbens = c.take<uint32_t>(kSmallEns);
+    int64_t chunks = 1;
+    for (const EnsC &E : P.ens) chunks = std::max(chunks, E.nchunks);
+    d.small = (P.nens <= kSmallEns && chunks <= kSmallChunks && d.ngt == 1) ? (chunks > 2 ? 4 : (int)chunks) : 0;
     d.ctile = c.take<uint32_t>(P.cap_tot / 1024 + 1);
     d.cellcnt = c.take<uint32_t>(P.cells_tot);
     d.cursor = c.take<uint32_t>(P.cells_tot);
@@ -448,6 +452,9 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
     const bool sort_now = !no_sort && (n + 1) % K == 0;
     hipError_t e;
     bool tm = c->timing && c->ev_used + 2 <= (int64_t)c->ev.size();
+    // without collisions, neutrals or a source nothing after the solve reads the step counter,
+    // so the solve advances it; with collisions the births' placement does
+    const bool adv_in_solve = !coll && d.ncap_tot == 0 && d.src_tot == 0;
     if (c->cfg.fused) {
         const bool piped = !f64 && K >= 2 && !no_sort;
         const bool sorting = piped && sort_now && ready;
@@ -456,7 +463,7 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
         const int hist = (prep || (sort_now && !sorting)) ? 1 : 0;
         // the solve's last block computes the collision bound, so the measurement hook
         // times the particle pass alone
-        if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, false, coll)) != hipSuccess) return e;
+        if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, false, coll, adv_in_solve)) != hipSuccess) return e;
         const int stages = coll ? (SB_PUSH | SB_COLLIDE | SB_DEPOSIT) : (SB_PUSH | SB_DEPOSIT);
         if (tm && (e = hipEventRecord(c->ev[c->ev_used], s)) != hipSuccess) return e;
         if (sorting)
@@ -471,7 +478,7 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
         if ((e = launch_after_pass(c, s, hist)) != hipSuccess) return e;
         if (coll) {
             if ((e = launch_births(d, f64, true, true, s)) != hipSuccess) return e;
-        } else if ((e = launch_advance(d, s)) != hipSuccess) {
+        } else if (!adv_in_solve && (e = launch_advance(d, s)) != hipSuccess) {
             return e;
         }
         if (sort_now && !sorting && (e = launch_sort(d, f64, c->L, s)) != hipSuccess) return e;
@@ -484,7 +491,9 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
         return hipSuccess;
     }
     ready = false;
-    if ((e = launch_solve(d, f64, c->P.chunks_tot, false, s)) != hipSuccess) return e;
+    // the solve clears the charge once it has read it (the stages before the deposit leave it
+    // alone) and computes the collision bound
+    if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, false, coll, adv_in_solve)) != hipSuccess) return e;
     if (tm && (e = hipEventRecord(c->ev[c->ev_used], s)) != hipSuccess) return e;
     if ((e = launch_particles(d, c->L, s, f64, SB_PUSH, 0)) != hipSuccess) return e;
     if (tm) {
@@ -493,14 +502,13 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
     }
     if ((e = launch_neutrals(d, s)) != hipSuccess) return e;
     if (coll) {
-        if ((e = launch_particles(d, c->L, s, f64, SB_COLLIDE, 0)) != hipSuccess) return e;
-        if ((e = launch_candidates(d, c->L, s, f64, 0)) != hipSuccess) return e;
+        if ((e = launch_particles(d, c->L, s, f64, SB_COLLIDE, 0, false)) != hipSuccess) return e;
+        if ((e = launch_candidates(d, c->L, s, f64, 0, false)) != hipSuccess) return e;
     }
-    if ((e = launch_source(d, 0, s)) != hipSuccess) return e;
-    if (coll && (e = launch_births(d, f64, true, false, s)) != hipSuccess) return e;
-    if ((e = launch_zero_q(d, f64, s)) != hipSuccess) return e;
+    if ((e = launch_source(d, 0, s, false)) != hipSuccess) return e;
+    if (coll && (e = launch_births(d, f64, true, true, s)) != hipSuccess) return e;
     if ((e = launch_particles(d, c->L, s, f64, SB_DEPOSIT, 0)) != hipSuccess) return e;
-    if ((e = launch_advance(d, s)) != hipSuccess) return e;
+    if (!coll && !adv_in_solve && (e = launch_advance(d, s)) != hipSuccess) return e;
     if (sort_now) {
         if ((e = launch_particles(d, c->L, s, f64, SB_HIST, 0)) != hipSuccess) return e;
         if ((e = launch_sort(d, f64, c->L, s)) != hipSuccess) return e;
@@ -1348,11 +1356,10 @@ hipError_t adj_forward_step(pic_ctx *c, hipStream_t s, int32_t *xc, float *xo, d
         if ((e = hipMemcpyAsync(xc, d.cell[0], n * 4, hipMemcpyDeviceToDevice, s)) != hipSuccess) return e;
         if ((e = hipMemcpyAsync(xo, d.off[0], n * 4, hipMemcpyDeviceToDevice, s)) != hipSuccess) return e;
     }
-    if ((e = launch_solve(d, false, c->P.chunks_tot, true, s)) != hipSuccess) return e;
+    if ((e = launch_solve(d, false, c->P.chunks_tot, true, s, false, false, true)) != hipSuccess) return e;
     if (E && (e = hipMemcpyAsync(E, d.E, c->P.ens[0].nnodes * 8, hipMemcpyDeviceToDevice, s)) != hipSuccess)
         return e;
-    if ((e = launch_particles(d, c->L, s, false, SB_PUSH | SB_DEPOSIT, 0)) != hipSuccess) return e;
-    return launch_advance(d, s);
+    return launch_particles(d, c->L, s, false, SB_PUSH | SB_DEPOSIT, 0);
 }
 
 }  // namespace

@@ -25,6 +25,8 @@ constexpr int kChunk = 1024;          // nodes per block in the field solve
 constexpr int kSolveThreads = 256;
 constexpr int kMaxEns = 256;          // ensembles per context
 constexpr int kMaxSmooth = 4;         // passes of the density filter
+constexpr int kSmallEns = 8;          // ensembles of a run whose solve is one launch
+constexpr int kSmallChunks = 4;       // and chunks of each
 // Birth ranking: a bit per parent id and a count per group of kGroupIds ids (a birth's rank
 // among its ensemble's births is the scanned count of the groups below its own plus the
 // bits below it in its group).
@@ -112,6 +114,8 @@ static_assert(__builtin_offsetof(Birth, pid) == 0 && __builtin_offsetof(Birth, e
 struct Dev {
     int32_t nseg, nens, nspecies, periodic, collisions;
     int32_t any_cx_rel;       // some ensemble uses relative-speed charge exchange (R26)
+    int32_t small;            // solve chunks per ensemble (1, 2 or 4) a one-launch solve takes
+                              // (solve_small); 0: the chunked solve
     const SegC *seg;
     const EnsC *ens;
     // particles (buffer b in {0,1}); FP32 and FP64 forms
@@ -157,6 +161,7 @@ struct Dev {
     uint32_t *gpre;           // [g_tot] exclusive scan of the current half's gcnt, per tile
                               // of kGroupTile groups when ngt > 0 (global otherwise)
     uint32_t *gtile;          // [max(ngt, 1)] group-count total of each tile
+    uint32_t *nbens;          // [kSmallEns] births of the step per ensemble (small runs)
     int32_t ngt;              // tiles of the tiled scan (0: the global three-kernel scan)
     int64_t g_tot;            // a multiple of 4096
     // null-collision candidates of the FP32 pass: tile t keeps its candidate slots in
@@ -244,41 +249,73 @@ __device__ __forceinline__ uint4 draw(uint32_t seed, int species, uint32_t id, u
 // Wave-level helpers (64 lanes).
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// One butterfly step: op(v of this lane, v of lane ^ M) for a commutative op.
+template <int M, typename T, typename Op>
+__device__ __forceinline__ T xor_step(T v, Op op)
+{
+    return op(v, __shfl_xor(v, M));
+}
+
+// Reduction over the 64 lanes, in every lane: butterfly steps 32, 16, 8, 4, 2, 1.
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op)
+{
+    v = xor_step<32>(v, op);
+    v = xor_step<16>(v, op);
+    v = xor_step<8>(v, op);
+    v = xor_step<4>(v, op);
+    v = xor_step<2>(v, op);
+    return xor_step<1>(v, op);
+}
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    return v;
-}
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    return v;
+    return wave_reduce(v, [](uint32_t a, uint32_t b) { return a + b; });
 }
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    return v;
+    return wave_reduce(v, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ double wave_max_f64(double v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = fmax(v, __shfl_xor(v, m));
-    return v;
+    return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 __device__ __forceinline__ int wave_min_i32(int v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = min(v, __shfl_xor(v, m));
-    return v;
+    return wave_reduce(v, [](int a, int b) { return min(a, b); });
 }
 __device__ __forceinline__ int wave_max_i32(int v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v = max(v, __shfl_xor(v, m));
+    return wave_reduce(v, [](int a, int b) { return max(a, b); });
+}
+
+// v of lane - O.
+template <int O, typename T>
+__device__ __forceinline__ T lane_up(T v)
+{
+    return __shfl_up(v, O);
+}
+
+// Inclusive scan with op(v, v of a lower lane) over the first N lanes of a wave (N a power of
+// two; the steps beyond N are left out and the lanes from N on hold no scan).
+template <int N, typename T, typename Op>
+__device__ __forceinline__ T wave_scan(T v, Op op)
+{
+    const int lane = __lane_id();
+    auto step = [&](T up, int o) {
+        if (lane >= o) v = op(v, up);
+    };
+    step(lane_up<1>(v), 1);
+    if constexpr (N > 2) step(lane_up<2>(v), 2);
+    if constexpr (N > 4) step(lane_up<4>(v), 4);
+    if constexpr (N > 8) step(lane_up<8>(v), 8);
+    if constexpr (N > 16) step(lane_up<16>(v), 16);
+    if constexpr (N > 32) step(lane_up<32>(v), 32);
     return v;
+}
+template <int N = kWave, typename T>
+__device__ __forceinline__ T wave_incl_scan(T v)
+{
+    return wave_scan<N>(v, [](T a, T b) { return a + b; });
 }
 
 // Double bits of a non-negative value order like unsigned integers.

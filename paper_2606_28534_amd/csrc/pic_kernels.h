@@ -26,8 +26,9 @@ hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f
 hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist);
 hipError_t launch_field_energy(const Dev &d, hipStream_t s);
 // After a pass with the COLLIDE stage: the FP32 form's candidate kernel (no-op for FP64,
-// whose pass scatters in place).
-hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist);
+// whose pass scatters in place).  Without `depo` the new pairs are left to a later deposit of
+// every particle (so too in launch_source).
+hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist, bool depo = true);
 hipError_t launch_init(const Dev &d, bool f64, int sg, int64_t n, int64_t ppc, int init_mode,
                        double vth, double amp, int mode, hipStream_t s);
 hipError_t launch_vmax(const Dev &d, bool f64, hipStream_t s);
@@ -35,9 +36,11 @@ hipError_t launch_zero_q(const Dev &d, bool f64, hipStream_t s);
 // The field solve; with `with_births` its two kernels also scan and place the previous
 // step's births in extra blocks (needs births_fit_solve: the one-block group scan); with
 // `with_params` extra blocks of the first kernel reduce the striped speed maxima per segment
-// and the second kernel's last block computes the null-collision bound from them.
+// and the second kernel's last block computes the null-collision bound from them; `advance`
+// advances the step counter (with_births always does).  Small runs (Dev::small) take one
+// kernel for all of it.
 hipError_t launch_solve(const Dev &d, bool f64, int64_t nchunks, bool zero_q, hipStream_t s,
-                        bool with_births = false, bool with_params = false);
+                        bool with_births = false, bool with_params = false, bool advance = false);
 bool births_fit_solve(const Dev &d);
 hipError_t launch_field_stats(const Dev &d, bool f64, int64_t nchunks, hipStream_t s);
 hipError_t launch_params(const Dev &d, hipStream_t s);
@@ -54,7 +57,7 @@ hipError_t launch_sort_prepare(const Dev &d, hipStream_t s);
 hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, bool nt);
 hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot,
                          bool nt);
-hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot);
+hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool depo);
 // the fused step's candidates, neutrals and source as one launch (FP32 form)
 hipError_t launch_after(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool coll);
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t nwords, bool nt, hipStream_t s);
@@ -77,6 +80,6 @@ hipError_t launch_moments(const Dev &d, bool f64, int sg, int64_t nn, double *ou
 // Recycled neutrals of the step (stream, recycle the absorbed ions the pass listed, flip
 // buffers) and the volumetric source pairs (FP32 form; no-ops when unused).
 hipError_t launch_neutrals(const Dev &d, hipStream_t s);
-hipError_t launch_source(const Dev &d, int hist, hipStream_t s);
+hipError_t launch_source(const Dev &d, int hist, hipStream_t s, bool depo = true);
 
 }  // namespace pic

@@ -9,6 +9,7 @@
 #include "pic_device.h"
 #include "pic_kernels.h"
 #include "pic_particle.h"
+#include "pic_solve.h"
 
 namespace pic {
 
@@ -171,89 +172,11 @@ __global__ void k_vmax(Dev d)
 // at bounded walls.  Periodic runs add the uniform background that cancels the deposited
 // charge and shift phi to zero mean afterwards.
 // =======================================================================================
-__device__ __forceinline__ double node_vol(const EnsC &e, int64_t j)
-{
-    if (!e.periodic && (j == 0 || j == e.ncells)) return 0.5 * e.dx;
-    return e.dx;
-}
-
-// Reading R23: p passes of the 1-2-1 filter equal one binomial stencil of width 2p + 1
-// (weights C(2p, p + i) / 4^p) applied to the periodic extension of rho, or on a bounded
-// grid to its even extension across both walls (a pass maps an even extension to an even
-// extension, with rho_{-1} = rho_1 at the wall, so the passes compose into the stencil).
-// Each node therefore reads its 2p + 1 neighbours once instead of p sweeps over the grid.
-// smooth_fold maps a node index in [-p, nn - 1 + p] onto the grid (p <= 4 and N >= 2, so a
-// couple of wraps or reflections at most).
-__device__ __forceinline__ int64_t smooth_fold(const EnsC &e, int64_t m)
-{
-    const int64_t n = e.ncells;
-    if (e.periodic) {
-        while (m < 0) m += n;
-        while (m >= n) m -= n;
-        return m;
-    }
-    for (int it = 0; it < 8; ++it) {
-        if (m < 0)
-            m = -m;
-        else if (m > n)
-            m = 2 * n - m;
-        else
-            break;
-    }
-    return m;
-}
-
-// One species' deposited charge at NQ nodes (offsets into the node arrays), all loads
-// issued before the first is used.
-template <bool F64, int NQ>
-__device__ __forceinline__ void node_q_row(const Dev &d, int64_t row, const int64_t (&at)[NQ],
-                                           double (&Q)[NQ])
-{
-    if constexpr (!F64) {
-        unsigned long long raw[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) raw[q] = d.Qi[row + at[q]];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) Q[q] = (double)(long long)raw[q] * (1.0 / kFix);
-    } else {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) Q[q] = d.Qd[row + at[q]];
-    }
-}
-
-// Charge density sum_s q_s w_s Q_s(j) / vol(j) at NQ nodes per thread (entries with ok[q]
-// false give 0).  The loads are unconditional (node 0 stands in for unused entries), so the
-// thread waits for memory once instead of once per node and species.
-template <bool F64, int NQ>
-__device__ __forceinline__ void node_rho_raw(const Dev &d, const EnsC &e, const int64_t (&j)[NQ],
-                                             const bool (&ok)[NQ], double (&r)[NQ])
-{
-    static_assert(sizeof(e.qw) / sizeof(e.qw[0]) == 2, "at most two charged species");
-    int64_t at[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) at[q] = e.gbase + (ok[q] ? j[q] : 0);
-    double Q0[NQ], Q1[NQ];
-    node_q_row<F64, NQ>(d, 0, at, Q0);
-    const bool two = e.nspecies > 1;
-    if (two) node_q_row<F64, NQ>(d, d.nodes_tot, at, Q1);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        double c = 0.0;
-        c += e.qw[0] * Q0[q];
-        if (two) c += e.qw[1] * Q1[q];
-        r[q] = ok[q] ? c / node_vol(e, j[q]) : 0.0;
-    }
-}
-
 // Block-wide inclusive scan of one double per thread (256 threads).
 __device__ double block_incl_scan(double v, double *s_buf)
 {
     const int lane = lane_id(), w = threadIdx.x / kWave;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const double n = __shfl_up(v, o);
-        if (lane >= o) v += n;
-    }
+    v = wave_incl_scan(v);
     if (lane == kWave - 1) s_buf[w] = v;
     __syncthreads();
     double add = 0.0;
@@ -308,7 +231,6 @@ __device__ __forceinline__ int chunk_ens(const Dev &d, int64_t k)
     return lo;
 }
 
-constexpr int kNodesPerThread = kChunk / kSolveThreads;
 // Blocks that place a step's births: the births grow with the particles (about 4.5e-4 of
 // the electrons per step), so the block count does too, from 64 (enough for the 4e7-particle
 // slab's ten thousand, under one per thread) to 256 from 5e8 slots on (64 batched
@@ -500,18 +422,6 @@ __device__ void compute_params_reduced(const Dev &d)
 
 __global__ void k_params(Dev d) { compute_params(d); }
 
-// Inclusive prefix sum over the 64 lanes of a wave (FP64).
-__device__ __forceinline__ double wave_incl_scan_f64(double v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const double n = __shfl_up(v, o);
-        if (lane >= o) v += n;
-    }
-    return v;
-}
-
 template <bool F64>
 __device__ void solve2_body(const Dev &d, int zero_q)
 {
@@ -568,9 +478,9 @@ __device__ void solve2_body(const Dev &d, int zero_q)
             n += gg[A_CNT];
             a += A;
         }
-        const double apre = wave_incl_scan_f64(a) - a;  // C_pre at c0
+        const double apre = wave_incl_scan(a) - a;  // C_pre at c0
         const double fin = n * apre + g;                // this range's sum of C over m
-        const double fpre = wave_incl_scan_f64(fin) - fin;
+        const double fpre = wave_incl_scan(fin) - fin;
         const double Stot = wave_sum_f64(fin), Ctot = wave_sum_f64(a);
         const double nab0 = wave_sum_f64(nabs[0]), nab1 = wave_sum_f64(nabs[1]);
         const int64_t me = k - e.chunk0;
@@ -742,8 +652,10 @@ __device__ void solve2_body(const Dev &d, int zero_q)
 // a kernel of its own; it reads max |E|, which other blocks of this launch updated, through
 // an atomic, which needs no fence.
 template <bool F64>
-__global__ void __launch_bounds__(kSolveThreads) k_solve2(Dev d, int zero_q, int nchunks, int params)
+__global__ void __launch_bounds__(kSolveThreads) k_solve2(Dev d, int zero_q, int nchunks, int params, int advance)
 {
+    // (without births nothing else in this launch reads the step counter)
+    if (advance && blockIdx.x == 0 && threadIdx.x == 0) *d.step += 1;
     if ((int)blockIdx.x >= nchunks)
         birth_place_body<F64>(d, 1, 1, (int)blockIdx.x - nchunks, (int)gridDim.x - nchunks);
     else
@@ -855,11 +767,7 @@ __device__ uint32_t block_excl_scan_u32(uint32_t v, uint32_t *s_buf, uint32_t &t
 {
     const int lane = lane_id(), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
     uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t n = __shfl_up(x, o);
-        if (lane >= o) x += n;
-    }
+    x = wave_incl_scan(x);
     if (lane == kWave - 1) s_buf[w] = x;
     __syncthreads();
     uint32_t add = 0, tot = 0;
@@ -962,11 +870,7 @@ __device__ __forceinline__ void stripe_prefix(const BirthBuf &bb, int64_t cap, u
     const int lane = lane_id();
     const uint32_t v = lane < kStripes ? (uint32_t)min((int64_t)bb.nbirth[lane], cap) : 0u;
     uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t n = __shfl_up(inc, o);
-        if (lane >= o) inc += n;
-    }
+    inc = wave_incl_scan(inc);
     if (lane < kStripes) s_pre[lane] = inc - v;
     if (lane == kStripes - 1) s_pre[kStripes] = inc;
 }
@@ -1031,11 +935,7 @@ __device__ void group_tile_scan_body(const Dev &d, int t)
     for (int r = 0; r < kRows; ++r) {
         const uint32_t ls = v[r].x + v[r].y + v[r].z + v[r].w;
         uint32_t inc = ls;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t n = __shfl_up(inc, o);
-            if (lane >= o) inc += n;
-        }
+        inc = wave_incl_scan(inc);
         const uint32_t ex = carry + inc - ls;
         out[r * kWave + lane] = make_uint4(ex, ex + v[r].x, ex + v[r].x + v[r].y, ex + v[r].x + v[r].y + v[r].z);
         carry += __shfl(inc, kWave - 1);
@@ -1092,34 +992,26 @@ __device__ __forceinline__ uint32_t group_prefix(const Dev &d, const uint32_t *s
     return s_tb[i / kGroupTile] + d.gpre[i];
 }
 
-template <bool F64>
-__device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk)
+// After a placement, by one block: the previous step's birth counts (with `deferred`), the
+// half of the speed maxima that was current (it accumulates the next step's) and the step
+// tallies of that half restart.
+__device__ __forceinline__ void place_reset(const Dev &d, int deferred, const BirthBuf &ob, int vc)
 {
-    __shared__ uint32_t s_pre[kStripes + 1];
-    __shared__ uint32_t s_old[kStripes + 1];
-    __shared__ uint32_t s_tb[kMaxGroupTiles];
-    __shared__ bool s_last;
-    __shared__ PlaceEns s_pe[PIC_MAX_ENSEMBLES];
-    __shared__ PlaceSeg s_ps[2 * PIC_MAX_ENSEMBLES];
-    const int64_t step = *d.step;
-    const int vc = *d.vcur;
-    const int p = (int)(step & 1);
-    const BirthBuf bb = birth_buf(d, p), ob = birth_buf(d, 1 - p);
-    if (threadIdx.x < kWave) {
-        stripe_prefix(bb, d.birth_stripe_cap, s_pre);
-        if (deferred) stripe_prefix(ob, d.birth_stripe_cap, s_old);
-    }
-    for (int en = threadIdx.x; en < d.nens; en += blockDim.x) {
-        const EnsC &e = d.ens[en];
-        s_pe[en] = PlaceEns{e.bm_base, e.grp_base, e.idcap, {e.seg[0], e.seg[1]}, e.nspecies};
-    }
-    for (int sg = threadIdx.x; sg < d.nseg; sg += blockDim.x) {
-        const SegC &S = d.seg[sg];
-        s_ps[sg] = PlaceSeg{S.base, S.cap, d.n_slots[sg], d.next_id[sg]};
-    }
-    stage_tile_bases(d, s_tb);
-    __syncthreads();
-    const int64_t M = s_pre[kStripes], Mo = deferred ? (int64_t)s_old[kStripes] : 0;
+    if (deferred)
+        for (int i = threadIdx.x; i < kStripes; i += blockDim.x) ob.nbirth[i] = 0u;
+    for (int64_t i = threadIdx.x; i < (int64_t)kCntStripes * d.nseg; i += blockDim.x)
+        d.vmax2[(int64_t)vc * kCntStripes * d.nseg + i] = 0ull;
+    for (int64_t i = threadIdx.x; i < (int64_t)kCntStripes * d.nseg * T_NSTEP; i += blockDim.x)
+        d.ssum[(int64_t)vc * kCntStripes * d.nseg * T_NSTEP + i] = 0.0;
+}
+
+// Places the step's births (k < M) and clears the marks of the previous step's (k < Mo): block
+// `bid` of `nblk`.  pre(i) is the births' scanned group count at group index i.
+template <bool F64, typename Pre>
+__device__ __forceinline__ void place_births(const Dev &d, const BirthBuf &bb, const BirthBuf &ob, int64_t M,
+                                             int64_t Mo, const uint32_t *s_pre, const uint32_t *s_old,
+                                             const PlaceEns *s_pe, const PlaceSeg *s_ps, int bid, int nblk, Pre pre)
+{
     const int b = *d.cur;
     // this step's births (k < M) and, with `deferred`, the previous step's (k < Mo), whose
     // bits and group counts are cleared; both records are loaded before either is used
@@ -1144,7 +1036,7 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
         const PlaceEns &E = s_pe[B.ens];
         const uint32_t pid = B.pid;
         const int64_t g = pid / kGroupIds;
-        const uint32_t r = group_prefix(d, s_tb, E.grp_base + g) - group_prefix(d, s_tb, E.grp_base) +
+        const uint32_t r = pre(E.grp_base + g) - pre(E.grp_base) +
                            rank_in_group(bb.bitmap + E.bm_base + g * kGroupWords, pid);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -1178,6 +1070,38 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
             d.id[b][i] = P.next_id + r;
         }
     }
+}
+
+template <bool F64>
+__device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk)
+{
+    __shared__ uint32_t s_pre[kStripes + 1];
+    __shared__ uint32_t s_old[kStripes + 1];
+    __shared__ uint32_t s_tb[kMaxGroupTiles];
+    __shared__ bool s_last;
+    __shared__ PlaceEns s_pe[PIC_MAX_ENSEMBLES];
+    __shared__ PlaceSeg s_ps[2 * PIC_MAX_ENSEMBLES];
+    const int64_t step = *d.step;
+    const int vc = *d.vcur;
+    const int p = (int)(step & 1);
+    const BirthBuf bb = birth_buf(d, p), ob = birth_buf(d, 1 - p);
+    if (threadIdx.x < kWave) {
+        stripe_prefix(bb, d.birth_stripe_cap, s_pre);
+        if (deferred) stripe_prefix(ob, d.birth_stripe_cap, s_old);
+    }
+    for (int en = threadIdx.x; en < d.nens; en += blockDim.x) {
+        const EnsC &e = d.ens[en];
+        s_pe[en] = PlaceEns{e.bm_base, e.grp_base, e.idcap, {e.seg[0], e.seg[1]}, e.nspecies};
+    }
+    for (int sg = threadIdx.x; sg < d.nseg; sg += blockDim.x) {
+        const SegC &S = d.seg[sg];
+        s_ps[sg] = PlaceSeg{S.base, S.cap, d.n_slots[sg], d.next_id[sg]};
+    }
+    stage_tile_bases(d, s_tb);
+    __syncthreads();
+    const int64_t M = s_pre[kStripes], Mo = deferred ? (int64_t)s_old[kStripes] : 0;
+    place_births<F64>(d, bb, ob, M, Mo, s_pre, s_old, s_pe, s_ps, bid, nblk,
+                      [&](int64_t i) { return group_prefix(d, s_tb, i); });
     // The last block only updates counters that no block of this launch reads after taking
     // its ticket (each block staged them before its first barrier), and the next kernel
     // sees every write, so no device-scope fence is needed here; on gfx950 such a fence
@@ -1198,18 +1122,11 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
             if (m) atomicAdd(d.cnt + ((int64_t)0 * d.nseg + sg) * C_NCNT + C_CREATED, (unsigned long long)m);
         }
     }
-    if (deferred)
-        for (int i = threadIdx.x; i < kStripes; i += blockDim.x) ob.nbirth[i] = 0u;
+    place_reset(d, deferred, ob, vc);
     if (threadIdx.x == 0) {
         d.ticket[1] = 0u;
         atomicExch(d.vcur, 1 - vc);  // atomic: the bound may be computed in this launch
     }
-    // the half that held the current maxima accumulates the next step's, and the step
-    // tallies of that half restart
-    for (int64_t i = threadIdx.x; i < (int64_t)kCntStripes * d.nseg; i += blockDim.x)
-        d.vmax2[(int64_t)vc * kCntStripes * d.nseg + i] = 0ull;
-    for (int64_t i = threadIdx.x; i < (int64_t)kCntStripes * d.nseg * T_NSTEP; i += blockDim.x)
-        d.ssum[(int64_t)vc * kCntStripes * d.nseg * T_NSTEP + i] = 0.0;
     if (threadIdx.x == 0 && advance) *d.step = step + 1;
 }
 
@@ -1217,6 +1134,130 @@ template <bool F64>
 __global__ void __launch_bounds__(256) k_birth_place(Dev d, int deferred, int advance)
 {
     birth_place_body<F64>(d, deferred, advance, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// =======================================================================================
+// Small runs (Dev::small > 0): at most kSmallEns ensembles of at most G chunks each and one
+// tile of birth groups.  Block `en` < nsolve solves ensemble en (solve_small); with `births`,
+// kSmallPlace more blocks rank and place the step's births, each scanning the one tile of
+// group counts into LDS for itself, and the last block to take its ticket updates the
+// placement's counters; `params`: block en also computes its segments' collision bounds.
+// Such a step is bound by its chain of dependent launches (about 5 us each, whatever they
+// do), so this one launch stands for k_solve1, k_solve2 and k_phi_shift, and for the births'
+// k_group_scan and k_birth_place: the 2048-cell periodic run's four launches beside its pass
+// took 22.5 us a step and this one 12.2, the 256-cell collisional run's pair 15.3 us and this
+// one 10.4.  Above four chunks per ensemble a block could not hold a chunk per group of
+// threads (1024 at most), and the chunked solve is no slower (13 + 9 us for 20 chunks).
+// =======================================================================================
+constexpr int kSmallPlace = 4;
+
+template <bool F64, int G>
+__global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nsolve, int zero_q, int births,
+                                                                  int deferred, int params, int advance)
+{
+    __shared__ SmallSolve<G> sh;
+    __shared__ bool s_last;
+    const int vc = *d.vcur;
+    const int64_t step = *d.step;
+    const int pb = (int)(step & 1);
+    const BirthBuf bb = birth_buf(d, pb), ob = birth_buf(d, 1 - pb);
+    if ((int)blockIdx.x < nsolve) {
+        const int ei = (int)blockIdx.x, w = (int)threadIdx.x / kWave;
+        const EnsC e = d.ens[ei];
+        // the speed maxima of the ensemble's segments (a wave each), in the half the births'
+        // placement makes current; read before the ticket that lets it be cleared
+        double m2 = 0.0;
+        if (params && w < e.nspecies) m2 = seg_vmax2(d, w == 0 ? e.seg[0] : e.seg[1], births ? 1 - vc : vc);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (births && threadIdx.x == 0) s_last = (atomicAdd(d.ticket + 6, 1u) == gridDim.x - 1);
+        const double emax = solve_small<F64, G, true>(d, e, ei, zero_q, sh, d.Ecell + e.gbase, d.E + e.gbase);
+        if (params && w < e.nspecies && lane_id() == 0) {
+            const int sg = w == 0 ? e.seg[0] : e.seg[1];
+            double numax, pnull;
+            seg_bound(d.seg[sg], e, m2, emax, numax, pnull);
+            d.numax[sg] = numax;
+            d.pnull[sg] = pnull;
+        }
+    } else {
+        __shared__ uint32_t s_pre[kStripes + 1], s_old[kStripes + 1], s_buf[16];
+        __shared__ uint32_t s_gp[kGroupTile];
+        __shared__ PlaceEns s_pe[kSmallEns];
+        __shared__ PlaceSeg s_ps[2 * kSmallEns];
+        const int bid = (int)blockIdx.x - nsolve;
+        if (threadIdx.x < kWave) {
+            stripe_prefix(bb, d.birth_stripe_cap, s_pre);
+            if (deferred) stripe_prefix(ob, d.birth_stripe_cap, s_old);
+        }
+        if ((int)threadIdx.x < d.nens) {
+            const EnsC &e = d.ens[threadIdx.x];
+            s_pe[threadIdx.x] = PlaceEns{e.bm_base, e.grp_base, e.idcap, {e.seg[0], e.seg[1]}, e.nspecies};
+        }
+        if ((int)threadIdx.x < d.nseg) {
+            const SegC &S = d.seg[threadIdx.x];
+            s_ps[threadIdx.x] = PlaceSeg{S.base, S.cap, d.n_slots[threadIdx.x], d.next_id[threadIdx.x]};
+        }
+        {
+            // exclusive scan of the tile's group counts, whole 16-byte vectors per thread
+            constexpr int kVec = kGroupTile / (4 * G * kSolveThreads);
+            uint4 v[kVec];
+            uint32_t sum = 0, tot;
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) v[i] = ((const uint4 *)bb.gcnt)[threadIdx.x * kVec + i];
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) sum += v[i].x + v[i].y + v[i].z + v[i].w;
+            uint32_t ex = block_excl_scan_u32(sum, s_buf, tot);
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) {
+                uint32_t *o = s_gp + (threadIdx.x * kVec + i) * 4;
+                o[0] = ex;
+                o[1] = (ex += v[i].x);
+                o[2] = (ex += v[i].y);
+                o[3] = (ex += v[i].z);
+                ex += v[i].w;
+            }
+        }
+        __syncthreads();
+        place_births<F64>(d, bb, ob, s_pre[kStripes], deferred ? (int64_t)s_old[kStripes] : 0, s_pre, s_old, s_pe,
+                          s_ps, bid, kSmallPlace, [&](int64_t i) { return s_gp[i]; });
+        // the births per ensemble, for the launch's last block (which may be another one)
+        if (bid == 0 && (int)threadIdx.x < d.nens) {
+            const PlaceEns &E = s_pe[threadIdx.x];
+            const int64_t ngrp = (E.idcap + kGroupIds - 1) / kGroupIds;
+            __hip_atomic_store(d.nbens + threadIdx.x, s_gp[E.grp_base + ngrp] - s_gp[E.grp_base], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    if (!births) {
+        if (advance && blockIdx.x == 0 && threadIdx.x == 0) *d.step = step + 1;
+        return;
+    }
+    if ((int)blockIdx.x >= nsolve) {
+        // every wave's memory operations are complete before the block takes its ticket
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (threadIdx.x == 0) s_last = (atomicAdd(d.ticket + 6, 1u) == gridDim.x - 1);
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // The last block updates what every block read before its ticket; the births per ensemble,
+    // from another block of this launch, went out and come in by device-scope atomics.
+    if (threadIdx.x == 0) d.ticket[6] = 0u;
+    if ((int)threadIdx.x < d.nens) {
+        const EnsC &e = d.ens[threadIdx.x];
+        const uint32_t m = __hip_atomic_load(d.nbens + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int s = 0; s < e.nspecies; ++s) {
+            const int sg = e.seg[s];
+            d.n_slots[sg] = min(d.n_slots[sg] + (int64_t)m, d.seg[sg].cap);
+            d.next_id[sg] += m;
+            if (m) atomicAdd(d.cnt + ((int64_t)0 * d.nseg + sg) * C_NCNT + C_CREATED, (unsigned long long)m);
+        }
+    }
+    place_reset(d, deferred, ob, vc);
+    if (threadIdx.x == 0) {
+        *d.vcur = 1 - vc;
+        if (advance) *d.step = step + 1;
+    }
 }
 
 // Clear one half (parity -1: the current step's): its bits and counts, then its birth counts.
@@ -1449,10 +1490,10 @@ hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f
     return launch_pass64(d, L.block, s, stages, hist);
 }
 
-hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist)
+hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist, bool depo)
 {
     if (f64) return hipSuccess;
-    return launch_cand32(d, L.ppt, s, hist, d.cap_tot);
+    return launch_cand32(d, L.ppt, s, hist, d.cap_tot, depo);
 }
 
 hipError_t launch_init(const Dev &d, bool f64, int sg, int64_t n, int64_t ppc, int init_mode,
@@ -1492,20 +1533,48 @@ hipError_t launch_zero_q(const Dev &d, bool f64, hipStream_t s)
 
 bool births_fit_solve(const Dev &d) { return d.ngt > 0; }
 
+template <bool F64>
+static hipError_t launch_solve_small(const Dev &d, int nsolve, int zero_q, int births, int deferred, int params,
+                                     int advance, hipStream_t s)
+{
+    const dim3 g((unsigned)(nsolve + (births ? kSmallPlace : 0)));
+    switch (d.small) {
+    case 1:
+        hipLaunchKernelGGL((k_solve_small<F64, 1>), g, dim3(kSolveThreads), 0, s, d, nsolve, zero_q, births, deferred,
+                           params, advance);
+        break;
+    case 2:
+        hipLaunchKernelGGL((k_solve_small<F64, 2>), g, dim3(2 * kSolveThreads), 0, s, d, nsolve, zero_q, births,
+                           deferred, params, advance);
+        break;
+    default:
+        hipLaunchKernelGGL((k_solve_small<F64, 4>), g, dim3(4 * kSolveThreads), 0, s, d, nsolve, zero_q, births,
+                           deferred, params, advance);
+        break;
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_solve(const Dev &d, bool f64, int64_t nchunks, bool zero_q, hipStream_t s,
-                        bool with_births, bool with_params)
+                        bool with_births, bool with_params, bool advance)
 {
     const int nc = (int)nchunks, zq = zero_q ? 1 : 0;
+    const int par = with_params ? 1 : 0, bir = with_births ? 1 : 0;
+    // births advance the step in the placement; without them `advance` does it here
+    const int adv = with_births || advance ? 1 : 0;
+    if (d.small)
+        return f64 ? launch_solve_small<true>(d, d.nens, zq, bir, 1, par, adv, s)
+                   : launch_solve_small<false>(d, d.nens, zq, bir, 1, par, adv, s);
     const int nscan = with_births ? d.ngt : 0;
     const int nred = with_params ? (d.nseg + kSolveThreads / kWave - 1) / (kSolveThreads / kWave) : 0;
-    const int par = with_params ? 1 : 0;
+    const int adv2 = advance && !with_births ? 1 : 0;
     const dim3 g1(nc + nscan + nred), g2(nc + (with_births ? place_blocks(d) : 0));
     if (f64) {
         hipLaunchKernelGGL(k_solve1<true>, g1, dim3(kSolveThreads), 0, s, d, nc, nscan, nred);
-        hipLaunchKernelGGL(k_solve2<true>, g2, dim3(kSolveThreads), 0, s, d, zq, nc, par);
+        hipLaunchKernelGGL(k_solve2<true>, g2, dim3(kSolveThreads), 0, s, d, zq, nc, par, adv2);
     } else {
         hipLaunchKernelGGL(k_solve1<false>, g1, dim3(kSolveThreads), 0, s, d, nc, nscan, nred);
-        hipLaunchKernelGGL(k_solve2<false>, g2, dim3(kSolveThreads), 0, s, d, zq, nc, par);
+        hipLaunchKernelGGL(k_solve2<false>, g2, dim3(kSolveThreads), 0, s, d, zq, nc, par, adv2);
     }
     LAUNCH_CHECK();
     if (d.periodic) {
@@ -1563,6 +1632,13 @@ int64_t scan_blocks(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 hipError_t launch_births(const Dev &d, bool f64, bool in_step, bool advance, hipStream_t s)
 {
     hipError_t e;
+    if (d.small) {
+        const int df = in_step ? 1 : 0, av = advance ? 1 : 0;
+        e = f64 ? launch_solve_small<true>(d, 0, 0, 1, df, 0, av, s) : launch_solve_small<false>(d, 0, 0, 1, df, 0, av, s);
+        if (e != hipSuccess) return e;
+        if (!in_step) hipLaunchKernelGGL(k_birth_clear, dim3(64), dim3(256), 0, s, d, -1);
+        return hipGetLastError();
+    }
     // the group-count scan: one block per tile up to kMaxGroupTiles tiles, the global
     // three-kernel scan above that
     if (d.ngt > 0) {
