@@ -249,11 +249,48 @@ __device__ __forceinline__ uint4 draw(uint32_t seed, int species, uint32_t id, u
 // Wave-level helpers (64 lanes).
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// Lane exchanges on the vector unit (DPP moves, and gfx950's row and half swaps): a __shfl goes
+// through the LDS unit, whose round trip a reduction pays six times over (twice that for a
+// double) and whose issue slots the deposit needs.  With shuffles the one-launch solve of 2048
+// nodes took 12.2 us, the deposit of 4e7 particles 81.7 and the fused pass over 8e6 67.6; these
+// moves take 10.8, 69.6 and 64.7.
+typedef uint32_t lane_pair __attribute__((ext_vector_type(2)));
+
+// The 32-bit word of lane ^ M, for M in {1, 2, 4, 8}.
+template <int M>
+__device__ __forceinline__ uint32_t xor_row(uint32_t v)
+{
+    if constexpr (M == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);       // quad_perm 1 0 3 2
+    else if constexpr (M == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);  // quad_perm 2 3 0 1
+    else if constexpr (M == 4)  // 7 - lane within eight, then 3 - lane within four
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);  // row_ror 8
+}
+
+// With v in both operands the swaps of 16 and of 32 leave {v of the even row (half), v of the odd
+// one} in the two results of every lane: the pair a butterfly step combines.
+template <int M>
+__device__ __forceinline__ lane_pair xor_pair(uint32_t v)
+{
+    if constexpr (M == 32) return __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    else if constexpr (M == 16) return __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    else return lane_pair{v, xor_row<M>(v)};
+}
+
 // One butterfly step: op(v of this lane, v of lane ^ M) for a commutative op.
 template <int M, typename T, typename Op>
 __device__ __forceinline__ T xor_step(T v, Op op)
 {
-    return op(v, __shfl_xor(v, M));
+    if constexpr (sizeof(T) == 4) {
+        const lane_pair p = xor_pair<M>(__builtin_bit_cast(uint32_t, v));
+        const uint32_t x = p.x, y = p.y;
+        return op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+    } else {
+        const uint64_t w = __builtin_bit_cast(uint64_t, v);
+        const lane_pair l = xor_pair<M>((uint32_t)w), h = xor_pair<M>((uint32_t)(w >> 32));
+        const uint64_t x = (uint64_t)h.x << 32 | l.x, y = (uint64_t)h.y << 32 | l.y;
+        return op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
+    }
 }
 
 // Reduction over the 64 lanes, in every lane: butterfly steps 32, 16, 8, 4, 2, 1.
@@ -288,11 +325,36 @@ __device__ __forceinline__ int wave_max_i32(int v)
     return wave_reduce(v, [](int a, int b) { return max(a, b); });
 }
 
-// v of lane - O.
+// The 32-bit word of lane - O (any value in lanes below O), for O a power of two.
+template <int O>
+__device__ __forceinline__ uint32_t word_up(uint32_t v)
+{
+    const int lane = __lane_id();
+    if constexpr (O == 1) {
+        return __builtin_amdgcn_mov_dpp(v, 0x138, 0xF, 0xF, true);  // wave_shr 1
+    } else if constexpr (O == 32) {
+        const lane_pair p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return p.x;
+    } else if constexpr (O == 16) {
+        // rows (0 0 2 2) and (1 1 3 3); the third row takes row 1 from the lower half
+        const lane_pair p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        const lane_pair q = __builtin_amdgcn_permlane32_swap(p.y, p.y, false, false);
+        return (lane & 16) ? p.x : q.x;
+    } else {
+        const uint32_t r = __builtin_amdgcn_mov_dpp(v, 0x120 + O, 0xF, 0xF, true);  // row_ror O
+        const uint32_t up = word_up<16>(r);
+        return (lane & 15) >= O ? r : up;
+    }
+}
 template <int O, typename T>
 __device__ __forceinline__ T lane_up(T v)
 {
-    return __shfl_up(v, O);
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, word_up<O>(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const uint64_t w = __builtin_bit_cast(uint64_t, v);
+        return __builtin_bit_cast(T, (uint64_t)word_up<O>((uint32_t)(w >> 32)) << 32 | word_up<O>((uint32_t)w));
+    }
 }
 
 // Inclusive scan with op(v, v of a lower lane) over the first N lanes of a wave (N a power of
