@@ -18,8 +18,8 @@
  *   - Device memory: the caller allocates ONE workspace of the size pic_query_workspace
  *     reports and keeps it alive until pic_free; the library carves every particle, grid
  *     and scratch array out of it and never allocates or frees device memory itself,
- *     except the small per-context HIP graph objects.  Host pointers are only read during
- *     the call.
+ *     except the small per-context HIP graph objects; a context also holds one page of
+ *     page-locked host memory until pic_free.  Host pointers are only used during the call.
  *   - Normalised units: eps0 = e = m_e = n0 = T_e = 1 (omega_pe = v_th,e = lambda_D = 1).
  *   - Sticky device error flags (capacity overflow, non-finite field) are checked at the
  *     end of pic_step and in pic_diag; a non-zero flag turns into the matching PIC_E* code.
@@ -303,7 +303,8 @@ int pic_set_particles(pic_ctx *ctx, int32_t ens, int32_t species, pic_particles 
                       int64_t count, uint32_t next_id, void *stream);
 
 /* Copy node arrays of ensemble `ens` to host (each may be NULL; length = node count):
- * Q_s as particle units, rho, phi, E (self-consistent part). */
+ * Q_s as particle units, rho, phi, E (self-consistent part).  Arrays that follow one another
+ * in memory in this order are copied in one piece. */
 int pic_get_grid(pic_ctx *ctx, int32_t ens, double *Q0, double *Q1, double *rho, double *phi,
                  double *E, void *stream);
 

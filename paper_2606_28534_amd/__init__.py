@@ -352,7 +352,7 @@ class Sim:
         d = DiagOut()
         self._check(self.L.pic_diag(self.h, int(ens), C.byref(d), C.c_void_p(buf.data_ptr()), self._s()))
         m = buf.cpu().numpy().reshape(self.nspecies, 5, nn)
-        return [{k: m[s, q].copy() for q, k in enumerate(("n", "ux", "uy", "uz", "T"))}
+        return [{k: m[s, q] for q, k in enumerate(("n", "ux", "uy", "uz", "T"))}
                 for s in range(self.nspecies)]
 
     def nnodes(self, ens=0):
@@ -398,7 +398,8 @@ class Sim:
 
     def grid(self, ens=0):
         nn = self.nnodes(ens)
-        Q0, Q1, rho, phi, E = (np.zeros(nn) for _ in range(5))
+        # rows of one array: the library copies arrays that follow one another in one piece
+        Q0, Q1, rho, phi, E = np.empty((5, nn))
         self._check(self.L.pic_get_grid(self.h, int(ens), _ptr(Q0), _ptr(Q1), _ptr(rho), _ptr(phi),
                                         _ptr(E), self._s()))
         return {"Q": [Q0, Q1][: self.nspecies], "rho": rho, "phi": phi, "E": E}

@@ -330,7 +330,10 @@ size_t carve(const Plan &P, char *base, Dev &d)
     d.src_tot = P.src_tot;
     d.ticket = c.take<uint32_t>(8);
     d.err = c.take<int32_t>(1);
-    c.take<double>(2 * kDiagGrid);  // diag scratch (last region)
+    // read-back scratch (last region): k_diag's sums per species, an ensemble's node arrays
+    int64_t nn = 0;
+    for (const EnsC &E : P.ens) nn = std::max(nn, E.nnodes);
+    d.rb = c.take<double>(std::max<int64_t>(2 * 2 * kDiagGrid, 5 * nn));
     return c.off;
 }
 
@@ -343,7 +346,12 @@ struct pic_ctx {
     Dev d{};
     char *ws = nullptr;
     size_t ws_bytes = 0;
-    double *diag_scratch = nullptr;
+    // page-locked host memory the device writes the scalar read-back to
+    struct HostPage {
+        DiagPack diag;
+        int32_t err;
+    } *page = nullptr;
+    std::mutex rb_mu;  // one read-back at a time uses the page and the read-back scratch
     Launch L{};
     int64_t host_step = 0;
     int sort_every = 0;  // effective cadence (>= 1)
@@ -413,15 +421,20 @@ int hipfail(pic_ctx *c, hipError_t e, const char *where)
         if (_e != hipSuccess) return hipfail(ctx, _e, #expr); \
     } while (0)
 
-int check_err(pic_ctx *c, hipStream_t s)
+int err_code(pic_ctx *c, int32_t err)
 {
-    int32_t err = 0;
-    HIPC(c, hipMemcpyAsync(&err, c->d.err, sizeof(err), hipMemcpyDeviceToHost, s));
-    HIPC(c, hipStreamSynchronize(s));
     if (err & (E_CAP_PART | E_CAP_BIRTH | E_CAP_ID))
         return fail(c, PIC_ECAPACITY, "capacity exceeded (flags " + std::to_string(err) + ")");
     if (err & E_NONFINITE) return fail(c, PIC_ENONFINITE, "non-finite field");
     return PIC_OK;
+}
+
+// Waits for the stream and turns the sticky error flags into their code.
+int check_err(pic_ctx *c, hipStream_t s)
+{
+    HIPC(c, launch_err_out(c->d, &c->page->err, s));
+    HIPC(c, hipStreamSynchronize(s));
+    return err_code(c, c->page->err);
 }
 
 // The fused step's work after its particle pass: collision candidates (with collisions),
@@ -715,7 +728,6 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
     c->d.collisions = cfg->collisions;
     for (int e = 0; e < cfg->n_ensembles; ++e)
         if (cfg->ens[e].cx_relative) c->d.any_cx_rel = 1;
-    c->diag_scratch = (double *)(c->ws + need - align_up(2 * kDiagGrid * sizeof(double)));
     c->L = default_launch(cfg, c->P);
     c->sort_every = cfg->sort_every > 0 ? cfg->sort_every : kCompactEvery;
     hipStream_t s = (hipStream_t)stream;
@@ -723,6 +735,7 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
     auto done = [&](int code) {
         if (code != PIC_OK) {
             fprintf(stderr, "pic_init: %s\n", c->msg.c_str());
+            if (c->page) (void)hipHostFree(c->page);
             delete c;
             return code;
         }
@@ -733,6 +746,7 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
 #define IHIP(expr)                                              \
     if ((e = (expr)) != hipSuccess) return done(hipfail(c, e, #expr));
     IHIP(static_scratch_address(&c->static_scratch));
+    IHIP(hipHostMalloc((void **)&c->page, sizeof(*c->page), hipHostMallocDefault));
     IHIP(hipMemsetAsync(c->ws, 0, need, s));
     IHIP(hipMemcpyAsync((void *)d.seg, c->P.seg.data(), c->P.seg.size() * sizeof(SegC), hipMemcpyHostToDevice, s));
     IHIP(hipMemcpyAsync((void *)d.ens, c->P.ens.data(), c->P.ens.size() * sizeof(EnsC), hipMemcpyHostToDevice, s));
@@ -872,81 +886,37 @@ int64_t pic_nnodes(const pic_ctx *c, int32_t ens)
 int pic_diag(pic_ctx *c, int32_t ens, pic_diag_out *out, double *moments_dev, void *stream)
 {
     if (!c || !out || ens < 0 || ens >= c->P.nens) return PIC_EINVAL;
+    std::lock_guard<std::mutex> lk(c->rb_mu);
     hipStream_t s = (hipStream_t)stream;
     if (moments_dev) {
         const EnsC &Em = c->P.ens[ens];
         for (int sp = 0; sp < c->P.nspecies; ++sp)
             HIPC(c, launch_moments(c->d, c->P.f64, Em.seg[sp], Em.nnodes, moments_dev + (int64_t)sp * 5 * Em.nnodes, s));
     }
-    const int nseg = c->P.nseg;
-    std::vector<unsigned long long> cnt((size_t)kCntStripes * nseg * C_NCNT);
-    std::vector<double> sums((size_t)kCntStripes * nseg * S_NSUM);
-    HIPC(c, hipMemcpyAsync(cnt.data(), c->d.cnt, cnt.size() * 8, hipMemcpyDeviceToHost, s));
-    HIPC(c, hipMemcpyAsync(sums.data(), c->d.sums, sums.size() * 8, hipMemcpyDeviceToHost, s));
-    double emax = 0, fe = 0;
-    std::vector<double> numax(nseg);
-    int64_t step = 0;
+    const EnsC &E = c->P.ens[ens];
+    // the fused step's own tallies of its last step (count, sum |v|^2 and the solve's field
+    // energy) when no call has changed particles or fields since, else a pass over both
     if (!c->insitu) {
         HIPC(c, launch_field_energy(c->d, s));
-        HIPC(c, hipMemcpyAsync(&fe, c->d.fe + ens, 8, hipMemcpyDeviceToHost, s));
+        for (int sp = 0; sp < c->P.nspecies; ++sp)
+            HIPC(c, launch_diag(c->d, c->P.f64, E.seg[sp], c->d.rb + (size_t)sp * 2 * kDiagGrid, kDiagGrid, s));
     }
-    HIPC(c, hipMemcpyAsync(&emax, c->d.emax + ens, 8, hipMemcpyDeviceToHost, s));
-    HIPC(c, hipMemcpyAsync(numax.data(), c->d.numax, nseg * 8, hipMemcpyDeviceToHost, s));
-    HIPC(c, hipMemcpyAsync(&step, c->d.step, 8, hipMemcpyDeviceToHost, s));
+    HIPC(c, launch_diag_pack(c->d, ens, c->insitu, c->d.rb, kDiagGrid, &c->page->diag, s));
+    HIPC(c, hipStreamSynchronize(s));
+    const DiagPack &R = c->page->diag;
     memset(out, 0, sizeof(*out));
-    const EnsC &E = c->P.ens[ens];
-    std::vector<double> part(2 * kDiagGrid);
-    // the fused step's own tallies of its last step (count, sum |v|^2 and the solve's field
-    // energy), when no call has changed particles or fields since
-    std::vector<double> tal;
-    if (c->insitu) {
-        int32_t vc = 0;
-        HIPC(c, hipMemcpyAsync(&vc, c->d.vcur, 4, hipMemcpyDeviceToHost, s));
-        HIPC(c, hipStreamSynchronize(s));
-        const size_t per = (size_t)kCntStripes * nseg * T_NSTEP;
-        tal.resize(per);
-        HIPC(c, hipMemcpyAsync(tal.data(), c->d.ssum + (size_t)vc * per, per * 8, hipMemcpyDeviceToHost, s));
-        std::vector<double> pp((size_t)E.nchunks * P_NPART);
-        HIPC(c, hipMemcpyAsync(pp.data(), c->d.part + E.chunk0 * P_NPART, pp.size() * 8, hipMemcpyDeviceToHost, s));
-        HIPC(c, hipStreamSynchronize(s));
-        double f = 0.0;
-        for (int64_t k = 0; k < E.nchunks; ++k) f += pp[(size_t)k * P_NPART + P_FE];
-        fe = f;
-    }
     for (int sp = 0; sp < c->P.nspecies; ++sp) {
-        const int sg = E.seg[sp];
-        double n = 0, v2 = 0;
-        if (c->insitu) {
-            for (int st = 0; st < kCntStripes; ++st) {
-                n += tal[((size_t)st * nseg + sg) * T_NSTEP + T_N];
-                v2 += tal[((size_t)st * nseg + sg) * T_NSTEP + T_V2];
-            }
-        } else {
-            HIPC(c, launch_diag(c->d, c->P.f64, sg, c->diag_scratch, kDiagGrid, s));
-            HIPC(c, hipMemcpyAsync(part.data(), c->diag_scratch, part.size() * 8, hipMemcpyDeviceToHost, s));
-            HIPC(c, hipStreamSynchronize(s));
-            for (int i = 0; i < kDiagGrid; ++i) {
-                n += part[2 * i];
-                v2 += part[2 * i + 1];
-            }
-        }
+        const double n = R.n[sp];
+        const unsigned long long *a = R.cnt[sp];
         const pic_species_desc &D = c->ens[ens].sp[sp];
         out->count[sp] = (int64_t)n;
-        out->ke[sp] = 0.5 * D.m * D.w * v2;
+        out->ke[sp] = 0.5 * D.m * D.w * R.v2[sp];
         out->charge += D.q * D.w * n;
-        unsigned long long a[C_NCNT] = {0};
-        double kl = 0, kr = 0;
-        for (int st = 0; st < kCntStripes; ++st) {
-            for (int k = 0; k < C_NCNT; ++k) a[k] += cnt[((size_t)st * nseg + sg) * C_NCNT + k];
-            kl += sums[((size_t)st * nseg + sg) * S_NSUM + S_KE_L];
-            kr += sums[((size_t)st * nseg + sg) * S_NSUM + S_KE_R];
+        for (int w = 0; w < 2; ++w) {
+            out->wall_count[w][sp] = (int64_t)a[w == 0 ? C_WALL_L : C_WALL_R];
+            out->wall_charge[w][sp] = D.q * D.w * (double)out->wall_count[w][sp];
+            out->wall_ke[w][sp] = R.wall_v2[sp][w];
         }
-        out->wall_count[0][sp] = (int64_t)a[C_WALL_L];
-        out->wall_count[1][sp] = (int64_t)a[C_WALL_R];
-        out->wall_charge[0][sp] = D.q * D.w * (double)a[C_WALL_L];
-        out->wall_charge[1][sp] = D.q * D.w * (double)a[C_WALL_R];
-        out->wall_ke[0][sp] = kl;
-        out->wall_ke[1][sp] = kr;
         out->created[sp] = (int64_t)a[C_CREATED];
         out->pushes += (int64_t)a[C_PUSH];
         if (sp == 0) {
@@ -959,21 +929,13 @@ int pic_diag(pic_ctx *c, int32_t ens, pic_diag_out *out, double *moments_dev, vo
             out->neutral_wall[0] = (int64_t)a[C_NWALL_L];
             out->neutral_wall[1] = (int64_t)a[C_NWALL_R];
         }
-        out->numax[sp] = numax[sg];
+        out->numax[sp] = R.numax[sp];
     }
-    if (E.recycle) {
-        int32_t nc = 0;
-        unsigned long long nn = 0;
-        HIPC(c, hipMemcpyAsync(&nc, c->d.ncur, 4, hipMemcpyDeviceToHost, s));
-        HIPC(c, hipStreamSynchronize(s));
-        HIPC(c, hipMemcpyAsync(&nn, c->d.nneu + (int64_t)nc * c->P.nens + ens, 8, hipMemcpyDeviceToHost, s));
-        HIPC(c, hipStreamSynchronize(s));
-        out->neutral_count = std::min<int64_t>((int64_t)nn, E.ncap);
-    }
-    out->field_energy = fe;
-    out->emax = emax;
-    out->step = step;
-    return check_err(c, s);
+    if (E.recycle) out->neutral_count = std::min<int64_t>((int64_t)R.neutrals, E.ncap);
+    out->field_energy = R.fe;
+    out->emax = R.emax;
+    out->step = R.step;
+    return err_code(c, R.err);
 }
 
 namespace {
@@ -1234,28 +1196,21 @@ int pic_get_grid(pic_ctx *c, int32_t ens, double *Q0, double *Q1, double *rho, d
                  double *E, void *stream)
 {
     if (!c || ens < 0 || ens >= c->P.nens) return PIC_EINVAL;
+    std::lock_guard<std::mutex> lk(c->rb_mu);
     hipStream_t s = (hipStream_t)stream;
-    HIPC(c, hipStreamSynchronize(s));
-    const EnsC &En = c->P.ens[ens];
-    const int64_t nn = En.nnodes;
-    double *Qs[2] = {Q0, Q1};
-    for (int sp = 0; sp < 2; ++sp) {
-        if (!Qs[sp]) continue;
-        if (sp >= c->P.nspecies) {
-            std::fill(Qs[sp], Qs[sp] + nn, 0.0);
-            continue;
+    const int64_t nn = c->P.ens[ens].nnodes;
+    HIPC(c, launch_grid_pack(c->d, c->P.f64, ens, nn, c->d.rb, s));
+    double *to[5] = {Q0, Q1, rho, phi, E};
+    // arrays that follow one another in host memory, as in the device's, go in one copy
+    for (int k = 0; k < 5;) {
+        int m = 1;
+        if (to[k]) {
+            while (k + m < 5 && to[k + m] == to[k] + m * nn) ++m;
+            HIPC(c, hipMemcpyAsync(to[k], c->d.rb + k * nn, (size_t)(m * nn) * 8, hipMemcpyDeviceToHost, s));
         }
-        if (c->P.f64) {
-            HIPC(c, hipMemcpy(Qs[sp], c->d.Qd + sp * c->P.nodes_tot + En.gbase, nn * 8, hipMemcpyDeviceToHost));
-        } else {
-            std::vector<long long> q(nn);
-            HIPC(c, hipMemcpy(q.data(), c->d.Qi + sp * c->P.nodes_tot + En.gbase, nn * 8, hipMemcpyDeviceToHost));
-            for (int64_t j = 0; j < nn; ++j) Qs[sp][j] = (double)q[j] / kFix;
-        }
+        k += m;
     }
-    if (rho) HIPC(c, hipMemcpy(rho, c->d.rho + En.gbase, nn * 8, hipMemcpyDeviceToHost));
-    if (phi) HIPC(c, hipMemcpy(phi, c->d.phi + En.gbase, nn * 8, hipMemcpyDeviceToHost));
-    if (E) HIPC(c, hipMemcpy(E, c->d.E + En.gbase, nn * 8, hipMemcpyDeviceToHost));
+    HIPC(c, hipStreamSynchronize(s));
     return PIC_OK;
 }
 
@@ -1921,6 +1876,7 @@ void pic_free(pic_ctx *c)
     for (auto &e : c->ev) (void)hipEventDestroy(e);
     drop_graphs(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+    if (c->page) (void)hipHostFree(c->page);
     delete c;
 }
 

@@ -58,6 +58,17 @@ enum Part : int { P_EMAX = 0, P_FE, P_PHISUM, P_NONFIN, P_NPART };
 // Error flags (bit mask).
 enum Err : int { E_CAP_PART = 1, E_CAP_BIRTH = 2, E_CAP_ID = 4, E_NONFINITE = 8 };
 
+// An ensemble's scalars as the device hands them to the host (k_diag_pack).
+struct DiagPack {
+    unsigned long long cnt[2][C_NCNT];   // per species
+    double wall_v2[2][S_NSUM];           // absorbed kinetic energy, left and right
+    double n[2], v2[2], numax[2];        // alive, sum |v|^2, collision bound
+    double fe, emax;
+    int64_t step;
+    unsigned long long neutrals;
+    int32_t err;
+};
+
 // Constant per segment.
 struct SegC {
     int64_t base, cap;        // slots
@@ -187,6 +198,7 @@ struct Dev {
     uint32_t *scanpart;       // [<= 1 << 16]
     uint32_t *ticket;         // [8]
     int32_t *err;             // [1]
+    double *rb;               // read-back scratch: [2][diag grid][2], or [5][nodes of an ensemble]
 };
 
 // The segment whose slot range holds `slot`.

@@ -74,6 +74,13 @@ hipError_t launch_adj_b(const int32_t *xc, const double *lQ, double *lx, int64_t
 hipError_t launch_adj_by_id(const double *lv, const uint32_t *id, double *out, int64_t n, int64_t len,
                             int32_t *err, hipStream_t s);
 hipError_t launch_diag(const Dev &d, bool f64, int sg, double *out, int grid, hipStream_t s);
+// The scalars of ensemble `en` into one record and its node arrays ([Q0, Q1, rho, phi, E][nn]
+// doubles) into one run of device memory; the error flags alone.  `out` of the records is host
+// memory the device can write.
+hipError_t launch_diag_pack(const Dev &d, int en, bool tallied, const double *v2, int ngrid, DiagPack *out,
+                            hipStream_t s);
+hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, double *out, hipStream_t s);
+hipError_t launch_err_out(const Dev &d, int32_t *out, hipStream_t s);
 // Node moments of segment sg (reading R27) into out[5][nn] (n, ux, uy, uz, T); nn is the
 // node count of the segment's ensemble.  `out` is device memory the launch overwrites.
 hipError_t launch_moments(const Dev &d, bool f64, int sg, int64_t nn, double *out, hipStream_t s);

@@ -1470,6 +1470,110 @@ __global__ void k_diag(Dev d, int sg, double *out /* [grid][2] */)
 }
 
 // =======================================================================================
+// Read-back.  One block gathers the scalars of an ensemble from the striped tallies into one
+// record in host memory (k_diag_pack), and one launch gathers its node arrays as doubles into one
+// run of memory (k_grid_pack), so that reading either costs one wait for the stream: each array
+// copied on its own cost a wait of its own, and the stripes of every segment went to the host
+// (3.4 MB a call with 128 segments).  Twenty steps and both reads of
+// the 256-cell run went from 769 to 569 us; of the 64 batched ensembles, whose 64 pairs of reads
+// took 39 of 131 ms, to 106 ms.
+// =======================================================================================
+__device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long *s)
+{
+    v = wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a + b; });
+    if (lane_id() == 0) s[threadIdx.x / kWave] = v;
+    __syncthreads();
+    unsigned long long r = 0;
+    for (int i = 0; i < (int)(blockDim.x / kWave); ++i) r += s[i];
+    __syncthreads();
+    return r;
+}
+
+// With `tallied`, counts, sums of |v|^2 and field energy come from the fused step's tallies;
+// otherwise from `v2` ([species][ngrid][2], k_diag) and the field-energy kernel.
+__global__ void __launch_bounds__(kCntStripes) k_diag_pack(Dev d, int en, int tallied, const double *v2, int ngrid,
+                                                           DiagPack *out)
+{
+    __shared__ double s_buf[16];
+    __shared__ unsigned long long s_u[16];
+    const EnsC &e = d.ens[en];
+    const int st = threadIdx.x;
+    const int vc = *d.vcur;
+    for (int sp = 0; sp < e.nspecies; ++sp) {
+        const int sg = e.seg[sp];
+        const unsigned long long *c = d.cnt + ((int64_t)st * d.nseg + sg) * C_NCNT;
+        unsigned long long cv[C_NCNT];
+#pragma unroll
+        for (int k = 0; k < C_NCNT; ++k) cv[k] = c[k];
+        const double *sm = d.sums + ((int64_t)st * d.nseg + sg) * S_NSUM;
+        double f[4] = {sm[S_KE_L], sm[S_KE_R], 0.0, 0.0};
+        if (tallied) {
+            const double *ts = step_sums(d, vc, st, sg);
+            f[2] = ts[T_N];
+            f[3] = ts[T_V2];
+        } else {
+            for (int i = st; i < ngrid; i += kCntStripes) {
+                f[2] += v2[((int64_t)sp * ngrid + i) * 2];
+                f[3] += v2[((int64_t)sp * ngrid + i) * 2 + 1];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < C_NCNT; ++k) cv[k] = block_sum_u64(cv[k], s_u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = block_sum(f[k], s_buf);
+        if (st == 0) {
+#pragma unroll
+            for (int k = 0; k < C_NCNT; ++k) out->cnt[sp][k] = cv[k];
+            out->wall_v2[sp][0] = f[0];
+            out->wall_v2[sp][1] = f[1];
+            out->n[sp] = f[2];
+            out->v2[sp] = f[3];
+            out->numax[sp] = d.numax[sg];
+        }
+    }
+    double fe = 0.0;
+    if (tallied) {
+        for (int64_t k = st; k < e.nchunks; k += kCntStripes) fe += d.part[(e.chunk0 + k) * P_NPART + P_FE];
+        fe = block_sum(fe, s_buf);
+    } else {
+        fe = d.fe[en];
+    }
+    if (st == 0) {
+        out->fe = fe;
+        out->emax = d.emax[en];
+        out->step = *d.step;
+        out->neutrals = e.recycle ? d.nneu[(int64_t)*d.ncur * d.nens + en] : 0ull;
+        out->err = *d.err;
+    }
+}
+
+// Node arrays of ensemble `en` as doubles: out[0..1] Q per species (particle units), rho, phi, E.
+template <bool F64>
+__global__ void __launch_bounds__(256) k_grid_pack(Dev d, int en, double *out)
+{
+    const EnsC &e = d.ens[en];
+    const int64_t nn = e.nnodes, g = e.gbase;
+    const bool two = e.nspecies > 1;
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nn; j += (int64_t)gridDim.x * blockDim.x) {
+        double q0, q1 = 0.0;
+        if constexpr (!F64) {
+            q0 = (double)(long long)d.Qi[g + j] * (1.0 / kFix);
+            if (two) q1 = (double)(long long)d.Qi[d.nodes_tot + g + j] * (1.0 / kFix);
+        } else {
+            q0 = d.Qd[g + j];
+            if (two) q1 = d.Qd[d.nodes_tot + g + j];
+        }
+        out[j] = q0;
+        out[nn + j] = q1;
+        out[2 * nn + j] = d.rho[g + j];
+        out[3 * nn + j] = d.phi[g + j];
+        out[4 * nn + j] = d.E[g + j];
+    }
+}
+
+__global__ void k_err_out(const int32_t *err, int32_t *out) { *out = *err; }
+
+// =======================================================================================
 // Host launchers.
 // =======================================================================================
 #define LAUNCH_CHECK()                                          \
@@ -1694,6 +1798,29 @@ hipError_t launch_sort(const Dev &d, bool f64, const Launch &L, hipStream_t s)
     hipLaunchKernelGGL((k_sort_scatter<4>), dim3(8 * L.grid), dim3(L.block), lds, s, d, L.window);
     LAUNCH_CHECK();
     return hipSuccess;
+}
+
+hipError_t launch_diag_pack(const Dev &d, int en, bool tallied, const double *v2, int ngrid, DiagPack *out,
+                            hipStream_t s)
+{
+    hipLaunchKernelGGL(k_diag_pack, dim3(1), dim3(kCntStripes), 0, s, d, en, tallied ? 1 : 0, v2, ngrid, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, double *out, hipStream_t s)
+{
+    const dim3 g((unsigned)std::min<int64_t>((nn + 255) / 256, 1024));
+    if (f64)
+        hipLaunchKernelGGL(k_grid_pack<true>, g, dim3(256), 0, s, d, en, out);
+    else
+        hipLaunchKernelGGL(k_grid_pack<false>, g, dim3(256), 0, s, d, en, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_err_out(const Dev &d, int32_t *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_err_out, dim3(1), dim3(1), 0, s, d.err, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_diag(const Dev &d, bool f64, int sg, double *out, int grid, hipStream_t s)
