@@ -1253,6 +1253,7 @@ struct AdjLayout {
     int64_t n, nn, nseg_ck, K;
     size_t off_ck_cell, off_ck_off, off_ck_vx, off_xc, off_xo, off_E, off_lx, off_lv, off_lE, off_lQ,
         off_tmp, off_ext, off_fin, bytes;
+    size_t off_ckQ, off_Q, off_v;  // small grids: charge per checkpoint, three charges, one v_x
 };
 
 // PIC_OK when the run is one the adjoint is defined for; otherwise *why says what is not.
@@ -1292,10 +1293,18 @@ AdjLayout adj_layout(pic_ctx *c, int nsteps, int K)
     A.off_E = take((size_t)K * A.nn * 8);
     A.off_lx = take((size_t)A.n * 8);
     A.off_lv = take((size_t)A.n * 8);
+    A.off_ext = take(64);
+    if (c->d.small) {
+        A.off_lE = take((size_t)3 * A.nn * 8);
+        A.off_ckQ = take((size_t)A.nseg_ck * A.nn * 8);
+        A.off_Q = take((size_t)3 * A.nn * 8);
+        A.off_v = take((size_t)A.n * 4);
+        A.bytes = o;
+        return A;
+    }
     A.off_lE = take((size_t)A.nn * 8);
     A.off_lQ = take((size_t)A.nn * 8);
     A.off_tmp = take((size_t)A.nn * 8);
-    A.off_ext = take(64);
     A.off_fin = take((size_t)A.n * 4 * 5);  // final state: cell, off, vx, vy, vz
     A.bytes = o;
     return A;
@@ -1329,21 +1338,11 @@ int pic_adjoint_query(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, size_t *by
 }
 
 namespace {
-// The adjoint window on scratch `base` (>= the layout's bytes).  With `gid` (device memory
-// of dvx_len doubles) the gradient is scattered by id on the device into gid, which first
-// receives the caller's dW_dvx so that entries of ids absent from the run stay as they
-// were, and is copied back whole; without it the host scatters (host staging vectors).
-int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *base, size_t bytes,
-                        double *W, double *dW_dvx, int64_t dvx_len, double *dW_dEext, double *gid,
-                        void *stream)
+// The forward window with its checkpoints and the reverse sweep: lv (by slot) and lext hold the
+// gradients, *fe the objective, and the run is in the window's final state.
+int adj_sweep(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int ckpt_every, int32_t b, int64_t nslots,
+              int64_t step0, double *fe, hipStream_t s)
 {
-    c->sort_ready = false;  // particles or the step count change: no prepared sort
-    c->insitu = false;
-    const char *why = "";
-    if (adj_check(c, &why)) return fail(c, PIC_EINVAL, why);
-    const AdjLayout A = adj_layout(c, nsteps, ckpt_every);
-    if (bytes < A.bytes) return fail(c, PIC_EINVAL, "adjoint scratch too small");
-    hipStream_t s = (hipStream_t)stream;
     Dev &d = c->d;
     int32_t *ck_cell = (int32_t *)(base + A.off_ck_cell);
     float *ck_off = (float *)(base + A.off_ck_off);
@@ -1364,11 +1363,6 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
     const EnsC &En = c->P.ens[0];
     const double qm = S.h * 2.0 / En.dt;  // q/m
     // the particle buffer must be buffer 0 and hold no absorbed slots (periodic, no sort here)
-    int32_t b = 0;
-    int64_t nslots = 0;
-    HIPC(c, hipMemcpyAsync(&b, d.cur, 4, hipMemcpyDeviceToHost, s));
-    HIPC(c, hipMemcpyAsync(&nslots, d.n_slots, 8, hipMemcpyDeviceToHost, s));
-    HIPC(c, hipStreamSynchronize(s));
     if (b != 0) {
         // move the live buffer to buffer 0 so the recorded pointers stay valid
         for (int k = 0; k < 5; ++k) {
@@ -1381,9 +1375,6 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
         HIPC(c, hipMemcpyAsync(d.cur, &zero, 4, hipMemcpyHostToDevice, s));
         HIPC(c, hipStreamSynchronize(s));
     }
-    if (dvx_len < nslots) return fail(c, PIC_EINVAL, "dW_dvx too short");
-    int64_t step0 = 0;
-    HIPC(c, hipMemcpy(&step0, d.step, 8, hipMemcpyDeviceToHost));
     // Q^0 from the current positions (they may have been injected)
     HIPC(c, launch_zero_q(d, false, s));
     HIPC(c, launch_particles(d, c->L, s, false, SB_DEPOSIT, 0));
@@ -1400,8 +1391,7 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
     // objective at the final positions
     HIPC(c, launch_solve(d, false, c->P.chunks_tot, false, s));
     HIPC(c, launch_field_energy(d, s));
-    double fe = 0.0;
-    HIPC(c, hipMemcpyAsync(&fe, d.fe, 8, hipMemcpyDeviceToHost, s));
+    HIPC(c, hipMemcpyAsync(fe, d.fe, 8, hipMemcpyDeviceToHost, s));
     // keep the final state
     HIPC(c, hipMemcpyAsync(fin, d.cell[0], n * 4, hipMemcpyDeviceToDevice, s));
     HIPC(c, hipMemcpyAsync(fin + n * 4, d.off[0], n * 4, hipMemcpyDeviceToDevice, s));
@@ -1450,13 +1440,131 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
     c->host_step = stN;
     HIPC(c, launch_zero_q(d, false, s));
     HIPC(c, launch_particles(d, c->L, s, false, SB_DEPOSIT, 0));
+    return PIC_OK;
+}
+
+// The same on a small grid: one launch per step, in which every block solves the field for
+// itself.  The forward steps store their checkpoints (charge included), so a recomputed segment
+// starts from them without copies and never touches the run's own arrays, which keep the
+// final state.
+int adj_sweep_small(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int C, int32_t b, int64_t nslots,
+                    int64_t step0, double *fe, hipStream_t s)
+{
+    const Dev &d = c->d;
+    const int64_t n = A.n, nn = A.nn;
+    const SegC &S = c->P.seg[0];
+    const EnsC &En = c->P.ens[0];
+    const double qm = S.h * 2.0 / En.dt;  // q/m
+    typedef unsigned long long u64;
+    auto ck = [&](int64_t k) {
+        return AdjState{(int32_t *)(base + A.off_ck_cell) + k * n, (float *)(base + A.off_ck_off) + k * n,
+                        (float *)(base + A.off_ck_vx) + k * n};
+    };
+    auto ckQ = [&](int64_t k) { return (u64 *)(base + A.off_ckQ) + k * nn; };
+    // state i of the segment in hand (0 is its checkpoint); one v_x for all of them
+    auto at = [&](int64_t k, int i) {
+        if (i == 0) return ck(k);
+        return AdjState{(int32_t *)(base + A.off_xc) + i * n, (float *)(base + A.off_xo) + i * n, (float *)(base + A.off_v)};
+    };
+    u64 *Qs = (u64 *)(base + A.off_Q);
+    double *Eb = (double *)(base + A.off_E), *lE = (double *)(base + A.off_lE);
+    double *lx = (double *)(base + A.off_lx), *lv = (double *)(base + A.off_lv), *lext = (double *)(base + A.off_ext);
+    const AdjState run{d.cell[b], d.off[b], d.fvx[b]}, none{nullptr, nullptr, nullptr};
+    Dev dd = d;  // with the charge a step reads
+    // forward from Q^0 of the current positions (they may have been injected); the charges rotate
+    // through the run's own array and two more
+    HIPC(c, launch_zero_q(d, false, s));
+    HIPC(c, launch_particles(d, c->L, s, false, SB_DEPOSIT, 0));
+    HIPC(c, hipMemsetAsync(Qs, 0, (size_t)3 * nn * 8, s));
+    u64 *ring[3] = {d.Qi, Qs, Qs + nn};
+    for (int t = 0; t < nsteps; ++t) {
+        dd.Qi = ring[t % 3];
+        const bool keep = t % C == 0;
+        // (the recomputation pushes every particle once more, and its pushes count too)
+        HIPC(c, launch_adj_fwd(dd, run, run, keep ? ck(t / C) : none, keep ? ckQ(t / C) : nullptr, ring[(t + 1) % 3],
+                               ring[(t + 2) % 3], nullptr, nslots, 2, s));
+    }
+    u64 *last = ring[nsteps % 3];
+    if (last != d.Qi) HIPC(c, hipMemcpyAsync(d.Qi, last, nn * 8, hipMemcpyDeviceToDevice, s));
+    // objective at the final positions, and its derivative by the node field as the seed
+    HIPC(c, launch_solve(d, false, c->P.chunks_tot, false, s));
+    HIPC(c, launch_field_energy(d, s));
+    HIPC(c, hipMemsetAsync(lx, 0, n * 8, s));
+    HIPC(c, hipMemsetAsync(lv, 0, n * 8, s));
+    HIPC(c, hipMemsetAsync(lext, 0, 8, s));
+    HIPC(c, hipMemsetAsync(lE, 0, (size_t)3 * nn * 8, s));
+    HIPC(c, hipMemsetAsync(Qs, 0, (size_t)3 * nn * 8, s));
+    int m = 0, r = 0;  // charges and field adjoints written so far: the next of each ring is clear
+    const int32_t *above = run.cell;  // cells of the step above
+    for (int64_t k = A.nseg_ck - 1; k >= 0; --k) {
+        const int t0 = (int)(k * C), len = std::min(nsteps, t0 + C) - t0;
+        for (int i = 0; i < len; ++i) {
+            dd.Qi = i == 0 ? ckQ(k) : Qs + (int64_t)((m + 2) % 3) * nn;
+            if (i + 1 < len) {
+                HIPC(c, launch_adj_fwd(dd, at(k, i), at(k, i + 1), none, nullptr, Qs + (int64_t)(m % 3) * nn,
+                                       Qs + (int64_t)((m + 1) % 3) * nn, Eb + (int64_t)i * nn, nslots, 0, s));
+                ++m;
+            } else {
+                HIPC(c, launch_adj_fwd(dd, none, none, none, nullptr, nullptr, nullptr, Eb + (int64_t)i * nn, 0, 0, s));
+            }
+        }
+        for (int i = len - 1; i >= 0; --i) {
+            const AdjState x = at(k, i);
+            HIPC(c, launch_adj_rev(d.small, r == 0 ? d.E : lE + (int64_t)((r + 2) % 3) * nn, lE + (int64_t)(r % 3) * nn,
+                                   lE + (int64_t)((r + 1) % 3) * nn, r == 0, En.eps0, En.dx, S.qw, above, x.cell, x.off,
+                                   Eb + (int64_t)i * nn, lx, lv, lext, nslots, En.dt, qm, (int)En.ncells, s));
+            ++r;
+            above = x.cell;
+        }
+    }
+    HIPC(c, hipMemcpyAsync(fe, d.fe, 8, hipMemcpyDeviceToHost, s));
+    const int64_t stN = step0 + nsteps;
+    HIPC(c, hipMemcpyAsync(d.step, &stN, 8, hipMemcpyHostToDevice, s));
+    HIPC(c, hipStreamSynchronize(s));
+    c->host_step = stN;
+    return PIC_OK;
+}
+
+// The adjoint window on scratch `base` (>= the layout's bytes).  With `gid` (device memory
+// of dvx_len doubles) the gradient is scattered by id on the device into gid, which first
+// receives the caller's dW_dvx so that entries of ids absent from the run stay as they
+// were, and is copied back whole; without it the host scatters (host staging vectors).
+int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *base, size_t bytes,
+                        double *W, double *dW_dvx, int64_t dvx_len, double *dW_dEext, double *gid,
+                        void *stream)
+{
+    c->sort_ready = false;  // particles or the step count change: no prepared sort
+    c->insitu = false;
+    const char *why = "";
+    if (adj_check(c, &why)) return fail(c, PIC_EINVAL, why);
+    const AdjLayout A = adj_layout(c, nsteps, ckpt_every);
+    if (bytes < A.bytes) return fail(c, PIC_EINVAL, "adjoint scratch too small");
+    hipStream_t s = (hipStream_t)stream;
+    const Dev &d = c->d;
+    double *lv = (double *)(base + A.off_lv);
+    double *lext = (double *)(base + A.off_ext);
+    int32_t b = 0;
+    int64_t nslots = 0;
+    HIPC(c, hipMemcpyAsync(&b, d.cur, 4, hipMemcpyDeviceToHost, s));
+    HIPC(c, hipMemcpyAsync(&nslots, d.n_slots, 8, hipMemcpyDeviceToHost, s));
+    int64_t step0 = 0;
+    HIPC(c, hipMemcpyAsync(&step0, d.step, 8, hipMemcpyDeviceToHost, s));
+    HIPC(c, hipStreamSynchronize(s));
+    if (dvx_len < nslots) return fail(c, PIC_EINVAL, "dW_dvx too short");
+    double fe = 0.0;
+    {
+        const int rc = d.small ? adj_sweep_small(c, A, base, nsteps, ckpt_every, b, nslots, step0, &fe, s)
+                               : adj_sweep(c, A, base, nsteps, ckpt_every, b, nslots, step0, &fe, s);
+        if (rc) return rc;
+        if (!d.small) b = 0;
+    }
     // gradients by id
     double gext = 0.0;
     if (gid) {
         int32_t *bad = (int32_t *)lext + 2;  // a flag beside lext (its 64-byte slot)
         HIPC(c, hipMemsetAsync(bad, 0, 4, s));
         HIPC(c, hipMemcpyAsync(gid, dW_dvx, (size_t)dvx_len * 8, hipMemcpyHostToDevice, s));
-        HIPC(c, launch_adj_by_id(lv, d.id[0], gid, nslots, dvx_len, bad, s));
+        HIPC(c, launch_adj_by_id(lv, d.id[b], gid, nslots, dvx_len, bad, s));
         int32_t badh = 0;
         HIPC(c, hipMemcpyAsync(&badh, bad, 4, hipMemcpyDeviceToHost, s));
         HIPC(c, hipMemcpyAsync(&gext, lext, 8, hipMemcpyDeviceToHost, s));
@@ -1468,7 +1576,7 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
         std::vector<double> glv(nslots);
         std::vector<uint32_t> ids(nslots);
         HIPC(c, hipMemcpyAsync(glv.data(), lv, nslots * 8, hipMemcpyDeviceToHost, s));
-        HIPC(c, hipMemcpyAsync(ids.data(), d.id[0], nslots * 4, hipMemcpyDeviceToHost, s));
+        HIPC(c, hipMemcpyAsync(ids.data(), d.id[b], nslots * 4, hipMemcpyDeviceToHost, s));
         HIPC(c, hipMemcpyAsync(&gext, lext, 8, hipMemcpyDeviceToHost, s));
         HIPC(c, hipStreamSynchronize(s));
         for (int64_t i = 0; i < nslots; ++i) {

@@ -62,6 +62,17 @@ hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t
 hipError_t launch_after(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool coll);
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t nwords, bool nt, hipStream_t s);
 hipError_t launch_sort32_scatter(const Dev &d, int ppt, int W, hipStream_t s, int64_t cap_tot, bool nt);
+// The adjoint window on a small grid (Dev::small), one launch per step in either direction.
+struct AdjState {
+    int32_t *cell;
+    float *off, *vx;
+};
+hipError_t launch_adj_fwd(const Dev &d, const AdjState &in, const AdjState &out, const AdjState &ck,
+                          unsigned long long *ckQ, unsigned long long *Qout, unsigned long long *Qzero, double *Erec,
+                          int64_t n, int pushes, hipStream_t s);
+hipError_t launch_adj_rev(int small, const double *lEin, double *lEout, double *lEzero, bool seed, double eps0,
+                          double dx, double qw, const int32_t *xc1, const int32_t *xc, const float *xo, const double *E,
+                          double *lx, double *lv, double *lEext, int64_t n, double dt, double qm, int N, hipStream_t s);
 hipError_t launch_adj_seed(const double *E, double *lE, int N, double eps0, double dx, hipStream_t s);
 hipError_t launch_adj_a(const Dev &d, const int32_t *xc, const float *xo, const double *E, double *lx,
                         double *lv, double *lE, double *lEext, int64_t n, double dt, double qm,
