@@ -339,6 +339,15 @@ size_t carve(const Plan &P, char *base, Dev &d)
 
 }  // namespace
 
+// Page-locked host memory the device writes a context's scalar read-back to.  Locking a page
+// takes about 55 us, a third of what creating a small context takes, so contexts share one
+// block of kHostPages, locked for every GPU when the first of them is created and held until the
+// process ends; a context beyond them locks its own.
+struct HostPage {
+    alignas(256) DiagPack diag;
+    int32_t err;
+};
+
 struct pic_ctx {
     pic_config cfg{};
     std::vector<pic_ensemble_desc> ens;
@@ -346,11 +355,7 @@ struct pic_ctx {
     Dev d{};
     char *ws = nullptr;
     size_t ws_bytes = 0;
-    // page-locked host memory the device writes the scalar read-back to
-    struct HostPage {
-        DiagPack diag;
-        int32_t err;
-    } *page = nullptr;
+    HostPage *page = nullptr;  // the device writes the scalar read-back there
     std::mutex rb_mu;  // one read-back at a time uses the page and the read-back scratch
     Launch L{};
     int64_t host_step = 0;
@@ -402,6 +407,42 @@ hipError_t static_scratch_address(void **out)
     }
     *out = g_scratch_ptr[dev];
     return hipSuccess;
+}
+
+constexpr int kHostPages = 64;
+std::mutex g_page_mu;
+HostPage *g_pages;
+uint64_t g_page_used;  // bit k: page k of the block is taken
+
+hipError_t host_page_take(HostPage **out)
+{
+    std::lock_guard<std::mutex> lk(g_page_mu);
+    if (!g_pages) {
+        void *p = nullptr;
+        const hipError_t e = hipHostMalloc(&p, kHostPages * sizeof(HostPage), hipHostMallocPortable);
+        if (e != hipSuccess) return e;
+        g_pages = (HostPage *)p;
+    }
+    if (~g_page_used) {
+        const int k = __builtin_ctzll(~g_page_used);
+        g_page_used |= 1ull << k;
+        *out = g_pages + k;
+        return hipSuccess;
+    }
+    void *p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, sizeof(HostPage), hipHostMallocPortable);
+    *out = (HostPage *)p;
+    return e;
+}
+
+void host_page_give(HostPage *p)
+{
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(g_page_mu);
+    if (p >= g_pages && p < g_pages + kHostPages)
+        g_page_used &= ~(1ull << (p - g_pages));
+    else
+        (void)hipHostFree(p);
 }
 
 int fail(pic_ctx *c, int code, const std::string &m)
@@ -735,7 +776,7 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
     auto done = [&](int code) {
         if (code != PIC_OK) {
             fprintf(stderr, "pic_init: %s\n", c->msg.c_str());
-            if (c->page) (void)hipHostFree(c->page);
+            host_page_give(c->page);
             delete c;
             return code;
         }
@@ -746,7 +787,7 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
 #define IHIP(expr)                                              \
     if ((e = (expr)) != hipSuccess) return done(hipfail(c, e, #expr));
     IHIP(static_scratch_address(&c->static_scratch));
-    IHIP(hipHostMalloc((void **)&c->page, sizeof(*c->page), hipHostMallocDefault));
+    IHIP(host_page_take(&c->page));
     IHIP(hipMemsetAsync(c->ws, 0, need, s));
     IHIP(hipMemcpyAsync((void *)d.seg, c->P.seg.data(), c->P.seg.size() * sizeof(SegC), hipMemcpyHostToDevice, s));
     IHIP(hipMemcpyAsync((void *)d.ens, c->P.ens.data(), c->P.ens.size() * sizeof(EnsC), hipMemcpyHostToDevice, s));
@@ -1984,7 +2025,7 @@ void pic_free(pic_ctx *c)
     for (auto &e : c->ev) (void)hipEventDestroy(e);
     drop_graphs(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
-    if (c->page) (void)hipHostFree(c->page);
+    host_page_give(c->page);
     delete c;
 }
 

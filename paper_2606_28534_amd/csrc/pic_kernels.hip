@@ -1478,68 +1478,57 @@ __global__ void k_diag(Dev d, int sg, double *out /* [grid][2] */)
 // the 256-cell run went from 769 to 569 us; of the 64 batched ensembles, whose 64 pairs of reads
 // took 39 of 131 ms, to 106 ms.
 // =======================================================================================
-__device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long *s)
-{
-    v = wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a + b; });
-    if (lane_id() == 0) s[threadIdx.x / kWave] = v;
-    __syncthreads();
-    unsigned long long r = 0;
-    for (int i = 0; i < (int)(blockDim.x / kWave); ++i) r += s[i];
-    __syncthreads();
-    return r;
-}
-
 // With `tallied`, counts, sums of |v|^2 and field energy come from the fused step's tallies;
-// otherwise from `v2` ([species][ngrid][2], k_diag) and the field-energy kernel.
-__global__ void __launch_bounds__(kCntStripes) k_diag_pack(Dev d, int en, int tallied, const double *v2, int ngrid,
-                                                           DiagPack *out)
+// otherwise from `v2` ([species][ngrid][2], k_diag) and the field-energy kernel.  A wave takes a
+// quantity of a species (or the field energy) on its own, its lanes the stripes.
+constexpr int kDiagThreads = 1024;
+__global__ void __launch_bounds__(kDiagThreads) k_diag_pack(Dev d, int en, int tallied, const double *v2, int ngrid,
+                                                            DiagPack *out)
 {
-    __shared__ double s_buf[16];
-    __shared__ unsigned long long s_u[16];
+    constexpr int Q = C_NCNT + S_NSUM + 2;  // counters, wall sums, alive and |v|^2
     const EnsC &e = d.ens[en];
-    const int st = threadIdx.x;
+    const int lane = lane_id(), nsp = e.nspecies;
     const int vc = *d.vcur;
-    for (int sp = 0; sp < e.nspecies; ++sp) {
-        const int sg = e.seg[sp];
-        const unsigned long long *c = d.cnt + ((int64_t)st * d.nseg + sg) * C_NCNT;
-        unsigned long long cv[C_NCNT];
-#pragma unroll
-        for (int k = 0; k < C_NCNT; ++k) cv[k] = c[k];
-        const double *sm = d.sums + ((int64_t)st * d.nseg + sg) * S_NSUM;
-        double f[4] = {sm[S_KE_L], sm[S_KE_R], 0.0, 0.0};
-        if (tallied) {
-            const double *ts = step_sums(d, vc, st, sg);
-            f[2] = ts[T_N];
-            f[3] = ts[T_V2];
+    for (int t = (int)threadIdx.x / kWave; t <= nsp * Q; t += kDiagThreads / kWave) {
+        const int sp = t / Q, q = t % Q;
+        if (t == nsp * Q) {
+            double fe = 0.0;
+            if (tallied)
+                for (int64_t k = lane; k < e.nchunks; k += kWave) fe += d.part[(e.chunk0 + k) * P_NPART + P_FE];
+            else if (lane == 0)
+                fe = d.fe[en];
+            fe = wave_sum_f64(fe);
+            if (lane == 0) out->fe = fe;
+        } else if (q < C_NCNT) {
+            unsigned long long c = 0;
+            for (int st = lane; st < kCntStripes; st += kWave) c += d.cnt[((int64_t)st * d.nseg + e.seg[sp]) * C_NCNT + q];
+            c = wave_reduce(c, [](unsigned long long a, unsigned long long b) { return a + b; });
+            if (lane == 0) out->cnt[sp][q] = c;
         } else {
-            for (int i = st; i < ngrid; i += kCntStripes) {
-                f[2] += v2[((int64_t)sp * ngrid + i) * 2];
-                f[3] += v2[((int64_t)sp * ngrid + i) * 2 + 1];
+            const int k = q - C_NCNT;
+            double f = 0.0;
+            if (k < S_NSUM) {
+                for (int st = lane; st < kCntStripes; st += kWave)
+                    f += d.sums[((int64_t)st * d.nseg + e.seg[sp]) * S_NSUM + k];
+            } else if (tallied) {
+                for (int st = lane; st < kCntStripes; st += kWave)
+                    f += step_sums(d, vc, st, e.seg[sp])[k == S_NSUM ? T_N : T_V2];
+            } else {
+                for (int i = lane; i < ngrid; i += kWave) f += v2[((int64_t)sp * ngrid + i) * 2 + (k - S_NSUM)];
+            }
+            f = wave_sum_f64(f);
+            if (lane == 0) {
+                if (k < S_NSUM)
+                    out->wall_v2[sp][k] = f;
+                else if (k == S_NSUM)
+                    out->n[sp] = f;
+                else
+                    out->v2[sp] = f;
             }
         }
-#pragma unroll
-        for (int k = 0; k < C_NCNT; ++k) cv[k] = block_sum_u64(cv[k], s_u);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) f[k] = block_sum(f[k], s_buf);
-        if (st == 0) {
-#pragma unroll
-            for (int k = 0; k < C_NCNT; ++k) out->cnt[sp][k] = cv[k];
-            out->wall_v2[sp][0] = f[0];
-            out->wall_v2[sp][1] = f[1];
-            out->n[sp] = f[2];
-            out->v2[sp] = f[3];
-            out->numax[sp] = d.numax[sg];
-        }
     }
-    double fe = 0.0;
-    if (tallied) {
-        for (int64_t k = st; k < e.nchunks; k += kCntStripes) fe += d.part[(e.chunk0 + k) * P_NPART + P_FE];
-        fe = block_sum(fe, s_buf);
-    } else {
-        fe = d.fe[en];
-    }
-    if (st == 0) {
-        out->fe = fe;
+    if (threadIdx.x < (unsigned)nsp) out->numax[threadIdx.x] = d.numax[e.seg[threadIdx.x]];
+    if (threadIdx.x == kDiagThreads - 1) {
         out->emax = d.emax[en];
         out->step = *d.step;
         out->neutrals = e.recycle ? d.nneu[(int64_t)*d.ncur * d.nens + en] : 0ull;
@@ -1803,7 +1792,7 @@ hipError_t launch_sort(const Dev &d, bool f64, const Launch &L, hipStream_t s)
 hipError_t launch_diag_pack(const Dev &d, int en, bool tallied, const double *v2, int ngrid, DiagPack *out,
                             hipStream_t s)
 {
-    hipLaunchKernelGGL(k_diag_pack, dim3(1), dim3(kCntStripes), 0, s, d, en, tallied ? 1 : 0, v2, ngrid, out);
+    hipLaunchKernelGGL(k_diag_pack, dim3(1), dim3(kDiagThreads), 0, s, d, en, tallied ? 1 : 0, v2, ngrid, out);
     return hipGetLastError();
 }
 
