@@ -484,7 +484,7 @@ hipError_t launch_after_pass(pic_ctx *c, hipStream_t s, int hist)
 {
     const Dev &d = c->d;
     const bool coll = c->cfg.collisions != 0;
-    if (!c->P.f64) return launch_after(d, c->L.ppt, s, hist, d.cap_tot, coll);
+    if (!c->P.f64) return launch_after(d, c->L.ppt, s, hist, d.cap_tot, coll && !inline_candidates(d, c->L.ppt));
     hipError_t e;
     if (coll && (e = launch_candidates(d, c->L, s, true, hist)) != hipSuccess) return e;
     if ((e = launch_neutrals(d, s)) != hipSuccess) return e;
@@ -556,7 +556,7 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
     }
     if ((e = launch_neutrals(d, s)) != hipSuccess) return e;
     if (coll) {
-        if ((e = launch_particles(d, c->L, s, f64, SB_COLLIDE, 0, false)) != hipSuccess) return e;
+        if ((e = launch_particles(d, c->L, s, f64, SB_COLLIDE, 0, false, false)) != hipSuccess) return e;
         if ((e = launch_candidates(d, c->L, s, f64, 0, false)) != hipSuccess) return e;
     }
     if ((e = launch_source(d, 0, s, false)) != hipSuccess) return e;

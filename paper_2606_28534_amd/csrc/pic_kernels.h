@@ -20,9 +20,11 @@ struct Launch {
 enum StageBits : int { SB_PUSH = 1, SB_COLLIDE = 2, SB_DEPOSIT = 4, SB_HIST = 8 };
 
 // With the COLLIDE stage the null-collision bound kernel runs first unless `with_params`
-// is false (the caller launched it).
+// is false (the caller launched it).  Small FP32 runs collide their candidates in the pass
+// (inline_candidates; without `depo` their new pairs are left to a later deposit), all others
+// in launch_candidates or launch_after.
 hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f64, int stages, int hist,
-                            bool with_params = true);
+                            bool with_params = true, bool depo = true);
 hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist);
 hipError_t launch_field_energy(const Dev &d, hipStream_t s);
 // After a pass with the COLLIDE stage: the FP32 form's candidate kernel (no-op for FP64,
@@ -55,8 +57,9 @@ hipError_t launch_sort_prepare(const Dev &d, hipStream_t s);
 // FP32 fused pass that also scatters into cell order (after launch_sort_prepare), then the
 // slot counts and the buffer flip.
 hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, bool nt);
-hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot,
-                         bool nt);
+hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, bool nt,
+                         bool depo);
+bool inline_candidates(const Dev &d, int ppt);
 hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool depo);
 // the fused step's candidates, neutrals and source as one launch (FP32 form)
 hipError_t launch_after(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool coll);

@@ -1572,20 +1572,20 @@ __global__ void k_err_out(const int32_t *err, int32_t *out) { *out = *err; }
     } while (0)
 
 hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f64, int stages, int hist,
-                            bool with_params)
+                            bool with_params, bool depo)
 {
     // the null-collision bound of every segment from this step's speed and field maxima
     if ((stages & SB_COLLIDE) && with_params) {
         hipLaunchKernelGGL(k_params, dim3(1), dim3(256), 0, s, d);
         LAUNCH_CHECK();
     }
-    if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt != 0);
+    if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt != 0, depo);
     return launch_pass64(d, L.block, s, stages, hist);
 }
 
 hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist, bool depo)
 {
-    if (f64) return hipSuccess;
+    if (f64 || inline_candidates(d, L.ppt)) return hipSuccess;
     return launch_cand32(d, L.ppt, s, hist, d.cap_tot, depo);
 }
 

@@ -169,11 +169,111 @@ __device__ __forceinline__ void tile_reserve(uint32_t *sCnt, int Ws, uint32_t *c
     }
 }
 
+// The collision candidates of one tile inside the pass (INL): one thread per candidate, from the
+// tile's records (staged in LDS, beyond kRecLds in the tile's part of crec), as k_cand32 does
+// for many tiles: scatter, write the velocity back, and on ionisation append and deposit the
+// new pair.  Called by the whole block after a barrier that the particles' stores have
+// passed; the tallies go to the pass's own.
+struct TileTally {
+    uint32_t *c;              // counters (C_EL, C_IZ, C_CX)
+    double *kes;              // change of sum |v|^2
+    uint32_t *nal;            // births
+    unsigned long long *v2;   // largest |v|^2
+};
+template <bool CXREL>
+__device__ __forceinline__ void tile_collide(const Dev &d, const SegC &S, const EnsC &e, int sg, int buf, uint32_t nc,
+                                             const uint4 *s_rec, const uint4 *g_rec, bool depo, bool hist, int st,
+                                             const TileTally &tl)
+{
+    __shared__ uint32_t s_nb, s_bbase;
+    const uint32_t tag = (uint32_t)(*d.step);
+    const int half = 1 - *d.vcur, bst = (int)(blockIdx.x & (kStripes - 1));
+    const double numax = d.numax[sg], pnull = d.pnull[sg];
+    const int oth = S.other;
+    const BirthBuf bb = birth_buf(d, (int)(tag & 1u));
+    for (uint32_t q0 = 0; q0 < nc; q0 += 256) {
+        const uint32_t q = q0 + threadIdx.x;
+        const bool act = q < nc;
+        int ch = -1;
+        PS<false> p;
+        double ve[3], vi[3];
+        if (threadIdx.x == 0) s_nb = 0u;
+        __syncthreads();
+        uint32_t lb = 0;
+        if (act) {
+            const uint4 *r = q < kRecLds ? s_rec + 2 * q : g_rec + 2 * q;
+            const uint4 r0 = r[0], r1 = r[1];
+            p.cell = (int)r0.y;
+            p.off = __uint_as_float(r0.z);
+            p.id = r0.w;
+            p.vx = __uint_as_float(r1.x);
+            p.vy = __uint_as_float(r1.y);
+            p.vz = __uint_as_float(r1.z);
+            ch = p_collide<false, CXREL>(e, S, S.species, numax, pnull, tag, p, ve, vi);
+            double v2m = speed2_rn(p.vx, p.vy, p.vz);
+            if (ch >= 0) {
+                const int64_t i = (int64_t)r0.x;
+                d.fvx[buf][i] = p.vx;
+                d.fvy[buf][i] = p.vy;
+                d.fvz[buf][i] = p.vz;
+                double dk = v2m - (double)speed2_f32(__uint_as_float(r1.x), __uint_as_float(r1.y), __uint_as_float(r1.z));
+                atomicAdd(tl.c + (ch == 0 ? C_EL : ch == 1 ? C_IZ : C_CX), 1u);
+                if (ch == 1) {
+                    lb = atomicAdd(&s_nb, 1u);
+                    v2m = fmax(v2m, speed2_rn(ve[0], ve[1], ve[2]));
+                    dk += speed2_rn((float)ve[0], (float)ve[1], (float)ve[2]);
+                    atomicAdd(tl.nal, 1u);
+                    if (oth >= 0) {
+                        const double ki = speed2_rn((float)vi[0], (float)vi[1], (float)vi[2]);
+                        double *ts = step_sums(d, half, st, oth);
+                        unsafeAtomicAdd(ts + T_V2, ki);
+                        unsafeAtomicAdd(ts + T_N, 1.0);
+                        atomicMax(d.vmax2 + ((int64_t)half * kCntStripes + st) * d.nseg + oth,
+                                  dbits(speed2_rn(vi[0], vi[1], vi[2])));
+                    }
+                }
+                unsafeAtomicAdd(tl.kes, dk);
+            }
+            if (v2m > 0.0) atomicMax(tl.v2, dbits(v2m));
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && s_nb) s_bbase = atomicAdd(bb.nbirth + bst, s_nb);
+        if (ch == 1 && depo) {
+            global_deposit32(d, S, S.species, p.cell, p.off, hist);
+            if (oth >= 0) global_deposit32(d, d.seg[oth], 1, p.cell, p.off, hist);
+        }
+        __syncthreads();
+        if (ch == 1) {
+            const uint32_t slot = s_bbase + lb;
+            if ((int64_t)slot < d.birth_stripe_cap) {
+                Birth &B = bb.births[(int64_t)bst * d.birth_stripe_cap + slot];
+                B.pid = p.id;
+                B.ens = S.ens;
+                B.cell = p.cell;
+                B.off = p.off;
+                B.x = ((double)p.cell + (double)p.off) * S.dx;
+                for (int c = 0; c < 3; ++c) {
+                    B.ve[c] = ve[c];
+                    B.vi[c] = vi[c];
+                }
+                birth_mark(bb, e, p.id);
+            } else {
+                atomicOr(d.err, (int)E_CAP_BIRTH);
+            }
+        }
+    }
+    __syncthreads();  // the tallies are complete
+}
+
 // With SORT (a fused pass on the step after a histogram step) every live particle is written
 // to the other buffer at its place in cell order instead of in place: the tile ranks its
 // particles by their cell before the push (the cells the previous pass counted) in LDS and
 // reserves one run per cell, as the sort scatter does, so the pass also sorts and compacts.
-template <int STAGES, int PPT, bool NT = false, bool SORT = false>
+// With INL (few tiles, see inline_candidates) the tile's collision candidates are collided here
+// as well; hist_rt then also says, in kNoDepo, that the new pairs' deposit is left out.
+constexpr int kHist = 1, kNoDepo = 2;
+enum Inl : int { INL_NO = 0, INL_YES = 1, INL_CXREL = 2 };
+template <int STAGES, int PPT, bool NT = false, bool SORT = false, int INL = INL_NO>
 __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64_t T)
 {
     constexpr bool PUSH = STAGES & PS_PUSH;
@@ -209,7 +309,7 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
     const EnsC &e = d.ens[S.ens];
     const int s = S.species;
     const int b = *d.cur;
-    const bool hist = HISTC || (hist_rt != 0);
+    const bool hist = HISTC || (hist_rt & kHist) != 0;
     const int tid = threadIdx.x;
 
     const int64_t i0 = first + (int64_t)tid * PPT;
@@ -555,7 +655,12 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
             atomicAdd(&s_nal, na);
         }
     }
+    // (INL: the particles' own stores are complete before a collision writes a velocity again)
+    if constexpr (INL != INL_NO) __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    if constexpr (INL != INL_NO)
+        tile_collide<INL == INL_CXREL>(d, S, e, sg, SORT ? 1 - b : b, s_nc, s_rec, d.crec + 2 * first,
+                                       (hist_rt & kNoDepo) == 0, hist, st, TileTally{s_c, &s_kes, &s_nal, &s_v2});
     if (WIN) {
         const int nn = G.periodic ? G.ncells : G.ncells + 1;
         unsigned long long *Q = d.Qi + (int64_t)s * d.nodes_tot + G.gbase;
@@ -577,7 +682,7 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
             }
         }
     }
-    if (COLL) {
+    if (COLL && INL == INL_NO) {
         const uint32_t nl = 2 * min(s_nc, (uint32_t)kRecLds);
         for (uint32_t i = tid; i < nl; i += 256) d.crec[2 * first + i] = s_rec[i];
         if (tid == 0) d.ctile[t] = s_nc | ctag;
@@ -589,10 +694,10 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
         double *sm = d.sums + ((int64_t)st * d.nseg + sg) * S_NSUM;
         if (s_ke[0] != 0.0) unsafeAtomicAdd(sm + S_KE_L, s_ke[0]);
         if (s_ke[1] != 0.0) unsafeAtomicAdd(sm + S_KE_R, s_ke[1]);
-        if (COLL && (s_v2 || s_nal)) {
+        if (COLL && (s_v2 || s_nal || s_kes != 0.0)) {
             const int half = 1 - *d.vcur;
             if (s_v2) atomicMax(d.vmax2 + ((int64_t)half * kCntStripes + st) * d.nseg + sg, s_v2);
-            if (PUSH && s_nal) {
+            if ((PUSH || INL != INL_NO) && (s_nal || s_kes != 0.0)) {
                 double *ts = step_sums(d, half, st, sg);
                 unsafeAtomicAdd(ts + T_V2, s_kes);
                 unsafeAtomicAdd(ts + T_N, (double)s_nal);
@@ -724,9 +829,6 @@ __global__ void k_sort_finish(Dev d)
 }
 
 // =======================================================================================
-hipError_t launch_pass32_stages(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist,
-                                int64_t cap_tot, bool nt);
-
 // The sorting pass ranks its tile in 4 more bytes of LDS per window cell; its window span
 // is capped so that its LDS stays within what the plain pass's occupancy allows (12 B per
 // cell x 1024 cells + the static LDS, seven blocks per CU).  Cells outside the window go
@@ -734,7 +836,16 @@ hipError_t launch_pass32_stages(const Dev &d, int ppt, int W, hipStream_t s, int
 // the window's words carry the counts.)
 constexpr int kCountWindowMax = 1024;
 
-template <int STAGES, bool NT = false, bool SORT = false>
+// The candidates are collided inside the pass in runs of at most kInlineTiles tiles of slot
+// capacity.  There the candidates' own launch, a chain of round trips behind the pass's, costs
+// more than what the collisions' registers (fewer waves per SIMD) and divergence cost the pass:
+// per fused step 29.3 us with the launch and 25.3 without at 108 tiles, 37.9 and 29.0 at 789, 61.2
+// and 49.8 at 3914, 73.8 and 67.0 at 7820, 103.3 and 101.4 at 15633 (half of each in use).  The
+// pass over 4e7 particles lost 45 us per step to it.
+constexpr int64_t kInlineTiles = 16384;
+bool inline_candidates(const Dev &d, int ppt) { return d.cap_tot / (256 * ppt) <= kInlineTiles; }
+
+template <int STAGES, bool NT = false, bool SORT = false, int INL = INL_NO>
 static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, int hist, int64_t cap_tot)
 {
     if (SORT) W = std::min(W, kCountWindowMax);
@@ -742,13 +853,21 @@ static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, i
     if (ppt == 4) {
         const int64_t T = cap_tot / (256 * 4);
         const int64_t G = (T + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_pass32<STAGES, 4, NT, SORT>), dim3(G), dim3(256), lds, s, d, W, hist, T);
+        hipLaunchKernelGGL((k_pass32<STAGES, 4, NT, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
     } else {
         const int64_t T = cap_tot / (256 * 8);
         const int64_t G = (T + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_pass32<STAGES, 8, NT, SORT>), dim3(G), dim3(256), lds, s, d, W, hist, T);
+        hipLaunchKernelGGL((k_pass32<STAGES, 8, NT, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
     }
     return hipGetLastError();
+}
+
+// A pass with the COLLIDE stage that also collides its candidates.
+template <int STAGES, bool SORT>
+static hipError_t launch_pass32_inl(const Dev &d, int ppt, int W, hipStream_t s, int hist, int64_t cap_tot)
+{
+    if (d.any_cx_rel) return launch_pass32_t<STAGES, false, SORT, INL_CXREL>(d, ppt, W, s, hist, cap_tot);
+    return launch_pass32_t<STAGES, false, SORT, INL_YES>(d, ppt, W, s, hist, cap_tot);
 }
 
 // The fused pass that also sorts (after launch_sort_prepare on the previous step's
@@ -756,7 +875,9 @@ static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, i
 hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, bool nt)
 {
     hipError_t e;
-    if (coll && nt)
+    if (coll && inline_candidates(d, ppt))
+        e = launch_pass32_inl<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, true>(d, ppt, W, s, 0, cap_tot);
+    else if (coll && nt)
         e = launch_pass32_t<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, true, true>(d, ppt, W, s, 0, cap_tot);
     else if (coll)
         e = launch_pass32_t<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, false, true>(d, ppt, W, s, 0, cap_tot);
@@ -795,17 +916,16 @@ hipError_t launch_stream_copy(const void *src, void *dst, int64_t nwords, bool n
 }
 
 
-hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot,
-                         bool nt)
+hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, bool nt,
+                         bool depo)
 {
-    return launch_pass32_stages(d, ppt, W, s, stages, hist, cap_tot, nt);
-}
-
-hipError_t launch_pass32_stages(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot,
-                                bool nt)
-{
-    if (nt && stages == (PS_PUSH | PS_COLLIDE | PS_DEPOSIT))
-        return launch_pass32_t<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, true>(d, ppt, W, s, hist, cap_tot);
+    constexpr int FUSED = PS_PUSH | PS_COLLIDE | PS_DEPOSIT;
+    if ((stages & PS_COLLIDE) && inline_candidates(d, ppt)) {
+        const int rt = (hist ? kHist : 0) | (depo ? 0 : kNoDepo);
+        if (stages == FUSED) return launch_pass32_inl<FUSED, false>(d, ppt, W, s, rt, cap_tot);
+        if (stages == PS_COLLIDE) return launch_pass32_inl<PS_COLLIDE, false>(d, ppt, W, s, rt, cap_tot);
+    }
+    if (nt && stages == FUSED) return launch_pass32_t<FUSED, true>(d, ppt, W, s, hist, cap_tot);
     switch (stages) {
     case PS_PUSH:
         return launch_pass32_t<PS_PUSH>(d, ppt, W, s, hist, cap_tot);
@@ -815,8 +935,8 @@ hipError_t launch_pass32_stages(const Dev &d, int ppt, int W, hipStream_t s, int
         return launch_pass32_t<PS_DEPOSIT>(d, ppt, W, s, hist, cap_tot);
     case PS_HIST:
         return launch_pass32_t<PS_HIST>(d, ppt, W, s, hist, cap_tot);
-    case PS_PUSH | PS_COLLIDE | PS_DEPOSIT:
-        return launch_pass32_t<PS_PUSH | PS_COLLIDE | PS_DEPOSIT>(d, ppt, W, s, hist, cap_tot);
+    case FUSED:
+        return launch_pass32_t<FUSED>(d, ppt, W, s, hist, cap_tot);
     case PS_PUSH | PS_DEPOSIT:
         return launch_pass32_t<PS_PUSH | PS_DEPOSIT>(d, ppt, W, s, hist, cap_tot);
     default:
