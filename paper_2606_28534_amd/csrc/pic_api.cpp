@@ -269,7 +269,7 @@ size_t carve(const Plan &P, char *base, Dev &d)
         }
     }
     d.cap_tot = P.cap_tot;
-    d.cur = c.take<int32_t>(1);
+    d.cur = c.take<int32_t>(2);
     d.n_slots = c.take<int64_t>(P.nseg);
     d.next_id = c.take<uint32_t>(P.nseg);
     d.step = c.take<int64_t>(1);
@@ -521,7 +521,7 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
         const int stages = coll ? (SB_PUSH | SB_COLLIDE | SB_DEPOSIT) : (SB_PUSH | SB_DEPOSIT);
         if (tm && (e = hipEventRecord(c->ev[c->ev_used], s)) != hipSuccess) return e;
         if (sorting)
-            e = launch_pass32_sort(d, c->L.ppt, c->L.window, s, coll, d.cap_tot, c->L.nt != 0);
+            e = launch_pass32_sort(d, c->L.ppt, c->L.window, s, coll, d.cap_tot, c->L.nt);
         else
             e = launch_particles(d, c->L, s, f64, stages, hist, false);
         if (e != hipSuccess) return e;
@@ -605,7 +605,7 @@ hipError_t enqueue_window(pic_ctx *c, hipStream_t s, int64_t n0, int len, bool &
         const int hist = (prep || (sort_now && !sorting)) ? 1 : 0;
         if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, pending, true)) != hipSuccess) return e;
         if (sorting)
-            e = launch_pass32_sort(d, c->L.ppt, c->L.window, s, true, d.cap_tot, c->L.nt != 0);
+            e = launch_pass32_sort(d, c->L.ppt, c->L.window, s, true, d.cap_tot, c->L.nt);
         else
             e = launch_particles(d, c->L, s, f64, stages, hist, false);
         if (e != hipSuccess) return e;
@@ -715,7 +715,7 @@ Launch default_launch(const pic_config *cfg, const Plan &P)
     L.ppt = 4;  // particles per thread of the FP32 pass (4 or 8; the autotuner may change it)
     if (cfg->precision == PIC_FP32_CELLOFF && (cfg->ppt == 4 || cfg->ppt == 8)) L.ppt = cfg->ppt;
     L.sort_ppt = (cfg->sort_ppt == 4 || cfg->sort_ppt == 8) ? cfg->sort_ppt : 4;
-    L.nt = (cfg->nontemporal & 1) ? 1 : 0;
+    L.nt = (cfg->nontemporal & 1) ? 1 : 2;
     L.sort_nt = (cfg->nontemporal & 2) ? 1 : 0;
     int64_t tiles = 0;
     for (const SegC &S : P.seg) tiles += (S.cap + (int64_t)L.block * L.ppt - 1) / ((int64_t)L.block * L.ppt);
@@ -805,6 +805,7 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
     }
     IHIP(hipMemcpyAsync(d.n_slots, nslots.data(), nslots.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
     IHIP(hipMemcpyAsync(d.next_id, nid.data(), nid.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+    IHIP(launch_stream_flag(d, s));
     IHIP(launch_vmax(d, c->P.f64, s));
     IHIP(launch_zero_q(d, c->P.f64, s));
     IHIP(launch_particles(d, c->L, s, c->P.f64, SB_DEPOSIT, 0));
@@ -1229,6 +1230,7 @@ int pic_set_particles(pic_ctx *c, int32_t ens, int32_t species, pic_particles in
     HIPC(c, hipMemcpy(&vc, c->d.vcur, 4, hipMemcpyDeviceToHost));
     HIPC(c, hipMemset(c->d.vmax2 + (size_t)vc * kCntStripes * c->P.nseg, 0, (size_t)kCntStripes * c->P.nseg * 8));
     HIPC(c, launch_vmax(c->d, c->P.f64, s));
+    HIPC(c, launch_stream_flag(c->d, s));
     HIPC(c, hipStreamSynchronize(s));
     return PIC_OK;
 }
@@ -1761,7 +1763,7 @@ int pic_autotune(pic_ctx *c, int32_t trial_steps, int32_t *shape, void *stream)
         shape[0] = c->L.ppt;
         shape[1] = c->L.window;
         shape[2] = c->L.sort_ppt;
-        shape[3] = c->L.nt;
+        shape[3] = c->L.nt == 1 ? 1 : 0;
         shape[4] = c->L.sort_nt;
     }
     return check_err(c, s);
@@ -1979,6 +1981,7 @@ int pic_load(pic_ctx *c, const void *host_buf, size_t bytes, void *stream)
     HIPC(c, hipMemcpyAsync(d.cur, &zero, 4, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.vcur, &zero, 4, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.step, &h.step, 8, hipMemcpyHostToDevice, s));
+    HIPC(c, launch_stream_flag(d, s));
     HIPC(c, hipStreamSynchronize(s));
     c->host_step = h.step;
     drop_graphs(c);

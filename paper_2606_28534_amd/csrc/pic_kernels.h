@@ -13,7 +13,7 @@ struct Launch {
     int grid;    // the FP64 sort scatter's blocks / 8 (a multiple of 8 for the XCD-aware mapping)
     int window;  // widest LDS window span, in cells, of the FP32 pass and of the sorts
     int sort_ppt;  // particles per thread of the FP32 sort scatter
-    int nt;        // fused FP32 pass: non-temporal particle loads and stores
+    int nt;        // fused FP32 pass: particle loads and stores cached (0), non-temporal (1) or by size (2)
     int sort_nt;   // FP32 sort scatter: non-temporal loads
 };
 
@@ -56,10 +56,12 @@ hipError_t launch_sort(const Dev &d, bool f64, const Launch &L, hipStream_t s);
 hipError_t launch_sort_prepare(const Dev &d, hipStream_t s);
 // FP32 fused pass that also scatters into cell order (after launch_sort_prepare), then the
 // slot counts and the buffer flip.
-hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, bool nt);
-hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, bool nt,
+hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, int nt);
+hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, int nt,
                          bool depo);
 bool inline_candidates(const Dev &d, int ppt);
+// after the host set the slots in use
+hipError_t launch_stream_flag(const Dev &d, hipStream_t s);
 hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool depo);
 // the fused step's candidates, neutrals and source as one launch (FP32 form)
 hipError_t launch_after(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool coll);

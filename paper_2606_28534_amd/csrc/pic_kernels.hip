@@ -1579,7 +1579,7 @@ hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f
         hipLaunchKernelGGL(k_params, dim3(1), dim3(256), 0, s, d);
         LAUNCH_CHECK();
     }
-    if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt != 0, depo);
+    if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt, depo);
     return launch_pass64(d, L.block, s, stages, hist);
 }
 

@@ -11,6 +11,7 @@
 // appended particles spread over many cells still deposits through LDS.
 // Block b takes tile b (see tile_of_block for why not an XCD-major order).
 #include <algorithm>
+#include <type_traits>
 
 #include "pic_device.h"
 #include "pic_kernels.h"
@@ -269,11 +270,21 @@ __device__ __forceinline__ void tile_collide(const Dev &d, const SegC &S, const 
 // to the other buffer at its place in cell order instead of in place: the tile ranks its
 // particles by their cell before the push (the cells the previous pass counted) in LDS and
 // reserves one run per cell, as the sort scatter does, so the pass also sorts and compacts.
+// How the pass moves the particle arrays: cached, non-temporal, or by the run's size.  In place
+// over more particle data than the 256 MB last-level cache holds, non-temporal streams are
+// faster, over less than that they throw away what the next pass finds cached: per fused step
+// (cached, non-temporal) 104.0 and 106.2 us at 8e6 particles (192 MB), 122.3 and 121.8 at 1e7,
+// 142.7 and 140.8 at 1.2e7, 192.8 and 169.9 at 1.6e7, 442 and 381 at 4e7.  The line lies at
+// kStreamSlots slots in use; the host knows only the capacity, so the sort counts them and the
+// pass reads the answer beside the buffer index (d.cur[1]).
+constexpr int64_t kStreamSlots = 10'000'000;
+enum NtMode : int { NT_CACHED = 0, NT_STREAM = 1, NT_AUTO = 2 };
+
 // With INL (few tiles, see inline_candidates) the tile's collision candidates are collided here
 // as well; hist_rt then also says, in kNoDepo, that the new pairs' deposit is left out.
 constexpr int kHist = 1, kNoDepo = 2;
 enum Inl : int { INL_NO = 0, INL_YES = 1, INL_CXREL = 2 };
-template <int STAGES, int PPT, bool NT = false, bool SORT = false, int INL = INL_NO>
+template <int STAGES, int PPT, int NTM = NT_CACHED, bool SORT = false, int INL = INL_NO>
 __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64_t T)
 {
     constexpr bool PUSH = STAGES & PS_PUSH;
@@ -317,7 +328,10 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
     int cell[PPT];
     float off[PPT], vx[PPT], vy[PPT], vz[PPT];
     uint32_t id[PPT];
-    if (full) {
+    // non-temporal loads and stores of the particle arrays (see kStreamSlots)
+    const bool nt = NTM == NT_STREAM || (NTM == NT_AUTO && d.cur[1] != 0);
+    auto load = [&](auto hint) {
+        constexpr bool NT = decltype(hint)::value;
         vload<PPT, NT>(d.cell[b] + i0, cell);
         vload<PPT, NT>(d.off[b] + i0, off);
         if (NEED_V) {
@@ -326,6 +340,12 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
             vload<PPT, NT>(d.fvz[b] + i0, vz);
         }
         if (NEED_ID) vload<PPT, NT>(d.id[b] + i0, id);
+    };
+    if (full) {
+        if (nt)
+            load(std::true_type{});
+        else
+            load(std::false_type{});
     } else {
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
@@ -584,7 +604,8 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
             d.id[nb][o] = id[k];
         }
     } else if (PUSH || COLL) {
-        if (full) {
+        auto store = [&](auto hint) {
+            constexpr bool NT = decltype(hint)::value;
             if (PUSH) {
                 // a group of four cells is stored only if one of them changed (the heavy
                 // ions almost never leave their cell in one step)
@@ -600,6 +621,12 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
             vstore<PPT, NT>(d.fvx[b] + i0, vx);
             vstore<PPT, NT>(d.fvy[b] + i0, vy);
             vstore<PPT, NT>(d.fvz[b] + i0, vz);
+        };
+        if (full) {
+            if (nt)
+                store(std::true_type{});
+            else
+                store(std::false_type{});
         } else {
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
@@ -817,15 +844,42 @@ __global__ void __launch_bounds__(256) k_sort32(Dev d, int W, int64_t T)
     }
 }
 
-__global__ void k_sort_finish(Dev d)
+// Whether the particle arrays in use call for non-temporal streams, by a block of 256 threads.
+__device__ __forceinline__ void set_stream_flag(const Dev &d, int64_t mine)
 {
+    __shared__ unsigned long long s_n;
+    if (threadIdx.x == 0) s_n = 0ull;
+    __syncthreads();
+    if (mine) atomicAdd(&s_n, (unsigned long long)mine);
+    __syncthreads();
+    if (threadIdx.x == 0) d.cur[1] = s_n >= (unsigned long long)kStreamSlots ? 1 : 0;
+}
+
+__global__ void __launch_bounds__(256) k_sort_finish(Dev d)
+{
+    int64_t mine = 0;
     for (int sg = threadIdx.x; sg < d.nseg; sg += blockDim.x) {
         const SegC &S = d.seg[sg];
-        const int64_t n = (int64_t)d.cursor[S.cbase + S.ncells - 1] - d.segstart[sg];
-        d.n_slots[sg] = min(max(n, (int64_t)0), S.cap);
+        const int64_t n = min(max((int64_t)d.cursor[S.cbase + S.ncells - 1] - d.segstart[sg], (int64_t)0), S.cap);
+        d.n_slots[sg] = n;
+        mine += n;
     }
-    __syncthreads();
+    set_stream_flag(d, mine);
     if (threadIdx.x == 0) *d.cur = 1 - *d.cur;
+}
+
+// After the host set the slots in use (a load, an injection, a restart).
+__global__ void __launch_bounds__(256) k_stream_flag(Dev d)
+{
+    int64_t mine = 0;
+    for (int sg = threadIdx.x; sg < d.nseg; sg += blockDim.x) mine += d.n_slots[sg];
+    set_stream_flag(d, mine);
+}
+
+hipError_t launch_stream_flag(const Dev &d, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_stream_flag, dim3(1), dim3(256), 0, s, d);
+    return hipGetLastError();
 }
 
 // =======================================================================================
@@ -845,7 +899,7 @@ constexpr int kCountWindowMax = 1024;
 constexpr int64_t kInlineTiles = 16384;
 bool inline_candidates(const Dev &d, int ppt) { return d.cap_tot / (256 * ppt) <= kInlineTiles; }
 
-template <int STAGES, bool NT = false, bool SORT = false, int INL = INL_NO>
+template <int STAGES, int NTM = NT_CACHED, bool SORT = false, int INL = INL_NO>
 static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, int hist, int64_t cap_tot)
 {
     if (SORT) W = std::min(W, kCountWindowMax);
@@ -853,11 +907,11 @@ static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, i
     if (ppt == 4) {
         const int64_t T = cap_tot / (256 * 4);
         const int64_t G = (T + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_pass32<STAGES, 4, NT, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
+        hipLaunchKernelGGL((k_pass32<STAGES, 4, NTM, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
     } else {
         const int64_t T = cap_tot / (256 * 8);
         const int64_t G = (T + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_pass32<STAGES, 8, NT, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
+        hipLaunchKernelGGL((k_pass32<STAGES, 8, NTM, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
     }
     return hipGetLastError();
 }
@@ -866,23 +920,26 @@ static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, i
 template <int STAGES, bool SORT>
 static hipError_t launch_pass32_inl(const Dev &d, int ppt, int W, hipStream_t s, int hist, int64_t cap_tot)
 {
-    if (d.any_cx_rel) return launch_pass32_t<STAGES, false, SORT, INL_CXREL>(d, ppt, W, s, hist, cap_tot);
-    return launch_pass32_t<STAGES, false, SORT, INL_YES>(d, ppt, W, s, hist, cap_tot);
+    if (d.any_cx_rel) return launch_pass32_t<STAGES, NT_CACHED, SORT, INL_CXREL>(d, ppt, W, s, hist, cap_tot);
+    return launch_pass32_t<STAGES, NT_CACHED, SORT, INL_YES>(d, ppt, W, s, hist, cap_tot);
 }
 
 // The fused pass that also sorts (after launch_sort_prepare on the previous step's
 // histogram), then the new slot counts and the buffer flip.
-hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, bool nt)
+hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, int nt)
 {
+    constexpr int FUSED = PS_PUSH | PS_COLLIDE | PS_DEPOSIT;
     hipError_t e;
     if (coll && inline_candidates(d, ppt))
-        e = launch_pass32_inl<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, true>(d, ppt, W, s, 0, cap_tot);
-    else if (coll && nt)
-        e = launch_pass32_t<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, true, true>(d, ppt, W, s, 0, cap_tot);
+        e = launch_pass32_inl<FUSED, true>(d, ppt, W, s, 0, cap_tot);
+    else if (coll && nt == NT_AUTO)
+        e = launch_pass32_t<FUSED, NT_AUTO, true>(d, ppt, W, s, 0, cap_tot);
+    else if (coll && nt == NT_STREAM)
+        e = launch_pass32_t<FUSED, NT_STREAM, true>(d, ppt, W, s, 0, cap_tot);
     else if (coll)
-        e = launch_pass32_t<PS_PUSH | PS_COLLIDE | PS_DEPOSIT, false, true>(d, ppt, W, s, 0, cap_tot);
+        e = launch_pass32_t<FUSED, NT_CACHED, true>(d, ppt, W, s, 0, cap_tot);
     else
-        e = launch_pass32_t<PS_PUSH | PS_DEPOSIT, false, true>(d, ppt, W, s, 0, cap_tot);
+        e = launch_pass32_t<PS_PUSH | PS_DEPOSIT, NT_CACHED, true>(d, ppt, W, s, 0, cap_tot);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_sort_finish, dim3(1), dim3(256), 0, s, d);
     return hipGetLastError();
@@ -916,7 +973,7 @@ hipError_t launch_stream_copy(const void *src, void *dst, int64_t nwords, bool n
 }
 
 
-hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, bool nt,
+hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, int nt,
                          bool depo)
 {
     constexpr int FUSED = PS_PUSH | PS_COLLIDE | PS_DEPOSIT;
@@ -925,9 +982,13 @@ hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages
         if (stages == FUSED) return launch_pass32_inl<FUSED, false>(d, ppt, W, s, rt, cap_tot);
         if (stages == PS_COLLIDE) return launch_pass32_inl<PS_COLLIDE, false>(d, ppt, W, s, rt, cap_tot);
     }
-    if (nt && stages == FUSED) return launch_pass32_t<FUSED, true>(d, ppt, W, s, hist, cap_tot);
+    if (stages == FUSED) {
+        if (nt == NT_AUTO) return launch_pass32_t<FUSED, NT_AUTO>(d, ppt, W, s, hist, cap_tot);
+        if (nt == NT_STREAM) return launch_pass32_t<FUSED, NT_STREAM>(d, ppt, W, s, hist, cap_tot);
+    }
     switch (stages) {
     case PS_PUSH:
+        if (nt == NT_AUTO) return launch_pass32_t<PS_PUSH, NT_AUTO>(d, ppt, W, s, hist, cap_tot);
         return launch_pass32_t<PS_PUSH>(d, ppt, W, s, hist, cap_tot);
     case PS_COLLIDE:
         return launch_pass32_t<PS_COLLIDE>(d, ppt, W, s, hist, cap_tot);
@@ -938,6 +999,7 @@ hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages
     case FUSED:
         return launch_pass32_t<FUSED>(d, ppt, W, s, hist, cap_tot);
     case PS_PUSH | PS_DEPOSIT:
+        if (nt == NT_AUTO) return launch_pass32_t<PS_PUSH | PS_DEPOSIT, NT_AUTO>(d, ppt, W, s, hist, cap_tot);
         return launch_pass32_t<PS_PUSH | PS_DEPOSIT>(d, ppt, W, s, hist, cap_tot);
     default:
         return hipErrorInvalidValue;
