@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(AdjTile<G>::kThreads) k_adj_fwd(Dev d, AdjStat
         if (Qzero) Qzero[j] = 0ull;
         if (ckQ) ckQ[j] = d.Qi[j];
     }
-    solve_small<false, G, false>(d, e, 0, 0, sh, s_tab, blockIdx.x == 0 ? Erec : nullptr);
+    solve_small<false, G, false>(d, e, 0, 0, sh, s_tab, blockIdx.x == 0 ? Erec : nullptr, [] {});
     if (n == 0) return;  // the field alone
     if (ck.cell && i0 < n) {
 #pragma unroll

@@ -253,6 +253,7 @@ size_t carve(const Plan &P, char *base, Dev &d)
     d.nspecies = P.nspecies;
     d.seg = c.take<SegC>(P.nseg);
     d.ens = c.take<EnsC>(P.nens);
+    for (int i = 0; i < std::min(P.nseg, kArgSegs); ++i) d.seg_base[i] = P.seg[i].base;
     for (int b = 0; b < 2; ++b) {
         d.id[b] = c.take<uint32_t>(P.cap_tot);
         if (P.f64) {

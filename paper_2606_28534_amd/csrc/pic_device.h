@@ -55,6 +55,7 @@ enum StepSum : int { T_V2 = 0, T_N, T_NSTEP };
 // Per-chunk solve aggregates.
 enum Agg : int { A_SUMRHO = 0, A_SUMPRE, A_TOTQ, A_N1, A_D, A_CNT, A_RHO0, A_NAGG };
 enum Part : int { P_EMAX = 0, P_FE, P_PHISUM, P_NONFIN, P_NPART };
+constexpr int kArgSegs = 4;           // segments whose first slot every kernel has as an argument
 // Error flags (bit mask).
 enum Err : int { E_CAP_PART = 1, E_CAP_BIRTH = 2, E_CAP_ID = 4, E_NONFINITE = 8 };
 
@@ -129,6 +130,7 @@ struct Dev {
                               // (solve_small); 0: the chunked solve
     const SegC *seg;
     const EnsC *ens;
+    int64_t seg_base[kArgSegs];  // first slots of the first segments, in the kernel's arguments
     // particles (buffer b in {0,1}); FP32 and FP64 forms
     int32_t *cell[2];
     float *off[2], *fvx[2], *fvy[2], *fvz[2];
@@ -201,9 +203,16 @@ struct Dev {
     double *rb;               // read-back scratch: [2][diag grid][2], or [5][nodes of an ensemble]
 };
 
-// The segment whose slot range holds `slot`.
+// The segment whose slot range holds `slot`: of a few segments from the kernel's arguments, which
+// saves a block a round trip before its first loads.
 __device__ __forceinline__ int seg_of_slot(const Dev &d, int64_t slot)
 {
+    if (d.nseg <= kArgSegs) {
+        int sg = 0;
+#pragma unroll
+        for (int i = 1; i < kArgSegs; ++i) sg += (i < d.nseg && d.seg_base[i] <= slot) ? 1 : 0;
+        return sg;
+    }
     int lo = 0, hi = d.nseg;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;

@@ -283,7 +283,7 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve1(Dev d, int nchunks, in
     const int64_t N = e.ncells, nn = e.nnodes;
     const int64_t a = (k - e.chunk0) * kChunk;
     const int64_t j0 = a + (int64_t)threadIdx.x * kNodesPerThread;
-    double loc = 0.0, sumpre = 0.0, totq = 0.0, n1 = 0.0, dd = 0.0, cnt = 0.0;
+    double loc = 0.0, sumpre = 0.0, totq = 0.0;
     // thread-local prefix of interior rho and its running sum
     double rho_loc[kNodesPerThread];
     double rho_first = 0.0;  // rho of the chunk's first node (thread 0), for the next chunk's solve
@@ -347,41 +347,27 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve1(Dev d, int nchunks, in
         loc += rho_loc[q];
     }
     const double excl = block_incl_scan(loc, s_buf) - loc;
-    // integer counts in this thread's node range: interior nodes and the prefix weights
     double run = excl;
-    int64_t c1_before = 0;  // interior nodes in [a, j0)
-    {
-        const int64_t lo = max(a, (int64_t)1), hi = min(j0, N);  // [lo, hi) interior, i < j0
-        c1_before = hi > lo ? hi - lo : 0;
-    }
-    int64_t c1 = c1_before;
 #pragma unroll
     for (int q = 0; q < kNodesPerThread; ++q) {
-        const int64_t j = j0 + q;
         run += rho_loc[q];
-        if (j >= 1 && j <= N - 1) {
-            ++c1;
-            n1 += 1.0;
-        }
-        if (j < N) {  // m in [0, N-1]
-            sumpre += run;
-            dd += (double)c1;
-            cnt += 1.0;
-        }
+        if (j0 + q < N) sumpre += run;  // m in [0, N-1]
     }
     // the ensemble's max |E| is accumulated by the second pass's blocks (atomic max)
     if (k == e.chunk0 && threadIdx.x == 0) d.emax[ei] = 0.0;
-    __shared__ double s_red[6 * 16];
-    double v[6] = {loc, sumpre, totq, n1, dd, cnt};
-    block_sums<6>(v, s_red);
+    __shared__ double s_red[3 * 16];
+    double v[3] = {loc, sumpre, totq};
+    block_sums<3>(v, s_red);
     if (threadIdx.x == 0) {
         double *g = d.agg + k * A_NAGG;
         g[A_SUMRHO] = v[0];
         g[A_SUMPRE] = v[1];
         g[A_TOTQ] = v[2];
-        g[A_N1] = v[3];
-        g[A_D] = v[4];
-        g[A_CNT] = v[5];
+        double n1, dd, cnt;
+        chunk_counts(a, nn, N, n1, dd, cnt);
+        g[A_N1] = n1;
+        g[A_D] = dd;
+        g[A_CNT] = cnt;
         g[A_RHO0] = rho_first;
     }
 }
@@ -1005,6 +991,44 @@ __device__ __forceinline__ void place_reset(const Dev &d, int deferred, const Bi
         d.ssum[(int64_t)vc * kCntStripes * d.nseg * T_NSTEP + i] = 0.0;
 }
 
+// The pair of one birth, r-th of its ensemble's in the step, to its slots.
+template <bool F64>
+__device__ __forceinline__ void put_birth(const Dev &d, const Birth &B, uint32_t r, const PlaceEns &E,
+                                          const PlaceSeg *s_ps, int b)
+{
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        if (s >= E.nspecies) break;
+        const PlaceSeg &P = s_ps[E.seg[s]];
+        const int64_t slot = P.n_slots + r;
+        if (slot >= P.cap) {
+            atomicOr(d.err, (int)E_CAP_PART);
+            continue;
+        }
+        if ((int64_t)P.next_id + r >= E.idcap) {
+            atomicOr(d.err, (int)E_CAP_ID);
+            continue;
+        }
+        const int64_t i = P.base + slot;
+        const double v0 = s == 0 ? B.ve[0] : B.vi[0];
+        const double v1 = s == 0 ? B.ve[1] : B.vi[1];
+        const double v2 = s == 0 ? B.ve[2] : B.vi[2];
+        if constexpr (!F64) {
+            d.cell[b][i] = B.cell;
+            d.off[b][i] = B.off;
+            d.fvx[b][i] = (float)v0;
+            d.fvy[b][i] = (float)v1;
+            d.fvz[b][i] = (float)v2;
+        } else {
+            d.x[b][i] = B.x;
+            d.dvx[b][i] = v0;
+            d.dvy[b][i] = v1;
+            d.dvz[b][i] = v2;
+        }
+        d.id[b][i] = P.next_id + r;
+    }
+}
+
 // Places the step's births (k < M) and clears the marks of the previous step's (k < Mo): block
 // `bid` of `nblk`.  pre(i) is the births' scanned group count at group index i.
 template <bool F64, typename Pre>
@@ -1038,37 +1062,7 @@ __device__ __forceinline__ void place_births(const Dev &d, const BirthBuf &bb, c
         const int64_t g = pid / kGroupIds;
         const uint32_t r = pre(E.grp_base + g) - pre(E.grp_base) +
                            rank_in_group(bb.bitmap + E.bm_base + g * kGroupWords, pid);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            if (s >= E.nspecies) break;
-            const PlaceSeg &P = s_ps[E.seg[s]];
-            const int64_t slot = P.n_slots + r;
-            if (slot >= P.cap) {
-                atomicOr(d.err, (int)E_CAP_PART);
-                continue;
-            }
-            if ((int64_t)P.next_id + r >= E.idcap) {
-                atomicOr(d.err, (int)E_CAP_ID);
-                continue;
-            }
-            const int64_t i = P.base + slot;
-            const double v0 = s == 0 ? B.ve[0] : B.vi[0];
-            const double v1 = s == 0 ? B.ve[1] : B.vi[1];
-            const double v2 = s == 0 ? B.ve[2] : B.vi[2];
-            if constexpr (!F64) {
-                d.cell[b][i] = B.cell;
-                d.off[b][i] = B.off;
-                d.fvx[b][i] = (float)v0;
-                d.fvy[b][i] = (float)v1;
-                d.fvz[b][i] = (float)v2;
-            } else {
-                d.x[b][i] = B.x;
-                d.dvx[b][i] = v0;
-                d.dvy[b][i] = v1;
-                d.dvz[b][i] = v2;
-            }
-            d.id[b][i] = P.next_id + r;
-        }
+        put_birth<F64>(d, B, r, E, s_ps, b);
     }
 }
 
@@ -1150,6 +1144,7 @@ __global__ void __launch_bounds__(256) k_birth_place(Dev d, int deferred, int ad
 // threads (1024 at most), and the chunked solve is no slower (13 + 9 us for 20 chunks).
 // =======================================================================================
 constexpr int kSmallPlace = 4;
+constexpr int kFewBirths = 256;  // ranked by comparison (at most one per thread of the smallest block)
 
 template <bool F64, int G>
 __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nsolve, int zero_q, int births,
@@ -1165,13 +1160,24 @@ __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nso
         const int ei = (int)blockIdx.x, w = (int)threadIdx.x / kWave;
         const EnsC e = d.ens[ei];
         // the speed maxima of the ensemble's segments (a wave each), in the half the births'
-        // placement makes current; read before the ticket that lets it be cleared
+        // placement makes current: loaded beside the charge, reduced once they are in, and only
+        // then does the block take the ticket that lets them be cleared
+        unsigned long long vm[kCntStripes / kWave] = {};
+        if (params && w < e.nspecies) {
+            const unsigned long long *row = d.vmax2 + (int64_t)(births ? 1 - vc : vc) * kCntStripes * d.nseg + (w == 0 ? e.seg[0] : e.seg[1]);
+#pragma unroll
+            for (int i = 0; i < kCntStripes / kWave; ++i) vm[i] = row[(int64_t)(i * kWave + lane_id()) * d.nseg];
+        }
         double m2 = 0.0;
-        if (params && w < e.nspecies) m2 = seg_vmax2(d, w == 0 ? e.seg[0] : e.seg[1], births ? 1 - vc : vc);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (births && threadIdx.x == 0) s_last = (atomicAdd(d.ticket + 6, 1u) == gridDim.x - 1);
-        const double emax = solve_small<F64, G, true>(d, e, ei, zero_q, sh, d.Ecell + e.gbase, d.E + e.gbase);
+        const double emax = solve_small<F64, G, true>(d, e, ei, zero_q, sh, d.Ecell + e.gbase, d.E + e.gbase, [&] {
+#pragma unroll
+            for (int i = 0; i < kCntStripes / kWave; ++i) m2 = fmax(m2, __longlong_as_double((long long)vm[i]));
+            if (!births) return;
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            if (threadIdx.x == 0) s_last = (atomicAdd(d.ticket + 6, 1u) == gridDim.x - 1);
+        });
+        m2 = wave_max_f64(m2);
         if (params && w < e.nspecies && lane_id() == 0) {
             const int sg = w == 0 ? e.seg[0] : e.seg[1];
             double numax, pnull;
@@ -1182,6 +1188,7 @@ __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nso
     } else {
         __shared__ uint32_t s_pre[kStripes + 1], s_old[kStripes + 1], s_buf[16];
         __shared__ uint32_t s_gp[kGroupTile];
+        __shared__ unsigned long long s_key[kFewBirths];
         __shared__ PlaceEns s_pe[kSmallEns];
         __shared__ PlaceSeg s_ps[2 * kSmallEns];
         const int bid = (int)blockIdx.x - nsolve;
@@ -1197,7 +1204,47 @@ __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nso
             const SegC &S = d.seg[threadIdx.x];
             s_ps[threadIdx.x] = PlaceSeg{S.base, S.cap, d.n_slots[threadIdx.x], d.next_id[threadIdx.x]};
         }
-        {
+        __syncthreads();
+        const int64_t M = s_pre[kStripes], Mo = deferred ? (int64_t)s_old[kStripes] : 0;
+        if (M <= kFewBirths) {
+            // a few births are ranked against one another in LDS by the first block: the scan of
+            // the group counts and the bitmap words would be two more round trips, which were
+            // what the launch waited for (10.2 us against 7.7 at 256 cells, a dozen births)
+            if (bid == 0) {
+                for (int64_t k = threadIdx.x; k < Mo; k += blockDim.x) {
+                    int st;
+                    uint32_t idx;
+                    birth_locate(d, k, st, idx, s_old);
+                    const uint2 o = *(const uint2 *)&ob.births[(int64_t)st * d.birth_stripe_cap + idx];
+                    const PlaceEns &E = s_pe[o.y];
+                    ob.bitmap[E.bm_base + (o.x >> 5)] = 0u;
+                    ob.gcnt[E.grp_base + o.x / kGroupIds] = 0u;
+                }
+                const int k = (int)threadIdx.x;
+                Birth B{};
+                unsigned long long key = 0;
+                if (k < M) {
+                    int st;
+                    uint32_t idx;
+                    birth_locate(d, k, st, idx, s_pre);
+                    B = bb.births[(int64_t)st * d.birth_stripe_cap + idx];
+                    key = (unsigned long long)(uint32_t)B.ens << 32 | B.pid;
+                    s_key[k] = key;
+                }
+                __syncthreads();
+                if (k < M) {
+                    uint32_t r = 0;
+                    for (int i = 0; i < (int)M; ++i)
+                        r += (s_key[i] < key && (s_key[i] >> 32) == (key >> 32)) ? 1u : 0u;
+                    put_birth<F64>(d, B, r, s_pe[B.ens], s_ps, *d.cur);
+                }
+                if (k < d.nens) {
+                    uint32_t m = 0;
+                    for (int i = 0; i < (int)M; ++i) m += (int)(s_key[i] >> 32) == k ? 1u : 0u;
+                    __hip_atomic_store(d.nbens + k, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        } else {
             // exclusive scan of the tile's group counts, whole 16-byte vectors per thread
             constexpr int kVec = kGroupTile / (4 * G * kSolveThreads);
             uint4 v[kVec];
@@ -1216,16 +1263,16 @@ __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nso
                 o[3] = (ex += v[i].z);
                 ex += v[i].w;
             }
-        }
-        __syncthreads();
-        place_births<F64>(d, bb, ob, s_pre[kStripes], deferred ? (int64_t)s_old[kStripes] : 0, s_pre, s_old, s_pe,
-                          s_ps, bid, kSmallPlace, [&](int64_t i) { return s_gp[i]; });
-        // the births per ensemble, for the launch's last block (which may be another one)
-        if (bid == 0 && (int)threadIdx.x < d.nens) {
-            const PlaceEns &E = s_pe[threadIdx.x];
-            const int64_t ngrp = (E.idcap + kGroupIds - 1) / kGroupIds;
-            __hip_atomic_store(d.nbens + threadIdx.x, s_gp[E.grp_base + ngrp] - s_gp[E.grp_base], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            place_births<F64>(d, bb, ob, M, Mo, s_pre, s_old, s_pe, s_ps, bid, kSmallPlace,
+                              [&](int64_t i) { return s_gp[i]; });
+            // the births per ensemble, for the launch's last block (which may be another one)
+            if (bid == 0 && (int)threadIdx.x < d.nens) {
+                const PlaceEns &E = s_pe[threadIdx.x];
+                const int64_t ngrp = (E.idcap + kGroupIds - 1) / kGroupIds;
+                __hip_atomic_store(d.nbens + threadIdx.x, s_gp[E.grp_base + ngrp] - s_gp[E.grp_base], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
     }
     if (!births) {

@@ -184,12 +184,10 @@ struct TileTally {
 template <bool CXREL>
 __device__ __forceinline__ void tile_collide(const Dev &d, const SegC &S, const EnsC &e, int sg, int buf, uint32_t nc,
                                              const uint4 *s_rec, const uint4 *g_rec, bool depo, bool hist, int st,
-                                             const TileTally &tl)
+                                             uint32_t tag, int half, double numax, double pnull, const TileTally &tl)
 {
     __shared__ uint32_t s_nb, s_bbase;
-    const uint32_t tag = (uint32_t)(*d.step);
-    const int half = 1 - *d.vcur, bst = (int)(blockIdx.x & (kStripes - 1));
-    const double numax = d.numax[sg], pnull = d.pnull[sg];
+    const int bst = (int)(blockIdx.x & (kStripes - 1));
     const int oth = S.other;
     const BirthBuf bb = birth_buf(d, (int)(tag & 1u));
     for (uint32_t q0 = 0; q0 < nc; q0 += 256) {
@@ -374,13 +372,16 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
 #pragma unroll
         for (int k = 0; k < PPT; ++k) ec[k] = Ecs[cell[k] < 0 ? 0u : (uint32_t)cell[k]];
     }
+    // (read before any store, so that a collision below waits for none of them again)
+    const uint32_t tag = COLL ? (uint32_t)(*d.step) : 0u;
+    const double pnull_in = COLL ? d.pnull[sg] : 0.0, numax_in = INL != INL_NO ? d.numax[sg] : 0.0;
+    const int half_in = INL != INL_NO ? 1 - *d.vcur : 0;
     uint32_t rmask = 0;  // bit k: particle k's first Philox word passes R1 < P_null
     if (COLL) {
         // Reading R12 decision R1 < P_null, taken exactly as the integer test
         // (r >> 9) < ceil(P_null 2^23 - 1/2) on the first Philox word of block 0.
-        const double X = d.pnull[sg] * 8388608.0 - 0.5;
+        const double X = pnull_in * 8388608.0 - 0.5;
         const uint32_t thr = X <= 0.0 ? 0u : (X >= 8388608.0 ? 8388608u : (uint32_t)ceil(X));
-        const uint32_t tag = (uint32_t)(*d.step);
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
             const uint4 w = philox(id[k], tag, 0u, 0u, S.seed, (uint32_t)s);
@@ -687,7 +688,8 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
     __syncthreads();
     if constexpr (INL != INL_NO)
         tile_collide<INL == INL_CXREL>(d, S, e, sg, SORT ? 1 - b : b, s_nc, s_rec, d.crec + 2 * first,
-                                       (hist_rt & kNoDepo) == 0, hist, st, TileTally{s_c, &s_kes, &s_nal, &s_v2});
+                                       (hist_rt & kNoDepo) == 0, hist, st, tag, half_in, numax_in, pnull_in,
+                                       TileTally{s_c, &s_kes, &s_nal, &s_v2});
     if (WIN) {
         const int nn = G.periodic ? G.ncells : G.ncells + 1;
         unsigned long long *Q = d.Qi + (int64_t)s * d.nodes_tot + G.gbase;

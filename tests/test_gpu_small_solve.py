@@ -94,3 +94,42 @@ def test_small_solve_fp64(pic, N):
         assert rel(g[k], r[k]) <= 1e-9, k
     assert sim.diag()["step"] == 22
     sim.close()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n_ens", [1, 3])
+def test_births_on_either_side_of_the_ranking_line(pic, precision, n_ens):
+    """Up to 256 births of a step are ranked by comparison, more through the group counts and the
+    bitmap: runs whose steps make from none to several thousand, against the chunked path."""
+    per_step = []
+    for rate in (0.0, 0.002, 0.02, 0.06, 0.1, 0.3, 3.0):
+        ens = []
+        for k in range(9):
+            e = synth.ensemble(900 + 50 * k if k < n_ens else 3, 60, collisions=True, seed=1 + k, sort_every=5,
+                               extra=200_000)
+            e["ngs_iz"] = rate
+            ens.append(e)
+        a, b = (pic.Sim(work_of(x, precision), fused=precision == "fp32") for x in (ens[:n_ens], ens))
+        last = 0
+        for _ in range(4):
+            a.step(1), b.step(1)
+            made = sum(a.diag(k)["created"][0] for k in range(n_ens))
+            per_step.append(made - last)
+            last = made
+        for x in (a, b):
+            x.step(7)
+        for k in range(n_ens):
+            da, db = a.diag(k), b.diag(k)
+            for q in ("count", "coll", "created", "step"):
+                assert da[q] == db[q], (rate, k, q)
+            for s in range(2):
+                sa, sb = by_id(a.particles(k, s)), by_id(b.particles(k, s))
+                assert np.array_equal(sa["id"], sb["id"])
+                for q in ("x", "vx", "vy", "vz"):
+                    if precision == "fp32":
+                        assert np.array_equal(sa[q], sb[q]), (rate, k, s, q)
+                    else:  # the FP64 deposit's atomics reorder sums
+                        assert np.max(np.abs(sa[q] - sb[q])) <= 1e-9 * np.max(np.abs(sb[q])), (rate, k, s, q)
+        a.close(), b.close()
+    per_step.sort()
+    assert per_step[0] == 0 and any(0 < m <= 256 for m in per_step) and per_step[-1] > 512
