@@ -27,8 +27,8 @@ namespace pic {
 // takes its particles, so the solve costs neither a launch nor a round trip.  The charge and
 // the field adjoint that one step adds up are read by the next from another buffer, while the
 // third of the three is cleared.  On the 2048-cell, 409,600-particle window a forward step took
-// 10.8 + 6.4 us in the run's two kernels (and three copies where it is recorded) and takes 11.3, a
-// reverse step 17.8 + 13.3 + 5.7 us in the three kernels of larger grids and takes 12.0.
+// 10.8 + 6.4 us in the run's two kernels (and three copies where it is recorded) and takes 9.6, a
+// reverse step 17.8 + 13.3 + 5.7 us in the three kernels of larger grids and takes 10.5.
 // =======================================================================================
 template <int G>
 struct AdjTile {
@@ -36,7 +36,7 @@ struct AdjTile {
 };
 
 // Inclusive scan and sum of one double per thread over the whole block (16 waves at most); the
-// sum in every thread.
+// sum in every thread.  s_w holds 16 doubles, used once.
 __device__ __forceinline__ double tile_scan(double v, double *s_w, double &total)
 {
     const int w = threadIdx.x / kWave, nw = blockDim.x / kWave;
@@ -44,11 +44,12 @@ __device__ __forceinline__ double tile_scan(double v, double *s_w, double &total
     if (lane_id() == kWave - 1) s_w[w] = v;
     __syncthreads();
     double add = 0.0, tot = 0.0;
-    for (int i = 0; i < nw; ++i) {
-        if (i < w) add += s_w[i];
-        tot += s_w[i];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const double t = i < nw ? s_w[i] : 0.0;
+        if (i < w) add += t;
+        tot += t;
     }
-    __syncthreads();
     total = tot;
     return v + add;
 }
@@ -59,8 +60,8 @@ __device__ __forceinline__ double tile_sum(double v, double *s_w)
     if (lane_id() == 0) s_w[w] = v;
     __syncthreads();
     double tot = 0.0;
-    for (int i = 0; i < nw; ++i) tot += s_w[i];
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tot += i < nw ? s_w[i] : 0.0;
     return tot;
 }
 
@@ -195,8 +196,9 @@ __global__ void __launch_bounds__(AdjTile<G>::kThreads) k_adj_fwd(Dev d, AdjStat
 }
 
 // One step of the reverse sweep.  From the field adjoint lEin of the step above (with `seed`, of
-// the objective: eps0 dx E) the block takes lQ = (q w / dx) S D lE (see k_adj_grid), adds its
-// gather at the positions of the step above (xc1) to lx, then the push and gather adjoint at
+// the objective: eps0 dx E) the block takes the slope g of lQ = (q w / dx) S D lE (see
+// k_adj_grid: lQ_{j+1} - lQ_j is -q w (E_{1/2} + (dx/eps0) C_j), the mean and the second sum cancel,
+// so one scan and one sum are all it needs), adds it at the positions of the step above (xc1) to lx, then the push and gather adjoint at
 // this step's positions (xc, xo) and field E: lv += dt lx, la = dt (q/m) lv,
 // lx += la (E_{j+1} - E_j) / dx, and the scatter of la into lEout (cleared before); lEzero is
 // cleared.  Dead slots (a run the push flagged non-finite) are skipped.
@@ -207,8 +209,8 @@ __global__ void __launch_bounds__(AdjTile<G>::kThreads)
               double *lEext, int64_t n, double dt, double qm, int N)
 {
     constexpr int TH = AdjTile<G>::kThreads, PPT = AdjTile<G>::kPpt, NPT = kNodesPerThread;
-    __shared__ double s_lQ[G * kChunk], s_E[G * kChunk], s_acc[G * kChunk];
-    __shared__ double s_w[16];
+    __shared__ double s_g[G * kChunk], s_dE[G * kChunk], s_acc[G * kChunk];
+    __shared__ double s_w[3][16];
     const int tid = threadIdx.x;
     const int64_t i0 = ((int64_t)blockIdx.x * TH + tid) * PPT;
     // the particle loads are in flight during the solve
@@ -254,56 +256,47 @@ __global__ void __launch_bounds__(AdjTile<G>::kThreads)
             sum += r[q];
         }
     }
+    {
+        double x[NPT + 1];
 #pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-        const int j = j0 + q;
-        if (j < N) {
-            s_E[j] = E[j];
-            s_acc[j] = 0.0;
+        for (int q = 0; q < NPT + 1; ++q) x[q] = E[j0 + q < N ? j0 + q : 0];  // (E_N is E_0)
+#pragma unroll
+        for (int q = 0; q < NPT; ++q) {
+            if (j0 + q >= N) continue;
+            s_dE[j0 + q] = (x[q + 1] - x[q]) / dx;
+            s_acc[j0 + q] = 0.0;
         }
     }
-    const double mean_r = tile_sum(sum, s_w) / (double)N;
-    double C[NPT], tot, loc = 0.0;
+    // C_j = sum_{i=1..j} (r_i - mean r): the scan of r gives the mean too
+    if (tid == 0) sum -= r[0];
+    double tot;
+    double R = tile_scan(sum, s_w[0], tot) - sum;
+    const double mean_r = (tot + (0.5 * f * (lEin[N > 1 ? 1 : 0] - lEin[N - 1])) / dx) / (double)N;
+    double C[NPT], cs = 0.0;
 #pragma unroll
     for (int q = 0; q < NPT; ++q) {
         const int j = j0 + q;
-        if (j >= 1 && j < N) loc += r[q] - mean_r;
-        C[q] = loc;
+        if (j >= 1) R += r[q];
+        C[q] = R - (double)j * mean_r;
+        if (j < N) cs += C[q];
     }
-    const double cex = tile_scan(loc, s_w, tot) - loc;
-    double cs = 0.0;
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-        C[q] += cex;
-        if (j0 + q < N) cs += C[q];
-    }
-    double F = tile_scan(cs, s_w, tot) - cs;
-    const double ce = dx / eps0, Eh = -ce * tot / (double)N;
-    double phi[NPT], ps = 0.0;
-#pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-        const int j = j0 + q;
-        phi[q] = -dx * ((double)j * Eh + ce * F);
-        F += C[q];
-        if (j < N) ps += phi[q];
-    }
-    const double mphi = tile_sum(ps, s_w) / (double)N;
+    const double ce = dx / eps0, Eh = -ce * tile_sum(cs, s_w[1]) / (double)N;
 #pragma unroll
     for (int q = 0; q < NPT; ++q)
-        if (j0 + q < N) s_lQ[j0 + q] = (qw / dx) * (phi[q] - mphi);
+        if (j0 + q < N) s_g[j0 + q] = -(qw / dx) * (Eh + ce * C[q]);
     __syncthreads();
     double ext = 0.0, r0 = 0.0, r1 = 0.0;
     int rk = -1;
     auto next = [&](int j) { return j + 1 == N ? 0 : j + 1; };
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        if (c1[k] >= 0) px[k] += (s_lQ[next(c1[k])] - s_lQ[c1[k]]) / dx;
+        if (c1[k] >= 0) px[k] += s_g[c1[k]];
         if (c0[k] < 0) continue;
         const int j = c0[k];
         const double fo = (double)o0[k];
         pv[k] += dt * px[k];
         const double la = dt * qm * pv[k];
-        px[k] += la * (s_E[next(j)] - s_E[j]) / dx;
+        px[k] += la * s_dE[j];
         ext += la;
         if (j != rk) {
             if (rk >= 0) {
@@ -334,7 +327,7 @@ __global__ void __launch_bounds__(AdjTile<G>::kThreads)
                 lv[i0 + k] = pv[k];
             }
     }
-    ext = tile_sum(ext, s_w);  // (its barriers complete the scatter)
+    ext = tile_sum(ext, s_w[2]);  // (its barriers complete the scatter)
     if (tid == 0) unsafeAtomicAdd(lEext, ext);
     for (int j = tid; j < N; j += TH) {
         const double v = s_acc[j];
@@ -569,6 +562,40 @@ __global__ void k_adj_by_id(const double *lv, const uint32_t *id, double *out, i
         else
             atomicOr(err, 1);
     }
+}
+
+// The same, counting the distinct ids in *distinct through a bit per id (cleared before).
+__global__ void __launch_bounds__(256) k_adj_by_id_count(const double *lv, const uint32_t *id, double *out,
+                                                         uint32_t *seen, int64_t n, int64_t len, int32_t *err,
+                                                         uint32_t *distinct)
+{
+    __shared__ uint32_t s_n;
+    if (threadIdx.x == 0) s_n = 0u;
+    __syncthreads();
+    uint32_t mine = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t k = id[i];
+        if ((int64_t)k < len) {
+            out[k] = lv[i];
+            const uint32_t bit = 1u << (k & 31);
+            mine += (atomicOr(seen + (k >> 5), bit) & bit) ? 0u : 1u;
+        } else {
+            atomicOr(err, 1);
+        }
+    }
+    mine = wave_sum_u32(mine);
+    if (lane_id() == 0 && mine) atomicAdd(&s_n, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_n) atomicAdd(distinct, s_n);
+}
+
+hipError_t launch_adj_by_id_count(const double *lv, const uint32_t *id, double *out, uint32_t *seen, int64_t n,
+                                  int64_t len, int32_t *err, uint32_t *distinct, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    const int64_t G = std::min<int64_t>((n + 255) / 256, 2048);
+    hipLaunchKernelGGL(k_adj_by_id_count, dim3((unsigned)G), dim3(256), 0, s, lv, id, out, seen, n, len, err, distinct);
+    return hipGetLastError();
 }
 
 hipError_t launch_adj_by_id(const double *lv, const uint32_t *id, double *out, int64_t n, int64_t len,

@@ -1616,17 +1616,40 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
         if (badh) return fail(c, PIC_EINVAL, "particle id beyond dW_dvx");
         HIPC(c, hipMemcpyAsync(dW_dvx, gid, (size_t)dvx_len * 8, hipMemcpyDeviceToHost, s));
         HIPC(c, hipStreamSynchronize(s));
-    } else {
-        std::vector<double> glv(nslots);
-        std::vector<uint32_t> ids(nslots);
-        HIPC(c, hipMemcpyAsync(glv.data(), lv, nslots * 8, hipMemcpyDeviceToHost, s));
-        HIPC(c, hipMemcpyAsync(ids.data(), d.id[b], nslots * 4, hipMemcpyDeviceToHost, s));
+        *W = fe;
+        *dW_dEext = gext;
+        return check_err(c, s);
+    }
+    // As many slots as entries: if their ids are distinct every entry is written, so the gradient
+    // is put in order on the device, in the room of the checkpoints, and copied straight to the
+    // caller (its slots, its ids and a loop over both on the host took 0.6 of 6.9 ms).
+    double *byid = (double *)(base + A.off_ck_cell);
+    uint32_t *seen = (uint32_t *)(byid + dvx_len);
+    if (nslots == dvx_len && (char *)(seen + dvx_len / 32 + 1) <= base + A.off_xc) {
+        uint32_t *fl = (uint32_t *)lext + 2, flags[2] = {0u, 0u};  // (lext has 64 bytes)
+        HIPC(c, hipMemsetAsync(seen, 0, (size_t)(dvx_len / 32 + 1) * 4, s));
+        HIPC(c, hipMemsetAsync(fl, 0, 8, s));
+        HIPC(c, launch_adj_by_id_count(lv, d.id[b], byid, seen, nslots, dvx_len, (int32_t *)fl, fl + 1, s));
+        HIPC(c, hipMemcpyAsync(flags, fl, 8, hipMemcpyDeviceToHost, s));
         HIPC(c, hipMemcpyAsync(&gext, lext, 8, hipMemcpyDeviceToHost, s));
         HIPC(c, hipStreamSynchronize(s));
-        for (int64_t i = 0; i < nslots; ++i) {
-            if ((int64_t)ids[i] >= dvx_len) return fail(c, PIC_EINVAL, "particle id beyond dW_dvx");
-            dW_dvx[ids[i]] = glv[i];
+        if (flags[0]) return fail(c, PIC_EINVAL, "particle id beyond dW_dvx");
+        if ((int64_t)flags[1] == nslots) {
+            HIPC(c, hipMemcpyAsync(dW_dvx, byid, (size_t)dvx_len * 8, hipMemcpyDeviceToHost, s));
+            *W = fe;
+            *dW_dEext = gext;
+            return check_err(c, s);
         }
+    }
+    std::vector<double> glv(nslots);
+    std::vector<uint32_t> ids(nslots);
+    HIPC(c, hipMemcpyAsync(glv.data(), lv, nslots * 8, hipMemcpyDeviceToHost, s));
+    HIPC(c, hipMemcpyAsync(ids.data(), d.id[b], nslots * 4, hipMemcpyDeviceToHost, s));
+    HIPC(c, hipMemcpyAsync(&gext, lext, 8, hipMemcpyDeviceToHost, s));
+    HIPC(c, hipStreamSynchronize(s));
+    for (int64_t i = 0; i < nslots; ++i) {
+        if ((int64_t)ids[i] >= dvx_len) return fail(c, PIC_EINVAL, "particle id beyond dW_dvx");
+        dW_dvx[ids[i]] = glv[i];
     }
     *W = fe;
     *dW_dEext = gext;

@@ -89,6 +89,9 @@ hipError_t launch_adj_b(const int32_t *xc, const double *lQ, double *lx, int64_t
 // out[id_i] = lv_i for n slots; ids >= len set *err (device int).
 hipError_t launch_adj_by_id(const double *lv, const uint32_t *id, double *out, int64_t n, int64_t len,
                             int32_t *err, hipStream_t s);
+// The same, with the number of distinct ids in *distinct; `seen` is a cleared bit per id.
+hipError_t launch_adj_by_id_count(const double *lv, const uint32_t *id, double *out, uint32_t *seen, int64_t n,
+                                  int64_t len, int32_t *err, uint32_t *distinct, hipStream_t s);
 hipError_t launch_diag(const Dev &d, bool f64, int sg, double *out, int grid, hipStream_t s);
 // The scalars of ensemble `en` into one record and its node arrays ([Q0, Q1, rho, phi, E][nn]
 // doubles) into one run of device memory; the error flags alone.  `out` of the records is host
