@@ -30,7 +30,7 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kCompactEvery = 20;  // sort cadence used for compaction when K = 0
-constexpr int kDiagGrid = 256;
+constexpr int kDiagGrid = 1024;
 
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }

@@ -46,7 +46,6 @@ hipError_t launch_solve(const Dev &d, bool f64, int64_t nchunks, bool zero_q, hi
 bool births_fit_solve(const Dev &d);
 hipError_t launch_field_stats(const Dev &d, bool f64, int64_t nchunks, hipStream_t s);
 hipError_t launch_params(const Dev &d, hipStream_t s);
-hipError_t launch_scan(uint32_t *in, uint32_t *out, int64_t n, uint32_t *part, bool zero_in, hipStream_t s);
 int64_t scan_blocks(int64_t n);
 hipError_t launch_births(const Dev &d, bool f64, bool in_step, bool advance, hipStream_t s);
 hipError_t launch_advance(const Dev &d, hipStream_t s);

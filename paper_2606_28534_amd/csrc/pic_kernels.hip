@@ -244,7 +244,7 @@ __host__ __forceinline__ int place_blocks(const Dev &d)
 // blocks of the two solve kernels (defined with the births below).
 __device__ void group_tile_scan_body(const Dev &d, int t);
 template <bool F64>
-__device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk);
+__device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk, uint32_t *s_gp = nullptr);
 
 // For the null-collision bound (R11) that the second solve kernel's last block computes: the
 // largest |v|^2 of each segment over the stripes of the half the bound uses, one wave per
@@ -745,7 +745,8 @@ __global__ void k_zero_q(Dev d)
 }
 
 // =======================================================================================
-// Generic exclusive scan of u32 (three kernels: block sums, scan of sums, down-sweep).
+// Generic exclusive scan of u32 (tile sums, down-sweep; a scan of the sums in between when they
+// are many).
 // =======================================================================================
 constexpr int kScanTile = kScanBlock * kScanItems;
 
@@ -800,6 +801,9 @@ __global__ void __launch_bounds__(1024) k_scan_part(uint32_t *part, int64_t nb)
     }
 }
 
+// With OWN each block adds up the tiles before its own from the tile sums (part unscanned);
+// otherwise part holds their scan.
+template <bool OWN>
 __global__ void __launch_bounds__(kScanBlock) k_scan_down(uint32_t *in, uint32_t *out, int64_t n,
                                                           const uint32_t *part, int zero_in,
                                                           const int64_t *parity_step)
@@ -810,14 +814,21 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_down(uint32_t *in, uint32_t
     // each thread owns kScanItems consecutive elements
     const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
     uint32_t v[kScanItems];
-    uint32_t s = 0;
+    uint32_t s = 0, before = 0;
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         v[q] = (i0 + q < n) ? in[i0 + q] : 0u;
         s += v[q];
     }
     uint32_t tot;
-    uint32_t ex = block_excl_scan_u32(s, s_buf, tot) + part[blockIdx.x];
+    if constexpr (OWN) {
+        uint32_t mine = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kScanBlock) mine += part[i];
+        block_excl_scan_u32(mine, s_buf, before);
+    } else {
+        before = part[blockIdx.x];
+    }
+    uint32_t ex = block_excl_scan_u32(s, s_buf, tot) + before;
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         if (i0 + q < n) {
@@ -826,6 +837,59 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_down(uint32_t *in, uint32_t
         }
         ex += v[q];
     }
+}
+
+// The sort's scan of a small run's cell counts into run cursors, and the segments' first
+// positions, by one block: a thread owns kScanItems consecutive cells of every 16384 (its loads
+// whole 16-byte vectors), the running total carried between rounds.  4096 cells take 3.7 us
+// and 20014 take 10.5, where the scan's three kernels and k_segstart took 18 and 23; 40022 would
+// take 18.5, more than the two kernels of the general scan and k_segstart.
+constexpr int kOneThreads = 1024;
+constexpr int64_t kOneScanMax = 2 * kOneThreads * kScanItems;
+__global__ void __launch_bounds__(kOneThreads) k_sort_scan(Dev d)
+{
+    __shared__ uint32_t s_buf[16];
+    const int64_t n = d.cells_tot;
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < n; base += kOneThreads * kScanItems) {
+        const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
+        uint32_t v[kScanItems], s = 0, tot;
+        const bool full = i0 + kScanItems <= n;
+        if (full) {
+#pragma unroll
+            for (int q = 0; q < kScanItems; q += 4) *(uint4 *)(v + q) = *(const uint4 *)(d.cellcnt + i0 + q);
+        } else {
+#pragma unroll
+            for (int q = 0; q < kScanItems; ++q) v[q] = i0 + q < n ? d.cellcnt[i0 + q] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) s += v[q];
+        uint32_t ex = block_excl_scan_u32(s, s_buf, tot) + carry;
+        carry += tot;
+#pragma unroll
+        for (int q = 0; q < kScanItems; ++q) {
+            const uint32_t c = v[q];
+            v[q] = ex;
+            ex += c;
+        }
+        if (full) {
+#pragma unroll
+            for (int q = 0; q < kScanItems; q += 4) {
+                *(uint4 *)(d.cursor + i0 + q) = *(const uint4 *)(v + q);
+                *(uint4 *)(d.cellcnt + i0 + q) = make_uint4(0u, 0u, 0u, 0u);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < kScanItems; ++q)
+                if (i0 + q < n) {
+                    d.cursor[i0 + q] = v[q];
+                    d.cellcnt[i0 + q] = 0u;
+                }
+        }
+    }
+    __threadfence_block();
+    __syncthreads();  // the cursors are written
+    for (int sg = threadIdx.x; sg < d.nseg; sg += kOneThreads) d.segstart[sg] = d.cursor[d.seg[sg].cbase];
 }
 
 // =======================================================================================
@@ -991,6 +1055,31 @@ __device__ __forceinline__ void place_reset(const Dev &d, int deferred, const Bi
         d.ssum[(int64_t)vc * kCntStripes * d.nseg * T_NSTEP + i] = 0.0;
 }
 
+// Exclusive scan of one tile of group counts into LDS by a block of T threads (whole 16-byte
+// vectors per thread); a barrier must follow.
+template <int T>
+__device__ __forceinline__ void scan_group_tile(const uint32_t *gcnt, uint32_t *s_gp)
+{
+    __shared__ uint32_t s_buf[16];
+    constexpr int kVec = kGroupTile / (4 * T);
+    uint4 v[kVec];
+    uint32_t sum = 0, tot;
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) v[i] = ((const uint4 *)gcnt)[threadIdx.x * kVec + i];
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) sum += v[i].x + v[i].y + v[i].z + v[i].w;
+    uint32_t ex = block_excl_scan_u32(sum, s_buf, tot);
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) {
+        uint32_t *o = s_gp + (threadIdx.x * kVec + i) * 4;
+        o[0] = ex;
+        o[1] = (ex += v[i].x);
+        o[2] = (ex += v[i].y);
+        o[3] = (ex += v[i].z);
+        ex += v[i].w;
+    }
+}
+
 // The pair of one birth, r-th of its ensemble's in the step, to its slots.
 template <bool F64>
 __device__ __forceinline__ void put_birth(const Dev &d, const Birth &B, uint32_t r, const PlaceEns &E,
@@ -1067,7 +1156,7 @@ __device__ __forceinline__ void place_births(const Dev &d, const BirthBuf &bb, c
 }
 
 template <bool F64>
-__device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk)
+__device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk, uint32_t *s_gp)
 {
     __shared__ uint32_t s_pre[kStripes + 1];
     __shared__ uint32_t s_old[kStripes + 1];
@@ -1091,11 +1180,15 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
         const SegC &S = d.seg[sg];
         s_ps[sg] = PlaceSeg{S.base, S.cap, d.n_slots[sg], d.next_id[sg]};
     }
-    stage_tile_bases(d, s_tb);
+    // (with s_gp the block scans the one tile of group counts itself)
+    if (s_gp)
+        scan_group_tile<256>(bb.gcnt, s_gp);
+    else
+        stage_tile_bases(d, s_tb);
     __syncthreads();
     const int64_t M = s_pre[kStripes], Mo = deferred ? (int64_t)s_old[kStripes] : 0;
     place_births<F64>(d, bb, ob, M, Mo, s_pre, s_old, s_pe, s_ps, bid, nblk,
-                      [&](int64_t i) { return group_prefix(d, s_tb, i); });
+                      [&](int64_t i) { return s_gp ? s_gp[i] : group_prefix(d, s_tb, i); });
     // The last block only updates counters that no block of this launch reads after taking
     // its ticket (each block staged them before its first barrier), and the next kernel
     // sees every write, so no device-scope fence is needed here; on gfx950 such a fence
@@ -1107,7 +1200,8 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
     for (int en = threadIdx.x; en < d.nens; en += blockDim.x) {
         const PlaceEns &E = s_pe[en];
         const int64_t ngrp = (E.idcap + kGroupIds - 1) / kGroupIds;
-        const uint32_t m = group_prefix(d, s_tb, E.grp_base + ngrp) - group_prefix(d, s_tb, E.grp_base);
+        const uint32_t m = s_gp ? s_gp[E.grp_base + ngrp] - s_gp[E.grp_base]
+                                : group_prefix(d, s_tb, E.grp_base + ngrp) - group_prefix(d, s_tb, E.grp_base);
         for (int s = 0; s < E.nspecies; ++s) {
             const int sg = E.seg[s];
             const PlaceSeg &P = s_ps[sg];
@@ -1124,10 +1218,13 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
     if (threadIdx.x == 0 && advance) *d.step = step + 1;
 }
 
-template <bool F64>
+// With OWN (one tile of birth groups) every block scans the group counts for itself, which saves
+// k_group_scan in front of it: 4.8 + 10.9 us in two launches, 11.9 in one.
+template <bool F64, bool OWN>
 __global__ void __launch_bounds__(256) k_birth_place(Dev d, int deferred, int advance)
 {
-    birth_place_body<F64>(d, deferred, advance, (int)blockIdx.x, (int)gridDim.x);
+    __shared__ uint32_t s_gp[OWN ? kGroupTile : 1];
+    birth_place_body<F64>(d, deferred, advance, (int)blockIdx.x, (int)gridDim.x, OWN ? s_gp : nullptr);
 }
 
 // =======================================================================================
@@ -1186,7 +1283,7 @@ __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nso
             d.pnull[sg] = pnull;
         }
     } else {
-        __shared__ uint32_t s_pre[kStripes + 1], s_old[kStripes + 1], s_buf[16];
+        __shared__ uint32_t s_pre[kStripes + 1], s_old[kStripes + 1];
         __shared__ uint32_t s_gp[kGroupTile];
         __shared__ unsigned long long s_key[kFewBirths];
         __shared__ PlaceEns s_pe[kSmallEns];
@@ -1245,24 +1342,7 @@ __global__ void __launch_bounds__(G *kSolveThreads) k_solve_small(Dev d, int nso
                 }
             }
         } else {
-            // exclusive scan of the tile's group counts, whole 16-byte vectors per thread
-            constexpr int kVec = kGroupTile / (4 * G * kSolveThreads);
-            uint4 v[kVec];
-            uint32_t sum = 0, tot;
-#pragma unroll
-            for (int i = 0; i < kVec; ++i) v[i] = ((const uint4 *)bb.gcnt)[threadIdx.x * kVec + i];
-#pragma unroll
-            for (int i = 0; i < kVec; ++i) sum += v[i].x + v[i].y + v[i].z + v[i].w;
-            uint32_t ex = block_excl_scan_u32(sum, s_buf, tot);
-#pragma unroll
-            for (int i = 0; i < kVec; ++i) {
-                uint32_t *o = s_gp + (threadIdx.x * kVec + i) * 4;
-                o[0] = ex;
-                o[1] = (ex += v[i].x);
-                o[2] = (ex += v[i].y);
-                o[3] = (ex += v[i].z);
-                ex += v[i].w;
-            }
+            scan_group_tile<G * kSolveThreads>(bb.gcnt, s_gp);
             __syncthreads();
             place_births<F64>(d, bb, ob, M, Mo, s_pre, s_old, s_pe, s_ps, bid, kSmallPlace,
                               [&](int64_t i) { return s_gp[i]; });
@@ -1749,22 +1829,24 @@ hipError_t launch_params(const Dev &d, hipStream_t s)
     return hipSuccess;
 }
 
-static hipError_t launch_scan_sel(uint32_t *in, uint32_t *out, int64_t n, uint32_t *part, bool zero_in,
-                                  const int64_t *parity_step, hipStream_t s)
+// Tile sums, then every tile's scan: on up to kOwnTiles tiles each block adds up the sums before
+// its own, beyond them one block scans the sums in between.
+constexpr int64_t kOwnTiles = 2048;
+static hipError_t launch_scan(uint32_t *in, uint32_t *out, int64_t n, uint32_t *part, bool zero_in,
+                              const int64_t *parity_step, hipStream_t s)
 {
     const int64_t nb = (n + kScanTile - 1) / kScanTile;
     if (nb <= 0) return hipSuccess;
+    const int zi = zero_in ? 1 : 0;
     hipLaunchKernelGGL(k_scan_sums, dim3(nb), dim3(kScanBlock), 0, s, in, n, part, parity_step);
-    hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(1024), 0, s, part, nb);
-    hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kScanBlock), 0, s, in, out, n, part, zero_in ? 1 : 0,
-                       parity_step);
+    if (nb <= kOwnTiles) {
+        hipLaunchKernelGGL(k_scan_down<true>, dim3(nb), dim3(kScanBlock), 0, s, in, out, n, part, zi, parity_step);
+    } else {
+        hipLaunchKernelGGL(k_scan_part, dim3(1), dim3(1024), 0, s, part, nb);
+        hipLaunchKernelGGL(k_scan_down<false>, dim3(nb), dim3(kScanBlock), 0, s, in, out, n, part, zi, parity_step);
+    }
     LAUNCH_CHECK();
     return hipSuccess;
-}
-
-hipError_t launch_scan(uint32_t *in, uint32_t *out, int64_t n, uint32_t *part, bool zero_in, hipStream_t s)
-{
-    return launch_scan_sel(in, out, n, part, zero_in, nullptr, s);
 }
 
 int64_t scan_blocks(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
@@ -1779,19 +1861,27 @@ hipError_t launch_births(const Dev &d, bool f64, bool in_step, bool advance, hip
         if (!in_step) hipLaunchKernelGGL(k_birth_clear, dim3(64), dim3(256), 0, s, d, -1);
         return hipGetLastError();
     }
-    // the group-count scan: one block per tile up to kMaxGroupTiles tiles, the global
-    // three-kernel scan above that
-    if (d.ngt > 0) {
-        hipLaunchKernelGGL(k_group_scan, dim3(d.ngt), dim3(256), 0, s, d);
-        LAUNCH_CHECK();
-    } else if ((e = launch_scan_sel(d.gcnt, d.gpre, d.g_tot, d.scanpart, false, d.step, s)) != hipSuccess) {
-        return e;
-    }
     const int deferred = in_step ? 1 : 0, adv = advance ? 1 : 0;
-    if (f64)
-        hipLaunchKernelGGL(k_birth_place<true>, dim3(place_blocks(d)), dim3(256), 0, s, d, deferred, adv);
-    else
-        hipLaunchKernelGGL(k_birth_place<false>, dim3(place_blocks(d)), dim3(256), 0, s, d, deferred, adv);
+    const dim3 g(place_blocks(d));
+    if (d.ngt == 1) {
+        if (f64)
+            hipLaunchKernelGGL((k_birth_place<true, true>), g, dim3(256), 0, s, d, deferred, adv);
+        else
+            hipLaunchKernelGGL((k_birth_place<false, true>), g, dim3(256), 0, s, d, deferred, adv);
+    } else {
+        // the group-count scan: one block per tile up to kMaxGroupTiles tiles, the global
+        // scan above that
+        if (d.ngt > 0) {
+            hipLaunchKernelGGL(k_group_scan, dim3(d.ngt), dim3(256), 0, s, d);
+            LAUNCH_CHECK();
+        } else if ((e = launch_scan(d.gcnt, d.gpre, d.g_tot, d.scanpart, false, d.step, s)) != hipSuccess) {
+            return e;
+        }
+        if (f64)
+            hipLaunchKernelGGL((k_birth_place<true, false>), g, dim3(256), 0, s, d, deferred, adv);
+        else
+            hipLaunchKernelGGL((k_birth_place<false, false>), g, dim3(256), 0, s, d, deferred, adv);
+    }
     LAUNCH_CHECK();
     if (!in_step) {
         hipLaunchKernelGGL(k_birth_clear, dim3(64), dim3(256), 0, s, d, -1);
@@ -1817,7 +1907,11 @@ hipError_t launch_advance(const Dev &d, hipStream_t s)
 
 hipError_t launch_sort_prepare(const Dev &d, hipStream_t s)
 {
-    hipError_t e = launch_scan(d.cellcnt, d.cursor, d.cells_tot, d.scanpart, true, s);
+    if (d.cells_tot <= kOneScanMax) {
+        hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(kOneThreads), 0, s, d);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_scan(d.cellcnt, d.cursor, d.cells_tot, d.scanpart, true, nullptr, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_segstart, dim3(1), dim3(256), 0, s, d);
     return hipGetLastError();
