@@ -243,7 +243,7 @@ __host__ __forceinline__ int place_blocks(const Dev &d)
 // Birth ranking and placement, callable by a block of a kernel of their own or by extra
 // blocks of the two solve kernels (defined with the births below).
 __device__ void group_tile_scan_body(const Dev &d, int t);
-template <bool F64>
+template <bool F64, bool OWN = false>
 __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk, uint32_t *s_gp = nullptr);
 
 // For the null-collision bound (R11) that the second solve kernel's last block computes: the
@@ -1155,7 +1155,7 @@ __device__ __forceinline__ void place_births(const Dev &d, const BirthBuf &bb, c
     }
 }
 
-template <bool F64>
+template <bool F64, bool OWN>
 __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bid, int nblk, uint32_t *s_gp)
 {
     __shared__ uint32_t s_pre[kStripes + 1];
@@ -1180,15 +1180,20 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
         const SegC &S = d.seg[sg];
         s_ps[sg] = PlaceSeg{S.base, S.cap, d.n_slots[sg], d.next_id[sg]};
     }
-    // (with s_gp the block scans the one tile of group counts itself)
-    if (s_gp)
+    // (with OWN the block scans the one tile of group counts into s_gp itself)
+    if constexpr (OWN)
         scan_group_tile<256>(bb.gcnt, s_gp);
     else
         stage_tile_bases(d, s_tb);
     __syncthreads();
     const int64_t M = s_pre[kStripes], Mo = deferred ? (int64_t)s_old[kStripes] : 0;
     place_births<F64>(d, bb, ob, M, Mo, s_pre, s_old, s_pe, s_ps, bid, nblk,
-                      [&](int64_t i) { return s_gp ? s_gp[i] : group_prefix(d, s_tb, i); });
+                      [&](int64_t i) {
+                          if constexpr (OWN)
+                              return s_gp[i];
+                          else
+                              return group_prefix(d, s_tb, i);
+                      });
     // The last block only updates counters that no block of this launch reads after taking
     // its ticket (each block staged them before its first barrier), and the next kernel
     // sees every write, so no device-scope fence is needed here; on gfx950 such a fence
@@ -1200,8 +1205,11 @@ __device__ void birth_place_body(const Dev &d, int deferred, int advance, int bi
     for (int en = threadIdx.x; en < d.nens; en += blockDim.x) {
         const PlaceEns &E = s_pe[en];
         const int64_t ngrp = (E.idcap + kGroupIds - 1) / kGroupIds;
-        const uint32_t m = s_gp ? s_gp[E.grp_base + ngrp] - s_gp[E.grp_base]
-                                : group_prefix(d, s_tb, E.grp_base + ngrp) - group_prefix(d, s_tb, E.grp_base);
+        uint32_t m;
+        if constexpr (OWN)
+            m = s_gp[E.grp_base + ngrp] - s_gp[E.grp_base];
+        else
+            m = group_prefix(d, s_tb, E.grp_base + ngrp) - group_prefix(d, s_tb, E.grp_base);
         for (int s = 0; s < E.nspecies; ++s) {
             const int sg = E.seg[s];
             const PlaceSeg &P = s_ps[sg];
@@ -1224,7 +1232,7 @@ template <bool F64, bool OWN>
 __global__ void __launch_bounds__(256) k_birth_place(Dev d, int deferred, int advance)
 {
     __shared__ uint32_t s_gp[OWN ? kGroupTile : 1];
-    birth_place_body<F64>(d, deferred, advance, (int)blockIdx.x, (int)gridDim.x, OWN ? s_gp : nullptr);
+    birth_place_body<F64, OWN>(d, deferred, advance, (int)blockIdx.x, (int)gridDim.x, s_gp);
 }
 
 // =======================================================================================
