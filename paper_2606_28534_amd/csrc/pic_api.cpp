@@ -331,10 +331,13 @@ size_t carve(const Plan &P, char *base, Dev &d)
     d.src_tot = P.src_tot;
     d.ticket = c.take<uint32_t>(8);
     d.err = c.take<int32_t>(1);
-    // read-back scratch (last region): k_diag's sums per species, an ensemble's node arrays
+    // read-back scratch: k_diag's sums per species, an ensemble's node arrays
     int64_t nn = 0;
     for (const EnsC &E : P.ens) nn = std::max(nn, E.nnodes);
     d.rb = c.take<double>(std::max<int64_t>(2 * 2 * kDiagGrid, 5 * nn));
+    bool per = true;
+    for (const EnsC &E : P.ens) per = per && E.periodic;
+    if (d.small > 0 && !P.f64 && per && P.cap_tot <= kStepSlots) d.Qx = c.take<unsigned long long>(4 * P.nodes_tot);
     return c.off;
 }
 
@@ -590,8 +593,24 @@ hipError_t enqueue_window(pic_ctx *c, hipStream_t s, int64_t n0, int len, bool &
     const bool coll = c->cfg.collisions != 0;
     hipError_t e;
     if (!coll || !births_fit_solve(d)) {
-        for (int i = 0; i < len; ++i)
+        const int64_t M = 2 * d.nodes_tot, K = c->sort_every;
+        unsigned long long *ring[3] = {d.Qi, d.Qx, d.Qx + M};
+        const bool one = step_in_one_launch(d);
+        for (int i = 0; i < len; ++i) {
+            // whole turns of the three charge buffers, so that the charge ends in d.Qi and the
+            // second buffer cleared, as the first step finds them
+            int m = 0;
+            if (one)
+                while (i + m < len - 1 && (n0 + i + m + 1) % K != 0 && (n0 + i + m + 2) % K != 0) ++m;
+            m = m / 3 * 3;
+            for (int q = 0; q < m; ++q) {
+                Dev dd = d;
+                dd.Qi = ring[q % 3];
+                if ((e = launch_step_small(dd, ring[(q + 1) % 3], ring[(q + 2) % 3], s)) != hipSuccess) return e;
+            }
+            i += m;
             if ((e = enqueue_step(c, s, n0 + i, ready, false)) != hipSuccess) return e;
+        }
         return hipSuccess;
     }
     const int K = c->sort_every;

@@ -27,6 +27,7 @@ constexpr int kMaxEns = 256;          // ensembles per context
 constexpr int kMaxSmooth = 4;         // passes of the density filter
 constexpr int kSmallEns = 8;          // ensembles of a run whose solve is one launch
 constexpr int kSmallChunks = 4;       // and chunks of each
+constexpr int64_t kStepSlots = 1 << 20;  // slots of a run whose plain step is one launch (pic_step_small.hip)
 // Birth ranking: a bit per parent id and a count per group of kGroupIds ids (a birth's rank
 // among its ensemble's births is the scanned count of the groups below its own plus the
 // bits below it in its group).
@@ -145,6 +146,7 @@ struct Dev {
     int64_t nodes_tot, cells_tot;
     unsigned long long *Qi;   // [2][nodes_tot] (int64 fixed point, two's complement)
     double *Qd;               // [2][nodes_tot]
+    unsigned long long *Qx;   // [2][2][nodes_tot] two more charge buffers (small periodic FP32 runs; else null)
     double *rho, *phi, *E;    // [nodes_tot]
     float2 *Ecell;            // [nodes_tot]
     double *agg;              // [nchunks_tot][A_NAGG]

@@ -44,6 +44,11 @@ hipError_t launch_zero_q(const Dev &d, bool f64, hipStream_t s);
 hipError_t launch_solve(const Dev &d, bool f64, int64_t nchunks, bool zero_q, hipStream_t s,
                         bool with_births = false, bool with_params = false, bool advance = false);
 bool births_fit_solve(const Dev &d);
+// A step of a small periodic run without collisions in one launch, from charge d.Qi to Qout (zero
+// before), clearing Qzero: for the runs step_in_one_launch takes, on steps that neither sort nor
+// count cells, when a full step follows before anyone reads the fields.
+bool step_in_one_launch(const Dev &d);
+hipError_t launch_step_small(const Dev &d, unsigned long long *Qout, unsigned long long *Qzero, hipStream_t s);
 hipError_t launch_field_stats(const Dev &d, bool f64, int64_t nchunks, hipStream_t s);
 hipError_t launch_params(const Dev &d, hipStream_t s);
 int64_t scan_blocks(int64_t n);
