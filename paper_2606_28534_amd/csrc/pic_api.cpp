@@ -1509,7 +1509,9 @@ int adj_sweep(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int ckpt_e
 // The same on a small grid: one launch per step, in which every block solves the field for
 // itself.  The forward steps store their checkpoints (charge included), so a recomputed segment
 // starts from them without copies and never touches the run's own arrays, which keep the
-// final state.
+// final state.  The last segment's steps leave their states and fields where a recomputation
+// would, so it has none (one launch of about 10 us a step saved; a window of one segment takes
+// two launches a step instead of three).
 int adj_sweep_small(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int C, int32_t b, int64_t nslots,
                     int64_t step0, double *fe, hipStream_t s)
 {
@@ -1543,9 +1545,13 @@ int adj_sweep_small(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int 
     for (int t = 0; t < nsteps; ++t) {
         dd.Qi = ring[t % 3];
         const bool keep = t % C == 0;
-        // (the recomputation pushes every particle once more, and its pushes count too)
-        HIPC(c, launch_adj_fwd(dd, run, run, keep ? ck(t / C) : none, keep ? ckQ(t / C) : nullptr, ring[(t + 1) % 3],
-                               ring[(t + 2) % 3], nullptr, nslots, 2, s));
+        const int64_t k = t / C;
+        const int i = t % C;
+        const bool rec = k == A.nseg_ck - 1;
+        const AdjState in = rec && i > 0 ? at(k, i) : run, out = rec && t + 1 < nsteps ? at(k, i + 1) : run;
+        // (a sweep counts every particle's pushes twice, also where it keeps the states)
+        HIPC(c, launch_adj_fwd(dd, in, out, keep ? ck(k) : none, keep ? ckQ(k) : nullptr, ring[(t + 1) % 3],
+                               ring[(t + 2) % 3], rec ? Eb + (int64_t)i * nn : nullptr, nslots, 2, s));
     }
     u64 *last = ring[nsteps % 3];
     if (last != d.Qi) HIPC(c, hipMemcpyAsync(d.Qi, last, nn * 8, hipMemcpyDeviceToDevice, s));
@@ -1561,7 +1567,7 @@ int adj_sweep_small(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int 
     const int32_t *above = run.cell;  // cells of the step above
     for (int64_t k = A.nseg_ck - 1; k >= 0; --k) {
         const int t0 = (int)(k * C), len = std::min(nsteps, t0 + C) - t0;
-        for (int i = 0; i < len; ++i) {
+        for (int i = 0; i < len && k < A.nseg_ck - 1; ++i) {
             dd.Qi = i == 0 ? ckQ(k) : Qs + (int64_t)((m + 2) % 3) * nn;
             if (i + 1 < len) {
                 HIPC(c, launch_adj_fwd(dd, at(k, i), at(k, i + 1), none, nullptr, Qs + (int64_t)(m % 3) * nn,
