@@ -177,7 +177,7 @@ struct Dev {
                               // of kGroupTile groups when ngt > 0 (global otherwise)
     uint32_t *gtile;          // [max(ngt, 1)] group-count total of each tile
     uint32_t *nbens;          // [kSmallEns] births of the step per ensemble (small runs)
-    int32_t ngt;              // tiles of the tiled scan (0: the global three-kernel scan)
+    int32_t ngt;              // tiles of the tiled scan (0: the global scan)
     int64_t g_tot;            // a multiple of 4096
     // null-collision candidates of the FP32 pass: tile t keeps its candidate slots in
     // cand[t * tile .. t * tile + ctile[t])

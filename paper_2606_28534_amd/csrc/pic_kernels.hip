@@ -1930,7 +1930,7 @@ hipError_t launch_sort(const Dev &d, bool f64, const Launch &L, hipStream_t s)
     hipError_t e = launch_sort_prepare(d, s);
     if (e != hipSuccess) return e;
     if (!f64) return launch_sort32_scatter(d, L.sort_ppt, L.window, s, d.cap_tot, L.sort_nt != 0);
-    // the scatter's static runs of tiles are short: 8x the pass's persistent grid (a sweep
+    // the scatter's static runs of tiles are short: 8 x Launch::grid blocks (a sweep
     // from 1/2x to 8x on the 4e7-particle slab: 1.33, 1.07, 0.92, 0.85, 0.83 ms)
     const size_t lds = (size_t)L.window * 4;
     hipLaunchKernelGGL((k_sort_scatter<4>), dim3(8 * L.grid), dim3(L.block), lds, s, d, L.window);
