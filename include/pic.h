@@ -19,7 +19,7 @@
  *     reports and keeps it alive until pic_free; the library carves every particle, grid
  *     and scratch array out of it and never allocates or frees device memory itself,
  *     except the small per-context HIP graph objects; contexts share a block of page-locked
- *     host memory (under 64 KiB) held until the process ends.  Host pointers are only used
+ *     host memory (under 64 KiB) given back with the last of them.  Host pointers are only used
  *     during the call.
  *   - Normalised units: eps0 = e = m_e = n0 = T_e = 1 (omega_pe = v_th,e = lambda_D = 1).
  *   - Sticky device error flags (capacity overflow, non-finite field) are checked at the

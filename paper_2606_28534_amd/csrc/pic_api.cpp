@@ -345,8 +345,8 @@ size_t carve(const Plan &P, char *base, Dev &d)
 
 // Page-locked host memory the device writes a context's scalar read-back to.  Locking a page
 // takes about 55 us, a third of what creating a small context takes, so contexts share one
-// block of kHostPages, locked for every GPU when the first of them is created and held until the
-// process ends; a context beyond them locks its own.
+// block of kHostPages, locked for every GPU when the first of them is created and given back with
+// the last; a context beyond them locks its own.
 struct HostPage {
     alignas(256) DiagPack diag;
     int32_t err;
@@ -443,10 +443,15 @@ void host_page_give(HostPage *p)
 {
     if (!p) return;
     std::lock_guard<std::mutex> lk(g_page_mu);
-    if (p >= g_pages && p < g_pages + kHostPages)
-        g_page_used &= ~(1ull << (p - g_pages));
-    else
+    if (!g_pages || p < g_pages || p >= g_pages + kHostPages) {
         (void)hipHostFree(p);
+        return;
+    }
+    g_page_used &= ~(1ull << (p - g_pages));
+    if (!g_page_used) {
+        (void)hipHostFree(g_pages);
+        g_pages = nullptr;
+    }
 }
 
 int fail(pic_ctx *c, int code, const std::string &m)

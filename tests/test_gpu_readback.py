@@ -75,3 +75,21 @@ def test_scalars_of_every_ensemble(pic, prec):
             v2 = sum(np.square(p[s][c]).sum() for c in ("vx", "vy", "vz"))
             assert r["ke"][s] == pytest.approx(0.5 * sp["m"] * sp["w"] * v2, rel=1e-12)
     sim.close()
+
+
+def test_contexts_share_the_read_back_block(pic):
+    """More contexts than the shared page-locked block has pages (64), closed out of order, then
+    one after the block was given back: each reads its own scalars."""
+    def one(k):
+        e = synth.ensemble(5 + k, 3, collisions=False, nspecies=1, seed=1 + k, extra=64)
+        return pic.Sim({"name": "t", "steps": 1, "precision": "fp32", "ensembles": [e]}, fused=True)
+
+    sims = [one(k) for k in range(67)]
+    for k, s in enumerate(sims):
+        assert s.diag()["count"][0] == 3 * (5 + k)
+    for s in sims[::2] + sims[1::2]:
+        s.close()
+    s = one(70)
+    s.step(1)
+    assert s.diag()["step"] == 1 and s.diag()["count"][0] <= 3 * 75
+    s.close()
