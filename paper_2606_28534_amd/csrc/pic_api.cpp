@@ -506,7 +506,15 @@ hipError_t launch_after_pass(pic_ctx *c, hipStream_t s, int hist)
 // particle pass writes every particle at its place in cell order (`ready` carries that
 // state between the two steps).  Otherwise the sort step counts and then sorts in kernels
 // of its own.
-hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool no_sort)
+//
+// With `pending` (the separate stages, stepped) the births of a step that another follows are left
+// to that step's solve, as in enqueue_window, and *pending carries them; their pairs' charge is
+// then added by the collide stage, since the deposit does not see them yet.  `last`: no step
+// follows, and the births are placed in line, as they are before a sort.  One launch a step
+// less: 20 steps of 256 FP64 cells 815 -> 757 us, of 1e4 FP32 cells (3e6 particles) 2220 -> 2054, of
+// 2e4 FP64 cells (8e6 particles) 5908 -> 5801.
+hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool no_sort, bool *pending = nullptr,
+                        bool last = true)
 {
     const Dev &d = c->d;
     const bool f64 = c->P.f64;
@@ -556,7 +564,9 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
     ready = false;
     // the solve clears the charge once it has read it (the stages before the deposit leave it
     // alone) and computes the collision bound
-    if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, false, coll, adv_in_solve)) != hipSuccess) return e;
+    const bool placed = pending && *pending;
+    const bool defer = pending && !last && coll && !sort_now && births_fit_solve(d);
+    if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, placed, coll, adv_in_solve)) != hipSuccess) return e;
     if (tm && (e = hipEventRecord(c->ev[c->ev_used], s)) != hipSuccess) return e;
     if ((e = launch_particles(d, c->L, s, f64, SB_PUSH, 0)) != hipSuccess) return e;
     if (tm) {
@@ -565,11 +575,12 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
     }
     if ((e = launch_neutrals(d, s)) != hipSuccess) return e;
     if (coll) {
-        if ((e = launch_particles(d, c->L, s, f64, SB_COLLIDE, 0, false, false)) != hipSuccess) return e;
-        if ((e = launch_candidates(d, c->L, s, f64, 0, false)) != hipSuccess) return e;
+        if ((e = launch_particles(d, c->L, s, f64, SB_COLLIDE, 0, false, defer)) != hipSuccess) return e;
+        if ((e = launch_candidates(d, c->L, s, f64, 0, defer)) != hipSuccess) return e;
     }
     if ((e = launch_source(d, 0, s, false)) != hipSuccess) return e;
-    if (coll && (e = launch_births(d, f64, true, true, s)) != hipSuccess) return e;
+    if (coll && !defer && (e = launch_births(d, f64, true, true, s)) != hipSuccess) return e;
+    if (pending) *pending = defer;
     if ((e = launch_particles(d, c->L, s, f64, SB_DEPOSIT, 0)) != hipSuccess) return e;
     if (!coll && !adv_in_solve && (e = launch_advance(d, s)) != hipSuccess) return e;
     if (sort_now) {
@@ -872,7 +883,7 @@ int pic_collide(pic_ctx *c, void *stream)
     c->sort_ready = false;  // particles or the step count change: no prepared sort
     hipStream_t s = (hipStream_t)stream;
     if (c->cfg.collisions) {
-        HIPC(c, launch_particles(c->d, c->L, s, c->P.f64, SB_COLLIDE, 0));
+        HIPC(c, launch_particles(c->d, c->L, s, c->P.f64, SB_COLLIDE, 0, true, !c->P.f64));
         HIPC(c, launch_candidates(c->d, c->L, s, c->P.f64, 0));
     }
     HIPC(c, launch_source(c->d, 0, s));
@@ -895,6 +906,8 @@ int pic_step(pic_ctx *c, int32_t nsteps, void *stream)
 {
     if (!c || nsteps < 0) return PIC_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    const int64_t end = c->host_step + nsteps;
+    bool pending = false;  // births of the step before, left to the next solve
     int rc = plan_windows(c, nsteps, false, [&](int64_t n, int len, bool graph) -> int {
         if (graph) {
             hipGraphExec_t x = nullptr;
@@ -904,7 +917,7 @@ int pic_step(pic_ctx *c, int32_t nsteps, void *stream)
             c->graph_launches += 1;
             c->sort_ready = ready_after(c, n + len - 1);
         } else {
-            HIPC(c, enqueue_step(c, s, n, c->sort_ready, false));
+            HIPC(c, enqueue_step(c, s, n, c->sort_ready, false, &pending, n + len == end));
         }
         c->host_step = n + len;
         return PIC_OK;

@@ -21,11 +21,11 @@ enum StageBits : int { SB_PUSH = 1, SB_COLLIDE = 2, SB_DEPOSIT = 4, SB_HIST = 8 
 
 // With the COLLIDE stage the null-collision bound kernel runs first unless `with_params`
 // is false (the caller launched it).  Small FP32 runs collide their candidates in the pass
-// (inline_candidates; without `depo` their new pairs are left to a later deposit), all others
-// in launch_candidates or launch_after.
+// (inline_candidates), all others in launch_candidates or launch_after.  Without `depo` the new
+// pairs of the COLLIDE stage are left to a later deposit of every particle.
 hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f64, int stages, int hist,
                             bool with_params = true, bool depo = true);
-hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist);
+hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist, bool pairs);
 hipError_t launch_field_energy(const Dev &d, hipStream_t s);
 // After a pass with the COLLIDE stage: the FP32 form's candidate kernel (no-op for FP64,
 // whose pass scatters in place).  Without `depo` the new pairs are left to a later deposit of

@@ -1715,7 +1715,7 @@ hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f
         LAUNCH_CHECK();
     }
     if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt, depo);
-    return launch_pass64(d, L.block, s, stages, hist);
+    return launch_pass64(d, L.block, s, stages, hist, depo && (stages & (SB_COLLIDE | SB_DEPOSIT)) == SB_COLLIDE);
 }
 
 hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist, bool depo)

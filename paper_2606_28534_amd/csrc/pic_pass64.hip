@@ -82,8 +82,8 @@ __device__ __forceinline__ void emit64(const Dev &d, const Seg64 &G, int s, cons
 // Collide one candidate (its post-push state is in memory): scatter, tally, append a birth.
 template <bool DEPO>
 __device__ __forceinline__ double collide64(const Dev &d, const SegC &S, const EnsC &e, int b, int64_t i,
-                                            double numax, double pnull, uint32_t tag, int half, int st, bool hist,
-                                            uint32_t *s_c)
+                                            double numax, double pnull, uint32_t tag, int half, int st, bool pairs,
+                                            bool hist, uint32_t *s_c)
 {
     PS<true> p;
     p.x = d.x[b][i];
@@ -125,7 +125,7 @@ __device__ __forceinline__ double collide64(const Dev &d, const SegC &S, const E
     }
     if (S.other >= 0)
         atomicMax(d.vmax2 + ((int64_t)half * kCntStripes + st) * d.nseg + S.other, dbits(speed2_rn(vi[0], vi[1], vi[2])));
-    if constexpr (DEPO) {
+    if (DEPO || pairs) {
         // the new pair sits at the parent's position
         global_deposit64(d, S, S.species, p.x, hist);
         if (S.other >= 0) global_deposit64(d, d.seg[S.other], 1, p.x, hist);
@@ -133,6 +133,9 @@ __device__ __forceinline__ double collide64(const Dev &d, const SegC &S, const E
     return fmax(v2m, speed2_rn(ve[0], ve[1], ve[2]));
 }
 
+// hist_rt: count cells in the deposit's window; a collide stage without deposit adds its new
+// pairs' charge all the same.
+constexpr int kHist64 = 1, kPairs = 2;
 template <int STAGES>
 __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T)
 {
@@ -163,7 +166,7 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
     const EnsC &e = d.ens[S.ens];
     const Seg64 G = seg64(S, e);  // gather, push and deposit constants in registers
     const int s = S.species, b = *d.cur;
-    const bool hist = HISTC || hist_rt != 0;
+    const bool hist = HISTC || (hist_rt & kHist64) != 0;
     const int st = stripe_of_block();
 
     // every load of the tile is issued before any is used
@@ -322,7 +325,8 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
         if ((uint32_t)tid < nc) {
             const double numax = d.numax[sg], pnull = d.pnull[sg];
             for (uint32_t q = tid; q < nc; q += BLOCK)
-                v2m = fmax(v2m, collide64<DEPO>(d, S, e, b, first + s_list[q], numax, pnull, tag, half, st, hist, s_c));
+                v2m = fmax(v2m, collide64<DEPO>(d, S, e, b, first + s_list[q], numax, pnull, tag, half, st,
+                                                (hist_rt & kPairs) != 0, hist, s_c));
         }
         v2m = wave_max_f64(v2m);
         if (lane == 0 && v2m > 0.0) atomicMax(&s_v2, dbits(v2m));
@@ -373,14 +377,15 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
 
 // One block per tile of the slot capacity (segment slot ranges are multiples of kSlotAlign,
 // a multiple of every tile).
-hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist)
+hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist, bool pairs)
 {
+    const int rt = (hist ? kHist64 : 0) | (pairs ? kPairs : 0);
     static_assert(kSlotAlign % (256 * kPpt64) == 0, "whole tiles per segment");
     const int64_t T = d.cap_tot / (block * kPpt64);
     const dim3 g((unsigned)T);
 #define PIC_CASE(ST)                                                                   \
     case ST:                                                                           \
-        hipLaunchKernelGGL((k_particles<ST>), g, dim3(block), 0, s, d, hist, T);       \
+        hipLaunchKernelGGL((k_particles<ST>), g, dim3(block), 0, s, d, rt, T);         \
         break;
     switch (stages) {
         PIC_CASE(ST_PUSH)
