@@ -162,8 +162,8 @@ typedef struct {
     int32_t sort_ppt;    /* particles per thread of the FP32 sort scatter; 0 = default     */
     int32_t nontemporal; /* bit 0: the fused FP32 pass always streams particles with
                           * non-temporal loads and stores (without it, it does so only while
-                          * more particles are in use than the last-level cache holds; no
-                          * result changes); bit 1: the FP32 sort scatter reads its input
+                          * more particles are in use than the last-level cache holds, as
+                          * the FP64 push does; no result changes); bit 1: the FP32 sort scatter reads its input
                           * with non-temporal loads; 0 = default                           */
     int32_t smooth;      /* passes (0..4) of the 1-2-1 density filter applied to rho before
                           * every solve (R23): periodic grids wrap, bounded grids mirror at

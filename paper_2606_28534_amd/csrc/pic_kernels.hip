@@ -1552,14 +1552,16 @@ __global__ void __launch_bounds__(256) k_sort_scatter(Dev d, int W)
     if (threadIdx.x == 0) s_last = (atomicAdd(d.ticket + 3, 1u) == gridDim.x - 1);
     __syncthreads();
     if (!s_last) return;
+    int64_t mine = 0;
     for (int sg = threadIdx.x; sg < d.nseg; sg += BLOCK) {
         const SegC &S = d.seg[sg];
         const uint32_t end =
             __hip_atomic_load(d.cursor + S.cbase + S.ncells - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t n = (int64_t)end - d.segstart[sg];
-        d.n_slots[sg] = min(max(n, (int64_t)0), S.cap);
+        const int64_t n = min(max((int64_t)end - d.segstart[sg], (int64_t)0), S.cap);
+        d.n_slots[sg] = n;
+        mine += n;
     }
-    __syncthreads();
+    set_stream_flag(d, mine);
     if (threadIdx.x == 0) {
         *d.cur = nb;
         d.ticket[3] = 0u;

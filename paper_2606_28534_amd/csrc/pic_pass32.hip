@@ -273,9 +273,8 @@ __device__ __forceinline__ void tile_collide(const Dev &d, const SegC &S, const 
 // faster, over less than that they throw away what the next pass finds cached: per fused step
 // (cached, non-temporal) 104.0 and 106.2 us at 8e6 particles (192 MB), 122.3 and 121.8 at 1e7,
 // 142.7 and 140.8 at 1.2e7, 192.8 and 169.9 at 1.6e7, 442 and 381 at 4e7.  The line lies at
-// kStreamSlots slots in use; the host knows only the capacity, so the sort counts them and the
+// kStreamSlots (1e7) slots in use; the host knows only the capacity, so the sort counts them and the
 // pass reads the answer beside the buffer index (d.cur[1]).
-constexpr int64_t kStreamSlots = 10'000'000;
 enum NtMode : int { NT_CACHED = 0, NT_STREAM = 1, NT_AUTO = 2 };
 
 // With INL (few tiles, see inline_candidates) the tile's collision candidates are collided here
@@ -844,17 +843,6 @@ __global__ void __launch_bounds__(256) k_sort32(Dev d, int W, int64_t T)
         ovz[o] = vz[k];
         oid[o] = id[k];
     }
-}
-
-// Whether the particle arrays in use call for non-temporal streams, by a block of 256 threads.
-__device__ __forceinline__ void set_stream_flag(const Dev &d, int64_t mine)
-{
-    __shared__ unsigned long long s_n;
-    if (threadIdx.x == 0) s_n = 0ull;
-    __syncthreads();
-    if (mine) atomicAdd(&s_n, (unsigned long long)mine);
-    __syncthreads();
-    if (threadIdx.x == 0) d.cur[1] = s_n >= (unsigned long long)kStreamSlots ? 1 : 0;
 }
 
 __global__ void __launch_bounds__(256) k_sort_finish(Dev d)

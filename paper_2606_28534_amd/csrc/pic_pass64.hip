@@ -34,16 +34,29 @@ constexpr int kWin64 = 1024;  // LDS window: nodes x copies
 
 // A run of consecutive slots of one array; `in` slots of it are in range (whole runs as one
 // vector: the run's first slot is even and the arrays are 256-byte aligned).
+typedef double vec2d __attribute__((ext_vector_type(2)));
+typedef uint32_t vec2u __attribute__((ext_vector_type(2)));
+template <bool NT>
 __device__ __forceinline__ void run_load(const double *p, int in, double fill, double (&v)[kRun64])
 {
     if (in == kRun64) {
-        const double2 t = *(const double2 *)p;
+        const vec2d t = NT ? __builtin_nontemporal_load((const vec2d *)p) : *(const vec2d *)p;
         v[0] = t.x;
         v[1] = t.y;
     } else {
         v[0] = in > 0 ? p[0] : fill;
         v[1] = fill;
     }
+}
+
+template <bool NT>
+__device__ __forceinline__ void run_store(double *p, double a, double b)
+{
+    const vec2d v = {a, b};
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, (vec2d *)p);
+    else
+        *(vec2d *)p = v;
 }
 
 // Adds a run of equal cell (its left and right shares and its count) to the tile's LDS window
@@ -136,8 +149,8 @@ __device__ __forceinline__ double collide64(const Dev &d, const SegC &S, const E
 // hist_rt: count cells in the deposit's window; a collide stage without deposit adds its new
 // pairs' charge all the same.
 constexpr int kHist64 = 1, kPairs = 2;
-template <int STAGES>
-__global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T)
+template <int STAGES, bool NT>
+__device__ __forceinline__ void particles_body(const Dev &d, int hist_rt, int64_t first, int64_t last, int sg, int b)
 {
     constexpr bool PUSH = STAGES & ST_PUSH;
     constexpr bool COLL = STAGES & ST_COLLIDE;
@@ -156,16 +169,10 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
     __shared__ int s_mn[4], s_mx[4];
 
     const int tid = threadIdx.x, BLOCK = blockDim.x, lane = lane_id(), w = tid / kWave, nw = BLOCK / kWave;
-    const int64_t t = blockIdx.x;
-    if (t >= T) return;
-    const int64_t first = t * BLOCK * kPpt64;
-    const int sg = seg_of_slot(d, first);
     const SegC &S = d.seg[sg];
-    const int64_t last = min(first + (int64_t)BLOCK * kPpt64, S.base + d.n_slots[sg]);
-    if (first >= last) return;
     const EnsC &e = d.ens[S.ens];
     const Seg64 G = seg64(S, e);  // gather, push and deposit constants in registers
-    const int s = S.species, b = *d.cur;
+    const int s = S.species;
     const bool hist = HISTC || (hist_rt & kHist64) != 0;
     const int st = stripe_of_block();
 
@@ -177,15 +184,16 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
         const int in = (int)min((int64_t)kRun64, max((int64_t)0, last - i));
         double x[kRun64], v[3][kRun64];
         uint32_t id[kRun64] = {0u, 0u};
-        run_load(d.x[b] + i, in, -1.0, x);
+        run_load<NT>(d.x[b] + i, in, -1.0, x);
         if (NEED_V) {
-            run_load(d.dvx[b] + i, in, 0.0, v[0]);
-            run_load(d.dvy[b] + i, in, 0.0, v[1]);
-            run_load(d.dvz[b] + i, in, 0.0, v[2]);
+            run_load<NT>(d.dvx[b] + i, in, 0.0, v[0]);
+            run_load<NT>(d.dvy[b] + i, in, 0.0, v[1]);
+            run_load<NT>(d.dvz[b] + i, in, 0.0, v[2]);
         }
         if (COLL) {
             if (in == kRun64) {
-                const uint2 u = *(const uint2 *)(d.id[b] + i);
+                const vec2u *ip = (const vec2u *)(d.id[b] + i);
+                const vec2u u = NT ? __builtin_nontemporal_load(ip) : *ip;
                 id[0] = u.x;
                 id[1] = u.y;
             } else if (in > 0) {
@@ -241,10 +249,10 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
             // the end of the slots in use keeps what lies beyond them
             if (!died && i + kRun64 <= last) {
                 const int k = g * kRun64;
-                *(double2 *)(d.x[b] + i) = make_double2(p[k].x, p[k + 1].x);
-                *(double2 *)(d.dvx[b] + i) = make_double2(p[k].vx, p[k + 1].vx);
-                *(double2 *)(d.dvy[b] + i) = make_double2(p[k].vy, p[k + 1].vy);
-                *(double2 *)(d.dvz[b] + i) = make_double2(p[k].vz, p[k + 1].vz);
+                run_store<NT>(d.x[b] + i, p[k].x, p[k + 1].x);
+                run_store<NT>(d.dvx[b] + i, p[k].vx, p[k + 1].vx);
+                run_store<NT>(d.dvy[b] + i, p[k].vy, p[k + 1].vy);
+                run_store<NT>(d.dvz[b] + i, p[k].vz, p[k + 1].vz);
             } else {
 #pragma unroll
                 for (int u = 0; u < kRun64; ++u) {
@@ -373,6 +381,26 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
             atomicMax(d.vmax2 + ((int64_t)half * kCntStripes + st) * d.nseg + sg, s_v2);
         }
     }
+}
+
+template <int STAGES>
+__global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T)
+{
+    const int64_t t = blockIdx.x;
+    if (t >= T) return;
+    const int64_t first = t * blockDim.x * kPpt64;
+    const int sg = seg_of_slot(d, first);
+    const int64_t last = min(first + (int64_t)blockDim.x * kPpt64, d.seg[sg].base + d.n_slots[sg]);
+    const int b = d.cur[0], nt = d.cur[1];
+    if (first >= last) return;
+    // The push streams its particles non-temporally once they outgrow the last-level cache (at
+    // kStreamSlots in use, as the FP32 pass): cached and non-temporal 40.6 and 45.1 us at 4e6, 81
+    // and 88 at 8e6, 145 and 130 at 1.2e7, 485 and 430 at 4e7.  A second form beside the collide
+    // stage's took it above 128 registers (80 -> 97 us at 8e6), so that one stays cached.
+    if (STAGES == ST_PUSH && nt)
+        particles_body<STAGES, true>(d, hist_rt, first, last, sg, b);
+    else
+        particles_body<STAGES, false>(d, hist_rt, first, last, sg, b);
 }
 
 // One block per tile of the slot capacity (segment slot ranges are multiples of kSlotAlign,

@@ -55,3 +55,30 @@ def test_stream_choice_changes_nothing(pic, ppc, collisions, fused):
     same(b, c)
     for x in (a, b, c):
         x.close()
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_fp64_push_on_either_side(pic, fused):
+    """The FP64 push streams by itself from 1e7 slots in use, as counted by the sort and where state
+    is set: one push of the same particles in a run that streams (filled to the line by a second
+    ensemble) and in one that does not is the same to the last bit."""
+    e = synth.ensemble(20_000, 100, collisions=True, seed=5, sort_every=3, cap_factor=1.25)
+    big = synth.ensemble(20_000, 160, collisions=True, seed=6, sort_every=3, cap_factor=1.25)
+    a = pic.Sim({"name": "t", "steps": 1, "precision": "fp64", "ensembles": [e]}, fused=fused)
+    b = pic.Sim({"name": "t", "steps": 1, "precision": "fp64", "ensembles": [e, big]}, fused=fused)
+    E = synth.random_field(e, seed=3)
+    st = synth.random_state(e, [2_000_001, 1_999_999], seed=8)
+    for rep in range(2):
+        for x in (a, b):
+            if rep:
+                x.sort()  # counts the slots in use itself
+            else:
+                x.set_state(st)
+            x.set_fields(E)
+            x.push()
+        for s in range(2):
+            pa, pb = (x.particles(0, s) for x in (a, b))
+            ia, ib = np.argsort(pa["id"]), np.argsort(pb["id"])
+            for q in ("id", "x", "vx", "vy", "vz"):
+                assert np.array_equal(pa[q][ia], pb[q][ib]), (rep, s, q)
+    a.close(), b.close()
