@@ -413,6 +413,18 @@ hipError_t static_scratch_address(void **out)
     return hipSuccess;
 }
 
+// While it lives, this thread may lock and free host memory though some stream is being captured
+// (another library's graph, say, while a dropped context is freed); otherwise the call fails and
+// spoils that capture.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool on = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture()
+    {
+        if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
 constexpr int kHostPages = 64;
 std::mutex g_page_mu;
 HostPage *g_pages;
@@ -421,6 +433,7 @@ uint64_t g_page_used;  // bit k: page k of the block is taken
 hipError_t host_page_take(HostPage **out)
 {
     std::lock_guard<std::mutex> lk(g_page_mu);
+    RelaxedCapture relaxed;
     if (!g_pages) {
         void *p = nullptr;
         const hipError_t e = hipHostMalloc(&p, kHostPages * sizeof(HostPage), hipHostMallocPortable);
@@ -443,6 +456,7 @@ void host_page_give(HostPage *p)
 {
     if (!p) return;
     std::lock_guard<std::mutex> lk(g_page_mu);
+    RelaxedCapture relaxed;
     if (!g_pages || p < g_pages || p >= g_pages + kHostPages) {
         (void)hipHostFree(p);
         return;
