@@ -392,6 +392,7 @@ __global__ void __launch_bounds__(256) k_adj_a(Dev d, const int32_t *xc, const f
         const int64_t i = i0 + k;
         if (i >= n) break;
         const int j = xc[i];
+        if (j < 0) continue;  // a slot the push dropped as non-finite (the call reports it)
         const double f = (double)xo[i];
         const int j1 = (j + 1 == N) ? 0 : j + 1;
         const double lvn = lv[i] + dt * lx[i];
@@ -431,6 +432,7 @@ __global__ void __launch_bounds__(256) k_adj_b(const int32_t *xc, const double *
         const int64_t i = i0 + k;
         if (i >= n) break;
         const int j = xc[i];
+        if (j < 0) continue;
         const int j1 = (j + 1 == N) ? 0 : j + 1;
         lx[i] += (lQ[j1] - lQ[j]) / dx;
     }
