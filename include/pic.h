@@ -329,7 +329,10 @@ int64_t pic_nnodes(const pic_ctx *ctx, int32_t ens);
 int pic_set_external_field(pic_ctx *ctx, int32_t ens, double E_ext);
 
 /* Scratch bytes pic_adjoint_window needs for `nsteps` steps with a checkpoint every
- * `ckpt_every` steps (caller-allocated device memory). */
+ * `ckpt_every` steps (caller-allocated device memory, of any alignment).  On a grid of at
+ * most 4096 nodes this is the room of its one-launch steps; a window whose scratch only holds
+ * the general sweep (smaller where the cells outnumber the particles and checkpoints are
+ * many) takes that one, with the same results. */
 int pic_adjoint_query(pic_ctx *ctx, int32_t nsteps, int32_t ckpt_every, size_t *bytes);
 
 /* Hand-written discrete adjoint of the collisionless push + deposit + Poisson window

@@ -1349,6 +1349,7 @@ struct AdjLayout {
     size_t off_ck_cell, off_ck_off, off_ck_vx, off_xc, off_xo, off_E, off_lx, off_lv, off_lE, off_lQ,
         off_tmp, off_ext, off_fin, bytes;
     size_t off_ckQ, off_Q, off_v;  // small grids: charge per checkpoint, three charges, one v_x
+    bool small;
 };
 
 // PIC_OK when the run is one the adjoint is defined for; otherwise *why says what is not.
@@ -1367,9 +1368,11 @@ int adj_check(pic_ctx *c, const char **why)
     return PIC_EINVAL;
 }
 
-AdjLayout adj_layout(pic_ctx *c, int nsteps, int K)
+// Scratch of the one-launch steps (`small`) or of the general sweep.
+AdjLayout adj_layout(pic_ctx *c, int nsteps, int K, bool small)
 {
     AdjLayout A{};
+    A.small = small;
     A.n = c->P.seg[0].cap;
     A.nn = c->P.ens[0].nnodes;
     A.K = K;
@@ -1389,7 +1392,7 @@ AdjLayout adj_layout(pic_ctx *c, int nsteps, int K)
     A.off_lx = take((size_t)A.n * 8);
     A.off_lv = take((size_t)A.n * 8);
     A.off_ext = take(64);
-    if (c->d.small) {
+    if (small) {
         A.off_lE = take((size_t)3 * A.nn * 8);
         A.off_ckQ = take((size_t)A.nseg_ck * A.nn * 8);
         A.off_Q = take((size_t)3 * A.nn * 8);
@@ -1403,6 +1406,26 @@ AdjLayout adj_layout(pic_ctx *c, int nsteps, int K)
     A.off_fin = take((size_t)A.n * 4 * 5);  // final state: cell, off, vx, vy, vz
     A.bytes = o;
     return A;
+}
+
+// The layout a window takes in `bytes` of scratch at *base, and whether it fits: on a small grid
+// the one-launch steps' (whose vector loads want it aligned, so *base moves up), or the general
+// sweep's where only that one fits: the former keeps a charge per checkpoint, so with about a
+// particle a cell and many checkpoints it is the larger.
+constexpr size_t kAdjAlign = 16;
+AdjLayout adj_choose(pic_ctx *c, int nsteps, int K, char **base, size_t bytes, bool *fits)
+{
+    const AdjLayout G = adj_layout(c, nsteps, K, false);
+    *fits = G.bytes <= bytes;
+    if (!c->d.small) return G;
+    const AdjLayout A = adj_layout(c, nsteps, K, true);
+    const size_t up = (kAdjAlign - (uintptr_t)*base % kAdjAlign) % kAdjAlign;
+    if (A.bytes + up <= bytes) {
+        *base += up;
+        *fits = true;
+        return A;
+    }
+    return *fits || G.bytes < A.bytes ? G : A;
 }
 
 // One forward step of the window (no sort, no collisions); optionally records x^n and E^n.
@@ -1428,7 +1451,7 @@ int pic_adjoint_query(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, size_t *by
     if (!c || !bytes || nsteps < 1 || ckpt_every < 1) return PIC_EINVAL;
     const char *why = "";
     if (adj_check(c, &why)) return fail(c, PIC_EINVAL, why);
-    *bytes = adj_layout(c, nsteps, ckpt_every).bytes;
+    *bytes = adj_layout(c, nsteps, ckpt_every, c->d.small != 0).bytes + (c->d.small ? kAdjAlign : 0);
     return PIC_OK;
 }
 
@@ -1638,8 +1661,9 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
     c->insitu = false;
     const char *why = "";
     if (adj_check(c, &why)) return fail(c, PIC_EINVAL, why);
-    const AdjLayout A = adj_layout(c, nsteps, ckpt_every);
-    if (bytes < A.bytes) return fail(c, PIC_EINVAL, "adjoint scratch too small");
+    bool fits = false;
+    const AdjLayout A = adj_choose(c, nsteps, ckpt_every, &base, bytes, &fits);
+    if (!fits) return fail(c, PIC_EINVAL, "adjoint scratch too small");
     hipStream_t s = (hipStream_t)stream;
     const Dev &d = c->d;
     double *lv = (double *)(base + A.off_lv);
@@ -1654,10 +1678,10 @@ int adjoint_window_impl(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, char *ba
     if (dvx_len < nslots) return fail(c, PIC_EINVAL, "dW_dvx too short");
     double fe = 0.0;
     {
-        const int rc = d.small ? adj_sweep_small(c, A, base, nsteps, ckpt_every, b, nslots, step0, &fe, s)
+        const int rc = A.small ? adj_sweep_small(c, A, base, nsteps, ckpt_every, b, nslots, step0, &fe, s)
                                : adj_sweep(c, A, base, nsteps, ckpt_every, b, nslots, step0, &fe, s);
         if (rc) return rc;
-        if (!d.small) b = 0;
+        if (!A.small) b = 0;
     }
     // gradients by id
     double gext = 0.0;
@@ -1730,15 +1754,18 @@ int pic_adjoint_window_noalloc(pic_ctx *c, int32_t nsteps, int32_t ckpt_every, d
     const char *why = "";
     if (adj_check(c, &why)) return fail(c, PIC_EINVAL, why);
     // the window's layout, then the by-id gradient (dvx_len doubles) after it
-    const size_t lay = adj_layout(c, nsteps, ckpt_every).bytes;
-    const size_t need = lay + align_up((size_t)std::max<int64_t>(dvx_len, 1) * 8);
-    if (need > kStaticScratchBytes)
+    const size_t by_id = align_up((size_t)std::max<int64_t>(dvx_len, 1) * 8);
+    const size_t room = by_id < kStaticScratchBytes ? kStaticScratchBytes - by_id : 0;
+    char *base = (char *)c->static_scratch;  // (aligned)
+    bool fits = false;
+    const size_t lay = adj_choose(c, nsteps, ckpt_every, &base, room, &fits).bytes;
+    const size_t need = lay + by_id;
+    if (!fits)
         return fail(c, PIC_EINVAL, "adjoint window needs " + std::to_string(need) +
                                        " bytes of scratch, more than the static array's " +
                                        std::to_string(kStaticScratchBytes) +
                                        " (fewer particles, steps or a longer checkpoint interval fit; "
                                        "pic_adjoint_window takes a caller buffer of any size)");
-    char *base = (char *)c->static_scratch;
     return adjoint_window_impl(c, nsteps, ckpt_every, base, lay, W, dW_dvx, dvx_len, dW_dEext,
                                (double *)(base + lay), stream);
 }
