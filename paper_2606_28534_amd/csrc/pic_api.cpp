@@ -15,6 +15,7 @@
 #include "../../include/pic.h"
 #include "pic_device.h"
 #include "pic_kernels.h"
+#include "pic_rules.h"
 
 using namespace pic;
 
@@ -270,7 +271,7 @@ size_t carve(const Plan &P, char *base, Dev &d)
         }
     }
     d.cap_tot = P.cap_tot;
-    d.cur = c.take<int32_t>(2);
+    d.cur = c.take<int32_t>(1);
     d.n_slots = c.take<int64_t>(P.nseg);
     d.next_id = c.take<uint32_t>(P.nseg);
     d.step = c.take<int64_t>(1);
@@ -350,6 +351,7 @@ size_t carve(const Plan &P, char *base, Dev &d)
 struct HostPage {
     alignas(256) DiagPack diag;
     int32_t err;
+    int64_t slots;
 };
 
 struct pic_ctx {
@@ -493,11 +495,19 @@ int err_code(pic_ctx *c, int32_t err)
     return PIC_OK;
 }
 
+// Waits for the stream and takes the error flags and the slots in use from it.
+hipError_t see_run(pic_ctx *c, hipStream_t s)
+{
+    hipError_t e = launch_err_out(c->d, &c->page->err, &c->page->slots, s);
+    if (e != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    c->L.lines = stream_lines(c->page->slots);
+    return hipSuccess;
+}
+
 // Waits for the stream and turns the sticky error flags into their code.
 int check_err(pic_ctx *c, hipStream_t s)
 {
-    HIPC(c, launch_err_out(c->d, &c->page->err, s));
-    HIPC(c, hipStreamSynchronize(s));
+    HIPC(c, see_run(c, s));
     return err_code(c, c->page->err);
 }
 
@@ -552,7 +562,7 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
         const int stages = coll ? (SB_PUSH | SB_COLLIDE | SB_DEPOSIT) : (SB_PUSH | SB_DEPOSIT);
         if (tm && (e = hipEventRecord(c->ev[c->ev_used], s)) != hipSuccess) return e;
         if (sorting)
-            e = launch_pass32_sort(d, c->L.ppt, c->L.window, s, coll, d.cap_tot, c->L.nt);
+            e = launch_pass32_sort(d, c->L, s, coll);
         else
             e = launch_particles(d, c->L, s, f64, stages, hist, false);
         if (e != hipSuccess) return e;
@@ -655,7 +665,7 @@ hipError_t enqueue_window(pic_ctx *c, hipStream_t s, int64_t n0, int len, bool &
         const int hist = (prep || (sort_now && !sorting)) ? 1 : 0;
         if ((e = launch_solve(d, f64, c->P.chunks_tot, true, s, pending, true)) != hipSuccess) return e;
         if (sorting)
-            e = launch_pass32_sort(d, c->L.ppt, c->L.window, s, true, d.cap_tot, c->L.nt);
+            e = launch_pass32_sort(d, c->L, s, true);
         else
             e = launch_particles(d, c->L, s, f64, stages, hist, false);
         if (e != hipSuccess) return e;
@@ -695,7 +705,8 @@ bool ready_after(const pic_ctx *c, int64_t n)
 
 int64_t window_key(const pic_ctx *c, int64_t n, int len)
 {
-    return (n % c->sort_every) * (int64_t)(c->sort_every + 1) + len;
+    const int64_t window = (n % c->sort_every) * (int64_t)(c->sort_every + 1) + len;
+    return window * 8 + c->L.lines;  // (the launches depend on how many lines the slots in use reach)
 }
 
 void drop_graphs(pic_ctx *c)
@@ -767,6 +778,7 @@ Launch default_launch(const pic_config *cfg, const Plan &P)
     L.sort_ppt = (cfg->sort_ppt == 4 || cfg->sort_ppt == 8) ? cfg->sort_ppt : 4;
     L.nt = (cfg->nontemporal & 1) ? 1 : 2;
     L.sort_nt = (cfg->nontemporal & 2) ? 1 : 0;
+    L.lines = 0;
     int64_t tiles = 0;
     for (const SegC &S : P.seg) tiles += (S.cap + (int64_t)L.block * L.ppt - 1) / ((int64_t)L.block * L.ppt);
     int g = cfg->grid > 0 ? cfg->grid : 1024;
@@ -843,19 +855,21 @@ int pic_init(const pic_config *cfg, void *workspace, size_t bytes, void *stream,
     IHIP(hipMemcpyAsync((void *)d.ens, c->P.ens.data(), c->P.ens.size() * sizeof(EnsC), hipMemcpyHostToDevice, s));
     std::vector<int64_t> nslots(c->P.nseg);
     std::vector<uint32_t> nid(c->P.nseg);
+    int64_t total = 0;
     for (int sg = 0; sg < c->P.nseg; ++sg) {
         const SegC &S = c->P.seg[sg];
         const pic_ensemble_desc &D = cfg->ens[S.ens];
         const pic_species_desc &sp = D.sp[S.species];
         const int64_t n = sp.ppc * D.ncells;
         nslots[sg] = n;
+        total += n;
         nid[sg] = (uint32_t)n;
         const double vth = std::sqrt(sp.T / sp.m);
         IHIP(launch_init(d, c->P.f64, sg, n, sp.ppc, D.init_mode, vth, D.perturb_amp, D.perturb_mode, s));
     }
+    c->L.lines = stream_lines(total);
     IHIP(hipMemcpyAsync(d.n_slots, nslots.data(), nslots.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
     IHIP(hipMemcpyAsync(d.next_id, nid.data(), nid.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-    IHIP(launch_stream_flag(d, s));
     IHIP(launch_vmax(d, c->P.f64, s));
     IHIP(launch_zero_q(d, c->P.f64, s));
     IHIP(launch_particles(d, c->L, s, c->P.f64, SB_DEPOSIT, 0));
@@ -998,6 +1012,7 @@ int pic_diag(pic_ctx *c, int32_t ens, pic_diag_out *out, double *moments_dev, vo
     HIPC(c, launch_diag_pack(c->d, ens, c->insitu, c->d.rb, kDiagGrid, &c->page->diag, s));
     HIPC(c, hipStreamSynchronize(s));
     const DiagPack &R = c->page->diag;
+    c->L.lines = stream_lines(R.slots);
     memset(out, 0, sizeof(*out));
     for (int sp = 0; sp < c->P.nspecies; ++sp) {
         const double n = R.n[sp];
@@ -1282,8 +1297,7 @@ int pic_set_particles(pic_ctx *c, int32_t ens, int32_t species, pic_particles in
     HIPC(c, hipMemcpy(&vc, c->d.vcur, 4, hipMemcpyDeviceToHost));
     HIPC(c, hipMemset(c->d.vmax2 + (size_t)vc * kCntStripes * c->P.nseg, 0, (size_t)kCntStripes * c->P.nseg * 8));
     HIPC(c, launch_vmax(c->d, c->P.f64, s));
-    HIPC(c, launch_stream_flag(c->d, s));
-    HIPC(c, hipStreamSynchronize(s));
+    HIPC(c, see_run(c, s));
     return PIC_OK;
 }
 
@@ -2089,7 +2103,6 @@ int pic_load(pic_ctx *c, const void *host_buf, size_t bytes, void *stream)
     HIPC(c, hipMemcpyAsync(d.cur, &zero, 4, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.vcur, &zero, 4, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.step, &h.step, 8, hipMemcpyHostToDevice, s));
-    HIPC(c, launch_stream_flag(d, s));
     HIPC(c, hipStreamSynchronize(s));
     c->host_step = h.step;
     drop_graphs(c);

@@ -68,6 +68,7 @@ struct DiagPack {
     double fe, emax;
     int64_t step;
     unsigned long long neutrals;
+    int64_t slots;                       // in use, of all segments
     int32_t err;
 };
 
@@ -138,7 +139,7 @@ struct Dev {
     double *x[2], *dvx[2], *dvy[2], *dvz[2];
     uint32_t *id[2];
     int64_t cap_tot;          // total slots (a multiple of kSlotAlign)
-    int32_t *cur;             // [2] current particle buffer; whether the FP32 pass streams by itself
+    int32_t *cur;             // [1] current particle buffer
     int64_t *n_slots;         // [nseg] slots in use (alive + absorbed-not-yet-compacted)
     uint32_t *next_id;        // [nseg]
     int64_t *step;            // [1]

@@ -14,6 +14,7 @@ struct Launch {
     int window;  // widest LDS window span, in cells, of the FP32 pass and of the sorts
     int sort_ppt;  // particles per thread of the FP32 sort scatter
     int nt;        // fused FP32 pass: particle loads and stores cached (0), non-temporal (1) or by size (2)
+    int lines;     // of kStreamSlots, reached by the slots in use as the host last saw them
     int sort_nt;   // FP32 sort scatter: non-temporal loads
 };
 
@@ -25,7 +26,7 @@ enum StageBits : int { SB_PUSH = 1, SB_COLLIDE = 2, SB_DEPOSIT = 4, SB_HIST = 8 
 // pairs of the COLLIDE stage are left to a later deposit of every particle.
 hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f64, int stages, int hist,
                             bool with_params = true, bool depo = true);
-hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist, bool pairs);
+hipError_t launch_pass64(const Dev &d, const Launch &L, hipStream_t s, int stages, int hist, bool pairs);
 hipError_t launch_field_energy(const Dev &d, hipStream_t s);
 // After a pass with the COLLIDE stage: the FP32 form's candidate kernel (no-op for FP64,
 // whose pass scatters in place).  Without `depo` the new pairs are left to a later deposit of
@@ -60,12 +61,9 @@ hipError_t launch_sort(const Dev &d, bool f64, const Launch &L, hipStream_t s);
 hipError_t launch_sort_prepare(const Dev &d, hipStream_t s);
 // FP32 fused pass that also scatters into cell order (after launch_sort_prepare), then the
 // slot counts and the buffer flip.
-hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, int nt);
-hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, int nt,
-                         bool depo);
+hipError_t launch_pass32_sort(const Dev &d, const Launch &L, hipStream_t s, bool coll);
+hipError_t launch_pass32(const Dev &d, const Launch &L, hipStream_t s, int stages, int hist, bool depo);
 bool inline_candidates(const Dev &d, int ppt);
-// after the host set the slots in use
-hipError_t launch_stream_flag(const Dev &d, hipStream_t s);
 hipError_t launch_cand32(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool depo);
 // the fused step's candidates, neutrals and source as one launch (FP32 form)
 hipError_t launch_after(const Dev &d, int ppt, hipStream_t s, int hist, int64_t cap_tot, bool coll);
@@ -98,12 +96,12 @@ hipError_t launch_adj_by_id_count(const double *lv, const uint32_t *id, double *
                                   int64_t len, int32_t *err, uint32_t *distinct, hipStream_t s);
 hipError_t launch_diag(const Dev &d, bool f64, int sg, double *out, int grid, hipStream_t s);
 // The scalars of ensemble `en` into one record and its node arrays ([Q0, Q1, rho, phi, E][nn]
-// doubles) into one run of device memory; the error flags alone.  `out` of the records is host
+// doubles) into one run of device memory; the error flags and slots in use alone.  `out` of the records is host
 // memory the device can write.
 hipError_t launch_diag_pack(const Dev &d, int en, bool tallied, const double *v2, int ngrid, DiagPack *out,
                             hipStream_t s);
 hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, double *out, hipStream_t s);
-hipError_t launch_err_out(const Dev &d, int32_t *out, hipStream_t s);
+hipError_t launch_err_out(const Dev &d, int32_t *out, int64_t *slots, hipStream_t s);
 // Node moments of segment sg (reading R27) into out[5][nn] (n, ux, uy, uz, T); nn is the
 // node count of the segment's ensemble.  `out` is device memory the launch overwrites.
 hipError_t launch_moments(const Dev &d, bool f64, int sg, int64_t nn, double *out, hipStream_t s);

@@ -1552,16 +1552,14 @@ __global__ void __launch_bounds__(256) k_sort_scatter(Dev d, int W)
     if (threadIdx.x == 0) s_last = (atomicAdd(d.ticket + 3, 1u) == gridDim.x - 1);
     __syncthreads();
     if (!s_last) return;
-    int64_t mine = 0;
     for (int sg = threadIdx.x; sg < d.nseg; sg += BLOCK) {
         const SegC &S = d.seg[sg];
         const uint32_t end =
             __hip_atomic_load(d.cursor + S.cbase + S.ncells - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int64_t n = min(max((int64_t)end - d.segstart[sg], (int64_t)0), S.cap);
-        d.n_slots[sg] = n;
-        mine += n;
+        const int64_t n = (int64_t)end - d.segstart[sg];
+        d.n_slots[sg] = min(max(n, (int64_t)0), S.cap);
     }
-    set_stream_flag(d, mine);
+    __syncthreads();
     if (threadIdx.x == 0) {
         *d.cur = nb;
         d.ticket[3] = 0u;
@@ -1615,6 +1613,14 @@ __global__ void k_diag(Dev d, int sg, double *out /* [grid][2] */)
 // the 256-cell run went from 769 to 569 us; of the 64 batched ensembles, whose 64 pairs of reads
 // took 39 of 131 ms, to 106 ms.
 // =======================================================================================
+// Slots in use of all segments, by one wave.
+__device__ __forceinline__ int64_t slots_in_use(const Dev &d)
+{
+    int64_t n = 0;
+    for (int sg = lane_id(); sg < d.nseg; sg += kWave) n += d.n_slots[sg];
+    return wave_reduce(n, [](int64_t a, int64_t b) { return a + b; });
+}
+
 // With `tallied`, counts, sums of |v|^2 and field energy come from the fused step's tallies;
 // otherwise from `v2` ([species][ngrid][2], k_diag) and the field-energy kernel.  A wave takes a
 // quantity of a species (or the field energy) on its own, its lanes the stripes.
@@ -1635,7 +1641,11 @@ __global__ void __launch_bounds__(kDiagThreads) k_diag_pack(Dev d, int en, int t
             else if (lane == 0)
                 fe = d.fe[en];
             fe = wave_sum_f64(fe);
-            if (lane == 0) out->fe = fe;
+            const int64_t n = slots_in_use(d);
+            if (lane == 0) {
+                out->fe = fe;
+                out->slots = n;
+            }
         } else if (q < C_NCNT) {
             unsigned long long c = 0;
             for (int st = lane; st < kCntStripes; st += kWave) c += d.cnt[((int64_t)st * d.nseg + e.seg[sp]) * C_NCNT + q];
@@ -1697,7 +1707,14 @@ __global__ void __launch_bounds__(256) k_grid_pack(Dev d, int en, double *out)
     }
 }
 
-__global__ void k_err_out(const int32_t *err, int32_t *out) { *out = *err; }
+__global__ void __launch_bounds__(kWave) k_err_out(Dev d, int32_t *out, int64_t *slots)
+{
+    const int64_t n = slots_in_use(d);
+    if (lane_id() == 0) {
+        *out = *d.err;
+        *slots = n;
+    }
+}
 
 // =======================================================================================
 // Host launchers.
@@ -1716,8 +1733,8 @@ hipError_t launch_particles(const Dev &d, const Launch &L, hipStream_t s, bool f
         hipLaunchKernelGGL(k_params, dim3(1), dim3(256), 0, s, d);
         LAUNCH_CHECK();
     }
-    if (!f64) return launch_pass32(d, L.ppt, L.window, s, stages, hist, d.cap_tot, L.nt, depo);
-    return launch_pass64(d, L.block, s, stages, hist, depo && (stages & (SB_COLLIDE | SB_DEPOSIT)) == SB_COLLIDE);
+    if (!f64) return launch_pass32(d, L, s, stages, hist, depo);
+    return launch_pass64(d, L, s, stages, hist, depo && (stages & (SB_COLLIDE | SB_DEPOSIT)) == SB_COLLIDE);
 }
 
 hipError_t launch_candidates(const Dev &d, const Launch &L, hipStream_t s, bool f64, int hist, bool depo)
@@ -1957,9 +1974,9 @@ hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, double *
     return hipGetLastError();
 }
 
-hipError_t launch_err_out(const Dev &d, int32_t *out, hipStream_t s)
+hipError_t launch_err_out(const Dev &d, int32_t *out, int64_t *slots, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_err_out, dim3(1), dim3(1), 0, s, d.err, out);
+    hipLaunchKernelGGL(k_err_out, dim3(1), dim3(kWave), 0, s, d, out, slots);
     return hipGetLastError();
 }
 

@@ -160,19 +160,6 @@ __device__ __forceinline__ int p_push64(const Dev &d, const Seg64 &G, PS<true> &
     return (x < 0.0) ? 1 : 2;
 }
 
-// Whether the particle arrays in use call for non-temporal streams, by one block from its
-// threads' shares of the slots in use (the line is explained at each pass).
-constexpr int64_t kStreamSlots = 10'000'000;
-__device__ __forceinline__ void set_stream_flag(const Dev &d, int64_t mine)
-{
-    __shared__ unsigned long long s_n;
-    if (threadIdx.x == 0) s_n = 0ull;
-    __syncthreads();
-    if (mine) atomicAdd(&s_n, (unsigned long long)mine);
-    __syncthreads();
-    if (threadIdx.x == 0) d.cur[1] = s_n >= (unsigned long long)kStreamSlots ? 1 : 0;
-}
-
 __device__ __forceinline__ void sc(float a, float *s, float *c) { sincosf(a, s, c); }
 __device__ __forceinline__ void sc(double a, double *s, double *c) { sincos(a, s, c); }
 __device__ __forceinline__ float msqrt(float a) { return sqrtf(a); }

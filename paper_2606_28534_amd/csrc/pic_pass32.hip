@@ -11,11 +11,11 @@
 // appended particles spread over many cells still deposits through LDS.
 // Block b takes tile b (see tile_of_block for why not an XCD-major order).
 #include <algorithm>
-#include <type_traits>
 
 #include "pic_device.h"
 #include "pic_kernels.h"
 #include "pic_particle.h"
+#include "pic_rules.h"
 
 namespace pic {
 
@@ -268,20 +268,11 @@ __device__ __forceinline__ void tile_collide(const Dev &d, const SegC &S, const 
 // to the other buffer at its place in cell order instead of in place: the tile ranks its
 // particles by their cell before the push (the cells the previous pass counted) in LDS and
 // reserves one run per cell, as the sort scatter does, so the pass also sorts and compacts.
-// How the pass moves the particle arrays: cached, non-temporal, or by the run's size.  In place
-// over more particle data than the 256 MB last-level cache holds, non-temporal streams are
-// faster, over less than that they throw away what the next pass finds cached: per fused step
-// (cached, non-temporal) 104.0 and 106.2 us at 8e6 particles (192 MB), 122.3 and 121.8 at 1e7,
-// 142.7 and 140.8 at 1.2e7, 192.8 and 169.9 at 1.6e7, 442 and 381 at 4e7.  The line lies at
-// kStreamSlots (1e7) slots in use; the host knows only the capacity, so the sort counts them and the
-// pass reads the answer beside the buffer index (d.cur[1]).
-enum NtMode : int { NT_CACHED = 0, NT_STREAM = 1, NT_AUTO = 2 };
-
 // With INL (few tiles, see inline_candidates) the tile's collision candidates are collided here
 // as well; hist_rt then also says, in kNoDepo, that the new pairs' deposit is left out.
 constexpr int kHist = 1, kNoDepo = 2;
 enum Inl : int { INL_NO = 0, INL_YES = 1, INL_CXREL = 2 };
-template <int STAGES, int PPT, int NTM = NT_CACHED, bool SORT = false, int INL = INL_NO>
+template <int STAGES, int PPT, int AC = AC_CACHED, bool SORT = false, int INL = INL_NO>
 __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64_t T)
 {
     constexpr bool PUSH = STAGES & PS_PUSH;
@@ -325,24 +316,16 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
     int cell[PPT];
     float off[PPT], vx[PPT], vy[PPT], vz[PPT];
     uint32_t id[PPT];
-    // non-temporal loads and stores of the particle arrays (see kStreamSlots)
-    const bool nt = NTM == NT_STREAM || (NTM == NT_AUTO && d.cur[1] != 0);
-    auto load = [&](auto hint) {
-        constexpr bool NT = decltype(hint)::value;
-        vload<PPT, NT>(d.cell[b] + i0, cell);
-        vload<PPT, NT>(d.off[b] + i0, off);
-        if (NEED_V) {
-            vload<PPT, NT>(d.fvx[b] + i0, vx);
-            vload<PPT, NT>(d.fvy[b] + i0, vy);
-            vload<PPT, NT>(d.fvz[b] + i0, vz);
-        }
-        if (NEED_ID) vload<PPT, NT>(d.id[b] + i0, id);
-    };
+    constexpr bool NTL = AC == AC_STREAM, NTS = AC != AC_CACHED;  // non-temporal loads, stores
     if (full) {
-        if (nt)
-            load(std::true_type{});
-        else
-            load(std::false_type{});
+        vload<PPT, NTL>(d.cell[b] + i0, cell);
+        vload<PPT, NTL>(d.off[b] + i0, off);
+        if (NEED_V) {
+            vload<PPT, NTL>(d.fvx[b] + i0, vx);
+            vload<PPT, NTL>(d.fvy[b] + i0, vy);
+            vload<PPT, NTL>(d.fvz[b] + i0, vz);
+        }
+        if (NEED_ID) vload<PPT, NTL>(d.id[b] + i0, id);
     } else {
 #pragma unroll
         for (int k = 0; k < PPT; ++k) {
@@ -607,27 +590,20 @@ __global__ void __launch_bounds__(256) k_pass32(Dev d, int W, int hist_rt, int64
         // (A collide stage alone writes nothing here: its candidates' velocities are written where
         // they are collided.  Storing every velocity back as well had taken a stepped stage cycle of
         // 4e7 particles 783 us against 684, of 3e6 particles 79.6 against 75.5.)
-        auto store = [&](auto hint) {
-            constexpr bool NT = decltype(hint)::value;
+        if (full) {
             // a group of four cells is stored only if one of them changed (the heavy
             // ions almost never leave their cell in one step)
 #pragma unroll
             for (int q = 0; q < PPT; q += 4) {
                 if ((cchg >> q) & 0xFu) {
                     int c4[4] = {cell[q], cell[q + 1], cell[q + 2], cell[q + 3]};
-                    vstore<4, NT>(d.cell[b] + i0 + q, c4);
+                    vstore<4, NTS>(d.cell[b] + i0 + q, c4);
                 }
             }
-            vstore<PPT, NT>(d.off[b] + i0, off);
-            vstore<PPT, NT>(d.fvx[b] + i0, vx);
-            vstore<PPT, NT>(d.fvy[b] + i0, vy);
-            vstore<PPT, NT>(d.fvz[b] + i0, vz);
-        };
-        if (full) {
-            if (nt)
-                store(std::true_type{});
-            else
-                store(std::false_type{});
+            vstore<PPT, NTS>(d.off[b] + i0, off);
+            vstore<PPT, NTS>(d.fvx[b] + i0, vx);
+            vstore<PPT, NTS>(d.fvy[b] + i0, vy);
+            vstore<PPT, NTS>(d.fvz[b] + i0, vz);
         } else {
 #pragma unroll
             for (int k = 0; k < PPT; ++k) {
@@ -844,31 +820,15 @@ __global__ void __launch_bounds__(256) k_sort32(Dev d, int W, int64_t T)
     }
 }
 
-__global__ void __launch_bounds__(256) k_sort_finish(Dev d)
+__global__ void k_sort_finish(Dev d)
 {
-    int64_t mine = 0;
     for (int sg = threadIdx.x; sg < d.nseg; sg += blockDim.x) {
         const SegC &S = d.seg[sg];
-        const int64_t n = min(max((int64_t)d.cursor[S.cbase + S.ncells - 1] - d.segstart[sg], (int64_t)0), S.cap);
-        d.n_slots[sg] = n;
-        mine += n;
+        const int64_t n = (int64_t)d.cursor[S.cbase + S.ncells - 1] - d.segstart[sg];
+        d.n_slots[sg] = min(max(n, (int64_t)0), S.cap);
     }
-    set_stream_flag(d, mine);
+    __syncthreads();
     if (threadIdx.x == 0) *d.cur = 1 - *d.cur;
-}
-
-// After the host set the slots in use (a load, an injection, a restart).
-__global__ void __launch_bounds__(256) k_stream_flag(Dev d)
-{
-    int64_t mine = 0;
-    for (int sg = threadIdx.x; sg < d.nseg; sg += blockDim.x) mine += d.n_slots[sg];
-    set_stream_flag(d, mine);
-}
-
-hipError_t launch_stream_flag(const Dev &d, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_stream_flag, dim3(1), dim3(256), 0, s, d);
-    return hipGetLastError();
 }
 
 // =======================================================================================
@@ -888,47 +848,57 @@ constexpr int kCountWindowMax = 1024;
 constexpr int64_t kInlineTiles = 16384;
 bool inline_candidates(const Dev &d, int ppt) { return d.cap_tot / (256 * ppt) <= kInlineTiles; }
 
-template <int STAGES, int NTM = NT_CACHED, bool SORT = false, int INL = INL_NO>
-static hipError_t launch_pass32_t(const Dev &d, int ppt, int W, hipStream_t s, int hist, int64_t cap_tot)
+template <int STAGES, int AC = AC_CACHED, bool SORT = false, int INL = INL_NO>
+static hipError_t launch_pass32_t(const Dev &d, const Launch &L, hipStream_t s, int hist)
 {
-    if (SORT) W = std::min(W, kCountWindowMax);
+    const int W = SORT ? std::min(L.window, kCountWindowMax) : L.window;
     const size_t lds = (size_t)W * 8 + (SORT ? (size_t)W * 4 : 0);
-    if (ppt == 4) {
-        const int64_t T = cap_tot / (256 * 4);
-        const int64_t G = (T + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_pass32<STAGES, 4, NTM, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
-    } else {
-        const int64_t T = cap_tot / (256 * 8);
-        const int64_t G = (T + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_pass32<STAGES, 8, NTM, SORT, INL>), dim3(G), dim3(256), lds, s, d, W, hist, T);
-    }
+    const int64_t T = d.cap_tot / (256 * L.ppt);
+    const dim3 G((unsigned)((T + 7) / 8 * 8));
+    if (L.ppt == 4)
+        hipLaunchKernelGGL((k_pass32<STAGES, 4, AC, SORT, INL>), G, dim3(256), lds, s, d, W, hist, T);
+    else
+        hipLaunchKernelGGL((k_pass32<STAGES, 8, AC, SORT, INL>), G, dim3(256), lds, s, d, W, hist, T);
     return hipGetLastError();
 }
 
 // A pass with the COLLIDE stage that also collides its candidates.
 template <int STAGES, bool SORT>
-static hipError_t launch_pass32_inl(const Dev &d, int ppt, int W, hipStream_t s, int hist, int64_t cap_tot)
+static hipError_t launch_pass32_inl(const Dev &d, const Launch &L, hipStream_t s, int hist)
 {
-    if (d.any_cx_rel) return launch_pass32_t<STAGES, NT_CACHED, SORT, INL_CXREL>(d, ppt, W, s, hist, cap_tot);
-    return launch_pass32_t<STAGES, NT_CACHED, SORT, INL_YES>(d, ppt, W, s, hist, cap_tot);
+    if (d.any_cx_rel) return launch_pass32_t<STAGES, AC_CACHED, SORT, INL_CXREL>(d, L, s, hist);
+    return launch_pass32_t<STAGES, AC_CACHED, SORT, INL_YES>(d, L, s, hist);
+}
+
+// A push by the access the run calls for (with SORT the stores scatter, so only its loads count).
+template <int STAGES, bool SORT = false>
+static hipError_t launch_pass32_by(Access ac, const Dev &d, const Launch &L, hipStream_t s, int hist)
+{
+    if (ac == AC_STREAM) return launch_pass32_t<STAGES, AC_STREAM, SORT>(d, L, s, hist);
+    if constexpr (!SORT)
+        if (ac == AC_STORES) return launch_pass32_t<STAGES, AC_STORES>(d, L, s, hist);
+    return launch_pass32_t<STAGES, AC_CACHED, SORT>(d, L, s, hist);
+}
+
+// (L.nt: 0 cached, 1 non-temporal, 2 by size)
+static Access access_of(const Launch &L, bool coll)
+{
+    if (L.nt == 2) return pass32_access(coll, L.ppt, L.lines);
+    return L.nt && coll ? AC_STREAM : AC_CACHED;
 }
 
 // The fused pass that also sorts (after launch_sort_prepare on the previous step's
 // histogram), then the new slot counts and the buffer flip.
-hipError_t launch_pass32_sort(const Dev &d, int ppt, int W, hipStream_t s, bool coll, int64_t cap_tot, int nt)
+hipError_t launch_pass32_sort(const Dev &d, const Launch &L, hipStream_t s, bool coll)
 {
     constexpr int FUSED = PS_PUSH | PS_COLLIDE | PS_DEPOSIT;
     hipError_t e;
-    if (coll && inline_candidates(d, ppt))
-        e = launch_pass32_inl<FUSED, true>(d, ppt, W, s, 0, cap_tot);
-    else if (coll && nt == NT_AUTO)
-        e = launch_pass32_t<FUSED, NT_AUTO, true>(d, ppt, W, s, 0, cap_tot);
-    else if (coll && nt == NT_STREAM)
-        e = launch_pass32_t<FUSED, NT_STREAM, true>(d, ppt, W, s, 0, cap_tot);
+    if (coll && inline_candidates(d, L.ppt))
+        e = launch_pass32_inl<FUSED, true>(d, L, s, 0);
     else if (coll)
-        e = launch_pass32_t<FUSED, NT_CACHED, true>(d, ppt, W, s, 0, cap_tot);
+        e = launch_pass32_by<FUSED, true>(access_of(L, true), d, L, s, 0);
     else
-        e = launch_pass32_t<PS_PUSH | PS_DEPOSIT, NT_CACHED, true>(d, ppt, W, s, 0, cap_tot);
+        e = launch_pass32_t<PS_PUSH | PS_DEPOSIT, AC_CACHED, true>(d, L, s, 0);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_sort_finish, dim3(1), dim3(256), 0, s, d);
     return hipGetLastError();
@@ -962,34 +932,27 @@ hipError_t launch_stream_copy(const void *src, void *dst, int64_t nwords, bool n
 }
 
 
-hipError_t launch_pass32(const Dev &d, int ppt, int W, hipStream_t s, int stages, int hist, int64_t cap_tot, int nt,
-                         bool depo)
+hipError_t launch_pass32(const Dev &d, const Launch &L, hipStream_t s, int stages, int hist, bool depo)
 {
     constexpr int FUSED = PS_PUSH | PS_COLLIDE | PS_DEPOSIT;
-    if ((stages & PS_COLLIDE) && inline_candidates(d, ppt)) {
+    if ((stages & PS_COLLIDE) && inline_candidates(d, L.ppt)) {
         const int rt = (hist ? kHist : 0) | (depo ? 0 : kNoDepo);
-        if (stages == FUSED) return launch_pass32_inl<FUSED, false>(d, ppt, W, s, rt, cap_tot);
-        if (stages == PS_COLLIDE) return launch_pass32_inl<PS_COLLIDE, false>(d, ppt, W, s, rt, cap_tot);
-    }
-    if (stages == FUSED) {
-        if (nt == NT_AUTO) return launch_pass32_t<FUSED, NT_AUTO>(d, ppt, W, s, hist, cap_tot);
-        if (nt == NT_STREAM) return launch_pass32_t<FUSED, NT_STREAM>(d, ppt, W, s, hist, cap_tot);
+        if (stages == FUSED) return launch_pass32_inl<FUSED, false>(d, L, s, rt);
+        if (stages == PS_COLLIDE) return launch_pass32_inl<PS_COLLIDE, false>(d, L, s, rt);
     }
     switch (stages) {
     case PS_PUSH:
-        if (nt == NT_AUTO) return launch_pass32_t<PS_PUSH, NT_AUTO>(d, ppt, W, s, hist, cap_tot);
-        return launch_pass32_t<PS_PUSH>(d, ppt, W, s, hist, cap_tot);
+        return launch_pass32_by<PS_PUSH>(access_of(L, false), d, L, s, hist);
     case PS_COLLIDE:
-        return launch_pass32_t<PS_COLLIDE>(d, ppt, W, s, hist, cap_tot);
+        return launch_pass32_t<PS_COLLIDE>(d, L, s, hist);
     case PS_DEPOSIT:
-        return launch_pass32_t<PS_DEPOSIT>(d, ppt, W, s, hist, cap_tot);
+        return launch_pass32_t<PS_DEPOSIT>(d, L, s, hist);
     case PS_HIST:
-        return launch_pass32_t<PS_HIST>(d, ppt, W, s, hist, cap_tot);
+        return launch_pass32_t<PS_HIST>(d, L, s, hist);
     case FUSED:
-        return launch_pass32_t<FUSED>(d, ppt, W, s, hist, cap_tot);
+        return launch_pass32_by<FUSED>(access_of(L, true), d, L, s, hist);
     case PS_PUSH | PS_DEPOSIT:
-        if (nt == NT_AUTO) return launch_pass32_t<PS_PUSH | PS_DEPOSIT, NT_AUTO>(d, ppt, W, s, hist, cap_tot);
-        return launch_pass32_t<PS_PUSH | PS_DEPOSIT>(d, ppt, W, s, hist, cap_tot);
+        return launch_pass32_by<PS_PUSH | PS_DEPOSIT>(access_of(L, false), d, L, s, hist);
     default:
         return hipErrorInvalidValue;
     }

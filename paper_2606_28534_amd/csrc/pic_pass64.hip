@@ -23,6 +23,7 @@
 #include "pic_device.h"
 #include "pic_kernels.h"
 #include "pic_particle.h"
+#include "pic_rules.h"
 
 namespace pic {
 
@@ -383,7 +384,7 @@ __device__ __forceinline__ void particles_body(const Dev &d, int hist_rt, int64_
     }
 }
 
-template <int STAGES>
+template <int STAGES, bool NT>
 __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T)
 {
     const int64_t t = blockIdx.x;
@@ -391,32 +392,34 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
     const int64_t first = t * blockDim.x * kPpt64;
     const int sg = seg_of_slot(d, first);
     const int64_t last = min(first + (int64_t)blockDim.x * kPpt64, d.seg[sg].base + d.n_slots[sg]);
-    const int b = d.cur[0], nt = d.cur[1];
     if (first >= last) return;
-    // The push streams its particles non-temporally once they outgrow the last-level cache (at
-    // kStreamSlots in use, as the FP32 pass): cached and non-temporal 40.6 and 45.1 us at 4e6, 81
-    // and 88 at 8e6, 145 and 130 at 1.2e7, 485 and 430 at 4e7.  A second form beside the collide
-    // stage's took it above 128 registers (80 -> 97 us at 8e6), so that one stays cached.
-    if (STAGES == ST_PUSH && nt)
-        particles_body<STAGES, true>(d, hist_rt, first, last, sg, b);
-    else
-        particles_body<STAGES, false>(d, hist_rt, first, last, sg, b);
+    particles_body<STAGES, NT>(d, hist_rt, first, last, sg, *d.cur);
 }
 
 // One block per tile of the slot capacity (segment slot ranges are multiples of kSlotAlign,
 // a multiple of every tile).
-hipError_t launch_pass64(const Dev &d, int block, hipStream_t s, int stages, int hist, bool pairs)
+//
+// The push streams its particles non-temporally once they outgrow the last-level cache (pass64_streams):
+// cached and non-temporal 40.6 and 45.1 us at 4e6, 81 and 88 at 8e6, 145 and 130 at 1.2e7, 485 and
+// 430 at 4e7.
+hipError_t launch_pass64(const Dev &d, const Launch &L, hipStream_t s, int stages, int hist, bool pairs)
 {
+    const int block = L.block;
     const int rt = (hist ? kHist64 : 0) | (pairs ? kPairs : 0);
     static_assert(kSlotAlign % (256 * kPpt64) == 0, "whole tiles per segment");
     const int64_t T = d.cap_tot / (block * kPpt64);
     const dim3 g((unsigned)T);
 #define PIC_CASE(ST)                                                                   \
     case ST:                                                                           \
-        hipLaunchKernelGGL((k_particles<ST>), g, dim3(block), 0, s, d, rt, T);         \
+        hipLaunchKernelGGL((k_particles<ST, false>), g, dim3(block), 0, s, d, rt, T);  \
         break;
     switch (stages) {
-        PIC_CASE(ST_PUSH)
+    case ST_PUSH:
+        if (pass64_streams(L.lines))
+            hipLaunchKernelGGL((k_particles<ST_PUSH, true>), g, dim3(block), 0, s, d, rt, T);
+        else
+            hipLaunchKernelGGL((k_particles<ST_PUSH, false>), g, dim3(block), 0, s, d, rt, T);
+        break;
         PIC_CASE(ST_COLLIDE)
         PIC_CASE(ST_DEPOSIT)
         PIC_CASE(ST_HIST)
