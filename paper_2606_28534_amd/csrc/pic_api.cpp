@@ -2098,7 +2098,7 @@ int pic_load(pic_ctx *c, const void *host_buf, size_t bytes, void *stream)
     HIPC(c, h2d(d.sums, (size_t)kCntStripes * c->P.nseg * S_NSUM * 8));
     HIPC(c, hipMemsetAsync(d.ssum, 0, (size_t)2 * kCntStripes * c->P.nseg * T_NSTEP * 8, s));
     const int32_t zero = 0;
-    HIPC(c, hipMemcpyAsync(d.n_slots, ns.data(), ns.size() * 8, hipMemcpyHostToDevice, s));
+    HIPC(c, hipMemcpyAsync(d.n_slots, ns.data(), (size_t)c->P.nseg * 8, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.next_id, ids.data(), ids.size() * 4, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.cur, &zero, 4, hipMemcpyHostToDevice, s));
     HIPC(c, hipMemcpyAsync(d.vcur, &zero, 4, hipMemcpyHostToDevice, s));
