@@ -840,11 +840,14 @@ __global__ void k_sort_finish(Dev d)
 constexpr int kCountWindowMax = 1024;
 
 // The candidates are collided inside the pass in runs of at most kInlineTiles tiles of slot
-// capacity.  There the candidates' own launch, a chain of round trips behind the pass's, costs
-// more than what the collisions' registers (fewer waves per SIMD) and divergence cost the pass:
-// per fused step 29.3 us with the launch and 25.3 without at 108 tiles, 37.9 and 29.0 at 789, 61.2
-// and 49.8 at 3914, 73.8 and 67.0 at 7820, 103.3 and 101.4 at 15633 (half of each in use).  The
-// pass over 4e7 particles lost 45 us per step to it.
+// capacity, which is 1.7e7 slots with four particles a thread and 3.4e7 with eight.  There the
+// candidates' own launch, a chain of round trips behind the pass's, costs more than what the
+// collisions' registers (fewer waves per SIMD) and divergence cost the pass.  Per fused step with the
+// launch and without, by slots in use, both sides with the access that pass32_access gives them:
+// four a thread 29.3 and 25.3 us at 108 tiles, 37.9 and 29.0 at 789, 75.3 and 68.8 at 5e6 slots,
+// 103.0 and 99.5 at 9e6, 120.9 and 118.5 at 1.1e7, 150.5 and 150.2 at 1.5e7, 192 and 191 at 2e7, 267 and 270 at
+// 3e7; eight 81.1 and 66.3 at 5e6, 109 and 97 at 9e6, 156 and 154 at 1.5e7, 181 and 196 at 1.8e7, 208 and 220
+// at 2e7, 258 and 249 at 2.4e7, 310 and 303 at 3e7.
 constexpr int64_t kInlineTiles = 16384;
 bool inline_candidates(const Dev &d, int ppt) { return d.cap_tot / (256 * ppt) <= kInlineTiles; }
 
@@ -855,29 +858,32 @@ static hipError_t launch_pass32_t(const Dev &d, const Launch &L, hipStream_t s, 
     const size_t lds = (size_t)W * 8 + (SORT ? (size_t)W * 4 : 0);
     const int64_t T = d.cap_tot / (256 * L.ppt);
     const dim3 G((unsigned)((T + 7) / 8 * 8));
+    // (pass32_access never asks for non-temporal stores alone with collisions and four a thread)
+    constexpr int AC4 = AC == AC_STORES && (STAGES & PS_COLLIDE) ? AC_STREAM : AC;
     if (L.ppt == 4)
-        hipLaunchKernelGGL((k_pass32<STAGES, 4, AC, SORT, INL>), G, dim3(256), lds, s, d, W, hist, T);
+        hipLaunchKernelGGL((k_pass32<STAGES, 4, AC4, SORT, INL>), G, dim3(256), lds, s, d, W, hist, T);
     else
         hipLaunchKernelGGL((k_pass32<STAGES, 8, AC, SORT, INL>), G, dim3(256), lds, s, d, W, hist, T);
     return hipGetLastError();
 }
 
-// A pass with the COLLIDE stage that also collides its candidates.
+// A push by the access the run calls for (with SORT the stores scatter, so only its loads count).
+template <int STAGES, bool SORT = false, int INL = INL_NO>
+static hipError_t launch_pass32_by(Access ac, const Dev &d, const Launch &L, hipStream_t s, int hist)
+{
+    if (ac == AC_STREAM) return launch_pass32_t<STAGES, AC_STREAM, SORT, INL>(d, L, s, hist);
+    if constexpr (!SORT)
+        if (ac == AC_STORES) return launch_pass32_t<STAGES, AC_STORES, SORT, INL>(d, L, s, hist);
+    return launch_pass32_t<STAGES, AC_CACHED, SORT, INL>(d, L, s, hist);
+}
+
+// A fused pass that also collides its candidates.
 template <int STAGES, bool SORT>
 static hipError_t launch_pass32_inl(const Dev &d, const Launch &L, hipStream_t s, int hist)
 {
-    if (d.any_cx_rel) return launch_pass32_t<STAGES, AC_CACHED, SORT, INL_CXREL>(d, L, s, hist);
-    return launch_pass32_t<STAGES, AC_CACHED, SORT, INL_YES>(d, L, s, hist);
-}
-
-// A push by the access the run calls for (with SORT the stores scatter, so only its loads count).
-template <int STAGES, bool SORT = false>
-static hipError_t launch_pass32_by(Access ac, const Dev &d, const Launch &L, hipStream_t s, int hist)
-{
-    if (ac == AC_STREAM) return launch_pass32_t<STAGES, AC_STREAM, SORT>(d, L, s, hist);
-    if constexpr (!SORT)
-        if (ac == AC_STORES) return launch_pass32_t<STAGES, AC_STORES>(d, L, s, hist);
-    return launch_pass32_t<STAGES, AC_CACHED, SORT>(d, L, s, hist);
+    const Access ac = pass32_access(true, L.ppt, L.lines);
+    if (d.any_cx_rel) return launch_pass32_by<STAGES, SORT, INL_CXREL>(ac, d, L, s, hist);
+    return launch_pass32_by<STAGES, SORT, INL_YES>(ac, d, L, s, hist);
 }
 
 // (L.nt: 0 cached, 1 non-temporal, 2 by size)
@@ -938,7 +944,9 @@ hipError_t launch_pass32(const Dev &d, const Launch &L, hipStream_t s, int stage
     if ((stages & PS_COLLIDE) && inline_candidates(d, L.ppt)) {
         const int rt = (hist ? kHist : 0) | (depo ? 0 : kNoDepo);
         if (stages == FUSED) return launch_pass32_inl<FUSED, false>(d, L, s, rt);
-        if (stages == PS_COLLIDE) return launch_pass32_inl<PS_COLLIDE, false>(d, L, s, rt);
+        if (stages == PS_COLLIDE)
+            return d.any_cx_rel ? launch_pass32_t<PS_COLLIDE, AC_CACHED, false, INL_CXREL>(d, L, s, rt)
+                                : launch_pass32_t<PS_COLLIDE, AC_CACHED, false, INL_YES>(d, L, s, rt);
     }
     switch (stages) {
     case PS_PUSH:
