@@ -160,11 +160,15 @@ typedef struct {
                             its own cells, so this bounds LDS per block; 0 = default 2048   */
     int32_t ppt;         /* particles per thread of the FP32 pass (4 or 8); 0 = default    */
     int32_t sort_ppt;    /* particles per thread of the FP32 sort scatter; 0 = default     */
-    int32_t nontemporal; /* bit 0: the fused FP32 pass always streams particles with
-                          * non-temporal loads and stores (without it, it does so only while
-                          * more particles are in use than the last-level cache holds, as
-                          * the FP64 push does; no result changes); bit 1: the FP32 sort scatter reads its input
-                          * with non-temporal loads; 0 = default                           */
+    int32_t nontemporal; /* no result changes.  Bit 0: the fused FP32 pass of a collisional
+                          * run always moves the particles with non-temporal accesses where
+                          * its collision candidates go to a launch of their own (above
+                          * 16384 tiles of 256 x ppt slots of capacity).  Everywhere else, and
+                          * without the bit, the FP32 passes and the FP64 push do so from as many
+                          * slots in use on as the last-level cache holds (1e7 to 2.1e7, by the
+                          * pass), as the library last saw them when a call waited for the run.
+                          * Bit 1: the FP32 sort scatter reads its input with non-temporal
+                          * loads.  0 = default                                            */
     int32_t smooth;      /* passes (0..4) of the 1-2-1 density filter applied to rho before
                           * every solve (R23): periodic grids wrap, bounded grids mirror at
                           * the walls; 0 = off                                              */
@@ -265,7 +269,9 @@ int pic_step(pic_ctx *ctx, int32_t nsteps, void *stream);
  * graph per window of up to K steps: whole sort cycles from whatever phase of the cycle
  * the run is in, then a shorter tail, which replays from a graph only if this call
  * prepared it (otherwise those steps run eagerly).  Graphs stay valid until pic_load,
- * pic_autotune or pic_free.  A no-op for cfg.fused = 0. */
+ * pic_autotune or pic_free; a run whose slots in use have since reached or left a size from
+ * which its particles are streamed (see nontemporal) captures its windows anew.  A no-op for
+ * cfg.fused = 0. */
 int pic_graph_prepare(pic_ctx *ctx, int32_t nsteps);
 
 /* Number of graph replays pic_step has made on this context (so a caller can tell that a

@@ -776,7 +776,7 @@ Launch default_launch(const pic_config *cfg, const Plan &P)
     L.ppt = 4;  // particles per thread of the FP32 pass (4 or 8; the autotuner may change it)
     if (cfg->precision == PIC_FP32_CELLOFF && (cfg->ppt == 4 || cfg->ppt == 8)) L.ppt = cfg->ppt;
     L.sort_ppt = (cfg->sort_ppt == 4 || cfg->sort_ppt == 8) ? cfg->sort_ppt : 4;
-    L.nt = (cfg->nontemporal & 1) ? 1 : 2;
+    L.nt = (cfg->nontemporal & 1) ? 1 : 0;
     L.sort_nt = (cfg->nontemporal & 2) ? 1 : 0;
     L.lines = 0;
     int64_t tiles = 0;
@@ -1885,7 +1885,7 @@ int pic_autotune(pic_ctx *c, int32_t trial_steps, int32_t *shape, void *stream)
         shape[0] = c->L.ppt;
         shape[1] = c->L.window;
         shape[2] = c->L.sort_ppt;
-        shape[3] = c->L.nt == 1 ? 1 : 0;
+        shape[3] = c->L.nt;
         shape[4] = c->L.sort_nt;
     }
     return check_err(c, s);

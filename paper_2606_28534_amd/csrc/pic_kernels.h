@@ -13,7 +13,7 @@ struct Launch {
     int grid;    // the FP64 sort scatter's blocks / 8 (a multiple of 8 for the XCD-aware mapping)
     int window;  // widest LDS window span, in cells, of the FP32 pass and of the sorts
     int sort_ppt;  // particles per thread of the FP32 sort scatter
-    int nt;        // fused FP32 pass: particle loads and stores cached (0), non-temporal (1) or by size (2)
+    int nt;        // fused FP32 pass with collisions: particle loads and stores by size (0), always non-temporal (1)
     int lines;     // of kStreamSlots, reached by the slots in use as the host last saw them
     int sort_nt;   // FP32 sort scatter: non-temporal loads
 };

@@ -881,16 +881,9 @@ static hipError_t launch_pass32_by(Access ac, const Dev &d, const Launch &L, hip
 template <int STAGES, bool SORT>
 static hipError_t launch_pass32_inl(const Dev &d, const Launch &L, hipStream_t s, int hist)
 {
-    const Access ac = pass32_access(true, L.ppt, L.lines);
+    const Access ac = pass32_access(true, true, L.ppt, L.lines, L.nt != 0);
     if (d.any_cx_rel) return launch_pass32_by<STAGES, SORT, INL_CXREL>(ac, d, L, s, hist);
     return launch_pass32_by<STAGES, SORT, INL_YES>(ac, d, L, s, hist);
-}
-
-// (L.nt: 0 cached, 1 non-temporal, 2 by size)
-static Access access_of(const Launch &L, bool coll)
-{
-    if (L.nt == 2) return pass32_access(coll, L.ppt, L.lines);
-    return L.nt && coll ? AC_STREAM : AC_CACHED;
 }
 
 // The fused pass that also sorts (after launch_sort_prepare on the previous step's
@@ -902,7 +895,7 @@ hipError_t launch_pass32_sort(const Dev &d, const Launch &L, hipStream_t s, bool
     if (coll && inline_candidates(d, L.ppt))
         e = launch_pass32_inl<FUSED, true>(d, L, s, 0);
     else if (coll)
-        e = launch_pass32_by<FUSED, true>(access_of(L, true), d, L, s, 0);
+        e = launch_pass32_by<FUSED, true>(pass32_access(true, false, L.ppt, L.lines, L.nt != 0), d, L, s, 0);
     else
         e = launch_pass32_t<PS_PUSH | PS_DEPOSIT, AC_CACHED, true>(d, L, s, 0);
     if (e != hipSuccess) return e;
@@ -950,7 +943,7 @@ hipError_t launch_pass32(const Dev &d, const Launch &L, hipStream_t s, int stage
     }
     switch (stages) {
     case PS_PUSH:
-        return launch_pass32_by<PS_PUSH>(access_of(L, false), d, L, s, hist);
+        return launch_pass32_by<PS_PUSH>(pass32_access(false, false, L.ppt, L.lines, L.nt != 0), d, L, s, hist);
     case PS_COLLIDE:
         return launch_pass32_t<PS_COLLIDE>(d, L, s, hist);
     case PS_DEPOSIT:
@@ -958,9 +951,9 @@ hipError_t launch_pass32(const Dev &d, const Launch &L, hipStream_t s, int stage
     case PS_HIST:
         return launch_pass32_t<PS_HIST>(d, L, s, hist);
     case FUSED:
-        return launch_pass32_by<FUSED>(access_of(L, true), d, L, s, hist);
+        return launch_pass32_by<FUSED>(pass32_access(true, false, L.ppt, L.lines, L.nt != 0), d, L, s, hist);
     case PS_PUSH | PS_DEPOSIT:
-        return launch_pass32_by<PS_PUSH | PS_DEPOSIT>(access_of(L, false), d, L, s, hist);
+        return launch_pass32_by<PS_PUSH | PS_DEPOSIT>(pass32_access(false, false, L.ppt, L.lines, L.nt != 0), d, L, s, hist);
     default:
         return hipErrorInvalidValue;
     }

@@ -29,9 +29,12 @@ inline int stream_lines(int64_t slots)
 // at 1.5e7, 107.7, 102 and 124 at 1.6e7, 162.8, 158 and 153 at 2e7; the pass without collisions turns at
 // the same sizes.  A kernel that held more than one form and chose by itself cost every tile (70.5 ->
 // 71.7 to 75.4 us a pass at 9.2e6 particles, or folded them into one), so the host chooses, from the
-// slots in use as it last saw them (where it waits for the run).
-inline Access pass32_access(bool coll, int ppt, int lines)
+// slots in use as it last saw them (where it waits for the run).  `always` (bit 0 of `nontemporal`)
+// streams at any size where the fused pass leaves its candidates to a launch behind it; everywhere
+// else small runs lost to it (the pass with candidates inside up to 18%), and the size decides.
+inline Access pass32_access(bool coll, bool inside, int ppt, int lines, bool always)
 {
+    if (always && coll && !inside) return AC_STREAM;
     if (ppt == 4 && coll) return lines >= 1 ? AC_STREAM : AC_CACHED;
     if (ppt == 4) return lines >= 3 ? AC_STREAM : lines >= 2 ? AC_STORES : AC_CACHED;
     return lines >= 4 ? AC_STREAM : lines >= 2 ? AC_STORES : AC_CACHED;

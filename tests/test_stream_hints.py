@@ -70,11 +70,14 @@ def test_fp64_push(kernels):
 
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
-    """The host's rules, compiled for the CPU: slots -> lines, (coll, ppt, lines) -> access."""
+    """The host's rules, compiled for the CPU: slots -> lines, (coll, inside, ppt, lines, always) -> access."""
     tmp = tmp_path_factory.mktemp("rules")
     (tmp / "r.cpp").write_text('''#include "pic_rules.h"
 extern "C" int lines(long n) { return pic::stream_lines(n); }
-extern "C" int access(int coll, int ppt, int lines) { return pic::pass32_access(coll != 0, ppt, lines); }
+extern "C" int access(int coll, int inside, int ppt, int lines, int always)
+{
+    return pic::pass32_access(coll != 0, inside != 0, ppt, lines, always != 0);
+}
 extern "C" int push64(int lines) { return pic::pass64_streams(lines); }
 ''')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", build.CSRC, str(tmp / "r.cpp"), "-o",
@@ -82,12 +85,25 @@ extern "C" int push64(int lines) { return pic::pass64_streams(lines); }
     return ctypes.CDLL(str(tmp / "r.so"))
 
 
-@pytest.mark.parametrize("coll,ppt,stores,stream", [(1, 4, 10_000_000, 10_000_000), (0, 4, 14_000_000, 16_500_000),
-                                                    (1, 8, 14_000_000, 21_000_000), (0, 8, 14_000_000, 21_000_000)])
-def test_choice_by_size(rules, coll, ppt, stores, stream):
+SIZES = [(1, 4, 10_000_000, 10_000_000), (0, 4, 14_000_000, 16_500_000), (1, 8, 14_000_000, 21_000_000),
+         (0, 8, 14_000_000, 21_000_000)]
+
+
+@pytest.mark.parametrize("coll,ppt,stores,stream", SIZES)
+@pytest.mark.parametrize("inside", [0, 1])
+def test_choice_by_size(rules, coll, ppt, stores, stream, inside):
     for n in (0, 1, stores - 1, stores, stream - 1, stream, 2**32 - 1):
         want = STREAM if n >= stream else STORES if n >= stores else CACHED
-        assert rules.access(coll, ppt, rules.lines(ctypes.c_long(n))) == want, n
+        assert rules.access(coll, inside, ppt, rules.lines(ctypes.c_long(n)), 0) == want, n
+
+
+@pytest.mark.parametrize("coll,ppt,stores,stream", SIZES)
+@pytest.mark.parametrize("inside", [0, 1])
+def test_the_option_never_streams_less(rules, coll, ppt, stores, stream, inside):
+    for n in (0, stores, stream):
+        lines = rules.lines(ctypes.c_long(n))
+        got = rules.access(coll, inside, ppt, lines, 1)
+        assert got == (STREAM if coll and not inside else rules.access(coll, inside, ppt, lines, 0)), n
 
 
 def test_choice_of_the_fp64_push(rules):
