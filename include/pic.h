@@ -370,11 +370,12 @@ int pic_adjoint_window_noalloc(pic_ctx *ctx, int32_t nsteps, int32_t ckpt_every,
                                double *dW_dvx, int64_t dvx_len, double *dW_dEext, void *stream);
 
 /* The library's autotuner: times the particle pass over `trial_steps` steps for every
- * candidate launch shape (particles per thread x widest LDS window span x, for the fused
- * pass, non-temporal streaming) and the sort scatter for each particles-per-thread and
+ * candidate launch shape (particles per thread x widest LDS window span x, where bit 0 of
+ * `nontemporal` makes a difference, that bit; in the fused step together with the launch
+ * behind the pass) and the sort scatter for each particles-per-thread and
  * non-temporal-load choice, all with HIP events on `stream`, keeps the fastest, and
- * writes {ppt, window, sort_ppt, pass non-temporal, sort non-temporal} to `shape`
- * (5 ints, may be NULL).  The trial steps advance the
+ * writes {ppt, window, sort_ppt, bit 0 and bit 1 of nontemporal} to `shape`
+ * (5 ints, may be NULL): a context created with these runs the same launches.  The trial steps advance the
  * run like pic_step (the sort is repeated on already-sorted data, which leaves the state
  * unchanged apart from slot order). */
 int pic_autotune(pic_ctx *ctx, int32_t trial_steps, int32_t *shape, void *stream);

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <optional>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -386,6 +387,7 @@ struct pic_ctx {
     std::string msg;
     // measurement hook
     bool timing = false;
+    bool tuning = false;  // the timed interval of a fused step ends behind the launch after the pass
     std::vector<hipEvent_t> ev;  // pairs
     int64_t ev_used = 0;
 };
@@ -566,11 +568,10 @@ hipError_t enqueue_step(pic_ctx *c, hipStream_t s, int64_t n, bool &ready, bool 
         else
             e = launch_particles(d, c->L, s, f64, stages, hist, false);
         if (e != hipSuccess) return e;
-        if (tm) {
-            if ((e = hipEventRecord(c->ev[c->ev_used + 1], s)) != hipSuccess) return e;
-            c->ev_used += 2;
-        }
+        if (tm && !c->tuning && (e = hipEventRecord(c->ev[c->ev_used + 1], s)) != hipSuccess) return e;
         if ((e = launch_after_pass(c, s, hist)) != hipSuccess) return e;
+        if (tm && c->tuning && (e = hipEventRecord(c->ev[c->ev_used + 1], s)) != hipSuccess) return e;
+        if (tm) c->ev_used += 2;
         if (coll) {
             if ((e = launch_births(d, f64, true, true, s)) != hipSuccess) return e;
         } else if (!adv_in_solve && (e = launch_advance(d, s)) != hipSuccess) {
@@ -1793,15 +1794,26 @@ int pic_autotune(pic_ctx *c, int32_t trial_steps, int32_t *shape, void *stream)
         const int ppts[2] = {4, 8};
         const int wins[3] = {1024, 2048, 4096};
         const bool verbose = std::getenv("PIC_AUTOTUNE_VERBOSE") != nullptr;
-        // candidates: particles per thread x LDS window x (fused pass only) non-temporal
-        // streaming; two rounds in opposite orders; a candidate's score is the sum of its
-        // two median per-launch pass times, so drift of the run's state between trials
-        // cancels
-        const int ncand = c->cfg.fused ? 12 : 6;
+        // candidates: particles per thread x LDS window x streaming by size or always (where the
+        // choice is one: the fused pass with its candidates in the launch behind it); two rounds in
+        // opposite orders; a candidate's score is the sum of its two median times of the pass (in the
+        // fused step with the launch behind it, since it decides what is left to that one), so drift
+        // of the run's state between trials cancels
+        const int ncand = 12;
+        const auto is_one = [&](int ci) {
+            return ci < 6 || (c->cfg.fused && c->cfg.collisions && !inline_candidates(c->d, ppts[(ci % 6) / 3]));
+        };
+        struct Tuning {
+            bool &on;
+            explicit Tuning(bool &b) : on(b) { on = true; }
+            ~Tuning() { on = false; }
+        };
+        std::optional<Tuning> tuning(std::in_place, c->tuning);
         double score[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         for (int round = 0; round < 2; ++round) {
             for (int q = 0; q < ncand; ++q) {
                 const int ci = round == 0 ? q : ncand - 1 - q;
+                if (!is_one(ci)) continue;
                 c->L.ppt = ppts[(ci % 6) / 3];
                 c->L.window = wins[ci % 3];
                 c->L.nt = ci / 6;
@@ -1836,7 +1848,7 @@ int pic_autotune(pic_ctx *c, int32_t trial_steps, int32_t *shape, void *stream)
         Launch bestL = c->L;
         double best = 1e300;
         for (int ci = 0; ci < ncand; ++ci) {
-            if (score[ci] < best) {
+            if (is_one(ci) && score[ci] < best) {
                 best = score[ci];
                 bestL.ppt = ppts[(ci % 6) / 3];
                 bestL.window = wins[ci % 3];
@@ -1844,6 +1856,7 @@ int pic_autotune(pic_ctx *c, int32_t trial_steps, int32_t *shape, void *stream)
             }
         }
         c->L = bestL;
+        tuning.reset();
         pic_timing(c, 0);
         // sort scatter: particles per thread x non-temporal streaming, each timed on one
         // histogram + sort after a few steps of motion since the last sort
