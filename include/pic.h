@@ -186,7 +186,8 @@ typedef struct {
     double wall_ke[2][2];        /* absorbed 1/2 m w |v|^2                                  */
     int64_t coll[3];             /* e-elastic, e-ionisation, ion CX events (cumulative)     */
     int64_t created[2];          /* particles created per species (cumulative)              */
-    int64_t pushes;              /* particles pushed, summed over steps (cumulative)        */
+    int64_t pushes;              /* particles pushed, summed over steps (cumulative); a step of
+                                    an adjoint window counts twice (see there)              */
     int64_t step;                /* steps taken                                             */
     double numax[2];             /* null-collision frequency bound of the last collide     */
     double emax;                 /* max |E| of the last solved / set field                  */
@@ -349,7 +350,10 @@ int pic_adjoint_query(pic_ctx *ctx, int32_t nsteps, int32_t ckpt_every, size_t *
  * recomputes each segment forward before its reverse sweep.  Requires one ensemble, one
  * periodic species, no collisions, B = 0 and the FP32 form; no sort runs inside the
  * window.  dW_dvx (host, length >= particle count) is indexed by particle id.  On return
- * the particle state is the final state of the window.  Synchronises `stream`. */
+ * the particle state is the final state of the window.  The push counter grows by two per
+ * particle and step on every grid, one of the forward sweep and one of the recomputation,
+ * also where the forward sweep kept the states and small grids save the second.
+ * Synchronises `stream`. */
 int pic_adjoint_window(pic_ctx *ctx, int32_t nsteps, int32_t ckpt_every, void *scratch,
                        size_t bytes, double *W, double *dW_dvx, int64_t dvx_len,
                        double *dW_dEext, void *stream);

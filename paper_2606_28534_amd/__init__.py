@@ -344,7 +344,8 @@ class Sim:
     def moments(self, ens=0):
         """Node moments (reading R27) of each species of ensemble `ens`: a list of dicts
         with n, ux, uy, uz, T per node (host arrays), computed by the library's kernels
-        into a device buffer through pic_diag."""
+        into a device buffer through pic_diag.  They are rows of one array (copy one to keep
+        it without the others)."""
         import torch
 
         nn = self.nnodes(ens)
@@ -397,6 +398,8 @@ class Sim:
             self.set_particles(ens, s, st["x"], st["vx"], st["vy"], st["vz"], st["id"], st["next_id"])
 
     def grid(self, ens=0):
+        """Node arrays Q (per species), rho, phi and E of ensemble `ens`.  They are rows of one
+        array (copy one to keep it without the others)."""
         nn = self.nnodes(ens)
         # rows of one array: the library copies arrays that follow one another in one piece
         Q0, Q1, rho, phi, E = np.empty((5, nn))

@@ -28,7 +28,11 @@ namespace pic {
 // the field adjoint that one step adds up are read by the next from another buffer, while the
 // third of the three is cleared.  On the 2048-cell, 409,600-particle window a forward step took
 // 10.8 + 6.4 us in the run's two kernels (and three copies where it is recorded) and takes 9.6, a
-// reverse step 17.8 + 13.3 + 5.7 us in the three kernels of larger grids and takes 10.5.
+// reverse step 17.8 + 13.3 + 5.7 us in the three kernels of larger grids and takes 10.5.  However
+// many particles such a grid holds this is the faster way: a window of 40 steps with a
+// checkpoint every 10 takes, in the general sweep and here, 3.5 and 1.0 ms for 1e5 particles in 250
+// cells, 13.9 and 2.5 for 1e6, 30 and 4.3 for 2e6, 144 and 15.8 for 8e6; in 4000 cells 3.9 and 1.6 ms for
+// 1e5, 6.0 and 2.6 for 1e6, 10.5 and 4.9 for 2e6, 44 and 19.5 for 8e6.
 // =======================================================================================
 template <int G>
 struct AdjTile {

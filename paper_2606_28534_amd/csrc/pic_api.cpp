@@ -1619,7 +1619,8 @@ int adj_sweep_small(pic_ctx *c, const AdjLayout &A, char *base, int nsteps, int 
         const int i = t % C;
         const bool rec = k == A.nseg_ck - 1;
         const AdjState in = rec && i > 0 ? at(k, i) : run, out = rec && t + 1 < nsteps ? at(k, i + 1) : run;
-        // (a sweep counts every particle's pushes twice, also where it keeps the states)
+        // (the window's count is two pushes per particle and step on every grid: the general sweep
+        // recomputes each step, and what is saved here does not change what is reported)
         HIPC(c, launch_adj_fwd(dd, in, out, keep ? ck(k) : none, keep ? ckQ(k) : nullptr, ring[(t + 1) % 3],
                                ring[(t + 2) % 3], rec ? Eb + (int64_t)i * nn : nullptr, nslots, 2, s));
     }
