@@ -313,7 +313,7 @@ int pic_set_particles(pic_ctx *ctx, int32_t ens, int32_t species, pic_particles 
 
 /* Copy node arrays of ensemble `ens` to host (each may be NULL; length = node count):
  * Q_s as particle units, rho, phi, E (self-consistent part).  Arrays that follow one another
- * in memory in this order are copied in one piece. */
+ * in memory in this order are copied in pieces of several. */
 int pic_get_grid(pic_ctx *ctx, int32_t ens, double *Q0, double *Q1, double *rho, double *phi,
                  double *E, void *stream);
 

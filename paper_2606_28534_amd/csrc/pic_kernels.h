@@ -100,7 +100,7 @@ hipError_t launch_diag(const Dev &d, bool f64, int sg, double *out, int grid, hi
 // memory the device can write.
 hipError_t launch_diag_pack(const Dev &d, int en, bool tallied, const double *v2, int ngrid, DiagPack *out,
                             hipStream_t s);
-hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, double *out, hipStream_t s);
+hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, bool fields, double *out, hipStream_t s);
 hipError_t launch_err_out(const Dev &d, int32_t *out, int64_t *slots, hipStream_t s);
 // Node moments of segment sg (reading R27) into out[5][nn] (n, ux, uy, uz, T); nn is the
 // node count of the segment's ensemble.  `out` is device memory the launch overwrites.

@@ -1683,9 +1683,10 @@ __global__ void __launch_bounds__(kDiagThreads) k_diag_pack(Dev d, int en, int t
     }
 }
 
-// Node arrays of ensemble `en` as doubles: out[0..1] Q per species (particle units), rho, phi, E.
+// Node arrays of ensemble `en` as doubles: out[0..1] Q per species (particle units) and, with `fields`,
+// rho, phi, E.
 template <bool F64>
-__global__ void __launch_bounds__(256) k_grid_pack(Dev d, int en, double *out)
+__global__ void __launch_bounds__(256) k_grid_pack(Dev d, int en, int fields, double *out)
 {
     const EnsC &e = d.ens[en];
     const int64_t nn = e.nnodes, g = e.gbase;
@@ -1701,6 +1702,7 @@ __global__ void __launch_bounds__(256) k_grid_pack(Dev d, int en, double *out)
         }
         out[j] = q0;
         out[nn + j] = q1;
+        if (!fields) continue;
         out[2 * nn + j] = d.rho[g + j];
         out[3 * nn + j] = d.phi[g + j];
         out[4 * nn + j] = d.E[g + j];
@@ -1967,13 +1969,13 @@ hipError_t launch_diag_pack(const Dev &d, int en, bool tallied, const double *v2
     return hipGetLastError();
 }
 
-hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, double *out, hipStream_t s)
+hipError_t launch_grid_pack(const Dev &d, bool f64, int en, int64_t nn, bool fields, double *out, hipStream_t s)
 {
     const dim3 g((unsigned)std::min<int64_t>((nn + 255) / 256, 1024));
     if (f64)
-        hipLaunchKernelGGL(k_grid_pack<true>, g, dim3(256), 0, s, d, en, out);
+        hipLaunchKernelGGL(k_grid_pack<true>, g, dim3(256), 0, s, d, en, fields ? 1 : 0, out);
     else
-        hipLaunchKernelGGL(k_grid_pack<false>, g, dim3(256), 0, s, d, en, out);
+        hipLaunchKernelGGL(k_grid_pack<false>, g, dim3(256), 0, s, d, en, fields ? 1 : 0, out);
     return hipGetLastError();
 }
 
