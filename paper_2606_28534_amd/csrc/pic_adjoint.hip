@@ -395,12 +395,12 @@ __global__ void __launch_bounds__(256) k_adj_a(Dev d, const int32_t *xc, const f
     for (int k = 0; k < PPT; ++k) {
         const int64_t i = i0 + k;
         if (i >= n) break;
-        const int j = xc[i];
-        if (j < 0) continue;  // a slot the push dropped as non-finite (the call reports it)
+        // a slot the push dropped as non-finite (the call reports it) holds no cell and adds nothing
+        const int c = xc[i], j = max(c, 0);
         const double f = (double)xo[i];
         const int j1 = (j + 1 == N) ? 0 : j + 1;
         const double lvn = lv[i] + dt * lx[i];
-        const double la = dt * qm * lvn;
+        const double la = c < 0 ? 0.0 : dt * qm * lvn;
         lv[i] = lvn;
         lx[i] += la * (E[j1] - E[j]) / dx;
         ext += la;
@@ -435,8 +435,7 @@ __global__ void __launch_bounds__(256) k_adj_b(const int32_t *xc, const double *
     for (int k = 0; k < PPT; ++k) {
         const int64_t i = i0 + k;
         if (i >= n) break;
-        const int j = xc[i];
-        if (j < 0) continue;
+        const int j = max(xc[i], 0);  // (a dropped slot's lx is not used)
         const int j1 = (j + 1 == N) ? 0 : j + 1;
         lx[i] += (lQ[j1] - lQ[j]) / dx;
     }
