@@ -163,10 +163,11 @@ typedef struct {
     int32_t nontemporal; /* no result changes.  Bit 0: the fused FP32 pass of a collisional
                           * run always moves the particles with non-temporal accesses where
                           * its collision candidates go to a launch of their own (above
-                          * 16384 tiles of 256 x ppt slots of capacity).  Everywhere else, and
-                          * without the bit, the FP32 passes and the FP64 push do so from as many
-                          * slots in use on as the last-level cache holds (1e7 to 2.1e7, by the
-                          * pass), as the library last saw them when a call waited for the run.
+                          * 16384 tiles of 256 x ppt slots of capacity).  Otherwise the FP32
+                          * passes that push (the collisionless one that also sorts apart) and
+                          * the FP64 push stage do so once more particles are in use than the
+                          * last-level cache holds (1e7 to 2.1e7, by the pass), as the library
+                          * last saw them when a call waited for the run.
                           * Bit 1: the FP32 sort scatter reads its input with non-temporal
                           * loads.  0 = default                                            */
     int32_t smooth;      /* passes (0..4) of the 1-2-1 density filter applied to rho before

@@ -401,7 +401,7 @@ __global__ void __launch_bounds__(256) k_particles(Dev d, int hist_rt, int64_t T
 //
 // The push streams its particles non-temporally once they outgrow the last-level cache (pass64_streams):
 // cached and non-temporal 40.6 and 45.1 us at 4e6, 81 and 88 at 8e6, 145 and 130 at 1.2e7, 485 and
-// 430 at 4e7.
+// 430 at 4e7.  The other stages read far less and write next to nothing in place.
 hipError_t launch_pass64(const Dev &d, const Launch &L, hipStream_t s, int stages, int hist, bool pairs)
 {
     const int block = L.block;
