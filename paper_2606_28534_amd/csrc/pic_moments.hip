@@ -87,7 +87,7 @@ __device__ __forceinline__ void mom_load(const Dev &d, const SegC &S, int b, int
 }
 
 // acc: [kMomQ][nn] of this segment's ensemble, zeroed by the caller.  On the sheath slab ten
-// steps after its load (2e7 particles of a species, 1e5 cells) it takes 123 us, 3.3 TB/s of the
+// steps after its load (2e7 particles of a species, 1e5 cells) it takes 117 us, 3.4 TB/s of the
 // 20 B a particle read; with one atomic per particle, node and quantity on a single copy of
 // each node it took 711 us.
 template <bool F64>
